@@ -1076,6 +1076,9 @@ __global__ __launch_bounds__(G * rows_per_wg<G>()) __attribute__((amdgpu_waves_p
 void k_num(NumArgs a) {
     constexpr int RPW = rows_per_wg<G>();
     constexpr int KB = sizeof(T) == 8 ? FLAT_KB_F64 : FLAT_KB_F32;
+    // sums in FP64 up to the tier that acc_bytes names (its lanes per row)
+    using V = std::conditional_t<(G <= 256), double, T>;
+    static_assert(ACC64_TIER == 6, "tiers up to 6 have groups of at most 256 lanes");
     extern __shared__ __align__(16) uint32_t smem[];
     __shared__ int red[48];
     const int bytes = tier_bytes(a.tier);
@@ -1127,16 +1130,16 @@ void k_num(NumArgs a) {
     uint2* l1 = reinterpret_cast<uint2*>(tab);
     uint2* cm = l1 + w1;
     int4* slots = reinterpret_cast<int4*>(tab);
-    T* vals;
+    V* vals;
     int TT = 0, logT = 0;
     if constexpr (MODE == MODE_DIRECT) {
-        vals = reinterpret_cast<T*>(tab + align8((int64_t)words * 8));
+        vals = reinterpret_cast<V*>(tab + align8((int64_t)words * 8));
     } else if constexpr (MODE == MODE_TWOLEVEL) {
-        vals = reinterpret_cast<T*>(tab + align8((int64_t)w1 * 8 + (int64_t)nb * 8));
+        vals = reinterpret_cast<V*>(tab + align8((int64_t)w1 * 8 + (int64_t)nb * 8));
     } else {
         TT = (int)num_hash_slots(nb);
         logT = 31 - __clz(TT);
-        vals = reinterpret_cast<T*>(tab + (int64_t)TT * 16);
+        vals = reinterpret_cast<V*>(tab + (int64_t)TT * 16);
     }
     const uint32_t vals_off = (uint32_t)(reinterpret_cast<uint8_t*>(vals) - lds0);
     const uint32_t cm_off = (uint32_t)(reinterpret_cast<uint8_t*>(cm) - lds0);
@@ -1148,7 +1151,7 @@ void k_num(NumArgs a) {
     } else {
         for (int c = lane; c < TT; c += G) slots[c] = make_int4(-1, 0, 0, 0);
     }
-    for (int r = lane; r < n; r += G) vals[r] = T(0);
+    for (int r = lane; r < n; r += G) vals[r] = V(0);
     win_clear<G, KB>(winb, lane);
     group_sync<G>();
 
@@ -1220,7 +1223,7 @@ void k_num(NumArgs a) {
             if (t < nb) {
                 const int b = e.x;
                 uint32_t mk = (uint32_t)e.y;
-                const uint32_t vo = vals_off + (uint32_t)(ex * (int)sizeof(T));
+                const uint32_t vo = vals_off + (uint32_t)(ex * (int)sizeof(V));
                 if constexpr (MODE == MODE_DIRECT) {
                     dw[b - base] = make_uint2(mk, vo);
                 } else if constexpr (MODE == MODE_TWOLEVEL) {
@@ -1247,12 +1250,12 @@ void k_num(NumArgs a) {
         uint32_t vo;
         if constexpr (MODE == MODE_DIRECT) {
             const uint2 mp = dw[(c >> 5) - base];
-            vo = mp.y + (uint32_t)sizeof(T) * __popc(mp.x & below(c & 31));
+            vo = mp.y + (uint32_t)sizeof(V) * __popc(mp.x & below(c & 31));
         } else if constexpr (MODE == MODE_TWOLEVEL) {
             const int w = (c >> 5) - base;
             const uint2 L = l1[w >> 5];
             const uint2 mp = *reinterpret_cast<const uint2*>(lds0 + L.y + 8u * __popc(L.x & below(w & 31)));
-            vo = mp.y + (uint32_t)sizeof(T) * __popc(mp.x & below(c & 31));
+            vo = mp.y + (uint32_t)sizeof(V) * __popc(mp.x & below(c & 31));
         } else {
             const int key = c >> 5;
             int h = hash_slot(key, logT);
@@ -1261,20 +1264,20 @@ void k_num(NumArgs a) {
                 h = (h + 1) & (TT - 1);
                 sl = slots[h];
             }
-            vo = (uint32_t)sl.z + (uint32_t)sizeof(T) * __popc((uint32_t)sl.y & below(c & 31));
+            vo = (uint32_t)sl.z + (uint32_t)sizeof(V) * __popc((uint32_t)sl.y & below(c & 31));
         }
-        return reinterpret_cast<T*>(lds0 + vo);
+        return reinterpret_cast<V*>(lds0 + vo);
     };
     // a group's slots are looked up together (elements past the group's end
     // repeat its first column), then its valid products are added
     auto add = [&](const BGroup<T>& g, int e) {
-        const T x = ava[e];
-        T* pv[4];
+        const V x = (V)ava[e];
+        V* pv[4];
 #pragma unroll
         for (int j = 0; j < 4; ++j) pv[j] = val_at(j < g.n ? g.c[j] : g.c[0]);
 #pragma unroll
         for (int j = 0; j < 4; ++j)
-            if (j < g.n) atomicAdd(pv[j], x * g.y[j]);
+            if (j < g.n) atomicAdd(pv[j], x * (V)g.y[j]);
     };
 
     stage(a0, h0, v0);
@@ -1300,22 +1303,23 @@ void k_num(NumArgs a) {
         // Jacobi-fused product: C(i,:) = B(i,:) - omega D^-1(i) E(i,:); the
         // row's table holds E(i,:), B(i,:) lies inside its pattern
         group_sync<G>();
-        const T sc = -(T)a.omega * reinterpret_cast<const T*>(a.dinv)[i];
+        const V sc = (V)(-(T)a.omega * reinterpret_cast<const T*>(a.dinv)[i]);
         for (int r = lane; r < n; r += G) vals[r] *= sc;
         group_sync<G>();
-        for (int q = a.brp[i] + lane; q < a.brp[i + 1]; q += G) atomicAdd(val_at(a.bci[q]), bv[q]);
+        for (int q = a.brp[i] + lane; q < a.brp[i + 1]; q += G) atomicAdd(val_at(a.bci[q]), (V)bv[q]);
     }
     group_sync<G>();
     T* cv = reinterpret_cast<T*>(a.cval) + off;
-    for (int r = lane; r < n; r += G) cv[r] = vals[r];
+    for (int r = lane; r < n; r += G) cv[r] = (T)vals[r];
 }
 
-// Global path of the numeric phase.  Values are summed in LDS, one segment
-// of `wide_vals` ranks at a time (every segment walks the row's products and
+// Global path of the numeric phase.  Values are summed in LDS (in FP64 for
+// either value type: LDS adds of FP32 are the slower ones, see acc_bytes), one
+// segment of `wide_vals` ranks at a time (every segment walks the row's products and
 // keeps those whose rank falls in it), then copied out coalesced; a row with
 // more than eight segments instead adds straight into C with global atomics.
 template <typename T, bool IN_LDS>
-__device__ void wide_num_row(const NumArgs& a, int i, uint32_t* masks, int2* off, T* ava, Win* win, T* lv,
+__device__ void wide_num_row(const NumArgs& a, int i, uint32_t* masks, int2* off, T* ava, Win* win, double* lv,
                              int* red) {
     constexpr int G = WIDE_THREADS;
     constexpr int KB = 2;  // B groups per lane and batch (1024 lanes: 8192 products per batch)
@@ -1384,31 +1388,31 @@ __device__ void wide_num_row(const NumArgs& a, int i, uint32_t* masks, int2* off
     if (in_lds) {
         for (int s0 = 0; s0 < n; s0 += seg) {
             const int len = min(seg, n - s0);
-            for (int r = tid; r < len; r += G) lv[r] = T(0);
+            for (int r = tid; r < len; r += G) lv[r] = 0.0;
             __syncthreads();
             flat_walk<G, KB, FLAT_VB, false, T>(a.aci, a.bhdr, av, a0, a1, off, ava, win, red, load_cv,
                                                 [&](const BGroup<T>& g, int e) {
-                                                    const T x = ava[e];
+                                                    const double x = (double)ava[e];
                                                     int rk[4];
                                                     ranks(g, rk);
 #pragma unroll
                                                     for (int j = 0; j < 4; ++j) {
                                                         const int r = rk[j] - s0;
                                                         if (j < g.n && (unsigned)r < (unsigned)len)
-                                                            atomicAdd(&lv[r], x * g.y[j]);
+                                                            atomicAdd(&lv[r], x * (double)g.y[j]);
                                                     }
                                                 });
             if (a.dinv) {  // Jacobi-fused: scale the segment, then add B(i,:)'s entries in it
                 const T sc = -(T)a.omega * reinterpret_cast<const T*>(a.dinv)[i];
-                for (int r = tid; r < len; r += G) lv[r] *= sc;
+                for (int r = tid; r < len; r += G) lv[r] *= (double)sc;
                 __syncthreads();
                 for (int q = a.brp[i] + tid; q < a.brp[i + 1]; q += G) {
                     const int r = rank_of(a.bci[q]) - s0;
-                    if ((unsigned)r < (unsigned)len) atomicAdd(&lv[r], bv[q]);
+                    if ((unsigned)r < (unsigned)len) atomicAdd(&lv[r], (double)bv[q]);
                 }
                 __syncthreads();
             }
-            for (int r = tid; r < len; r += G) cv[s0 + r] = lv[r];
+            for (int r = tid; r < len; r += G) cv[s0 + r] = (T)lv[r];
             __syncthreads();
         }
     } else {
@@ -1455,7 +1459,7 @@ __global__ __launch_bounds__(WIDE_THREADS) void k_num_wide(NumArgs a) {
     int2* off = reinterpret_cast<int2*>(stage);
     T* ava = reinterpret_cast<T*>(stage + WIDE_THREADS * 8);
     Win* win = reinterpret_cast<Win*>(stage + WIDE_THREADS * 16);
-    T* lv = reinterpret_cast<T*>(stage + WIDE_THREADS * 16 + WIDE_WIN_BYTES);
+    double* lv = reinterpret_cast<double*>(stage + WIDE_THREADS * 16 + WIDE_WIN_BYTES);
     const int count = a.count_dev ? *a.count_dev : a.count;
     for (int r = blockIdx.x; r < count; r += gridDim.x) {
         const int i = a.perm[r];
@@ -1847,7 +1851,7 @@ int launch_num_class(hipStream_t s, const NumArgs& a, int elem_bytes, int grid_c
     if (a.tier == TIER_GLOBAL) {
         int grid = a.count_dev ? grid_cap : (a.count < grid_cap ? a.count : grid_cap);
         if (grid < 1) return 0;
-        const size_t smem = wide_smem_bytes(a.wide_lds, 1, a.wide_vals * elem_bytes);
+        const size_t smem = wide_smem_bytes(a.wide_lds, 1, a.wide_vals * (int)sizeof(double));
         if (elem_bytes == 8) hipLaunchKernelGGL(k_num_wide<double>, dim3(grid), dim3(WIDE_THREADS), smem, s, a);
         else hipLaunchKernelGGL(k_num_wide<float>, dim3(grid), dim3(WIDE_THREADS), smem, s, a);
         return grid;

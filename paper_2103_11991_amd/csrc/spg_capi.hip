@@ -334,11 +334,11 @@ int wide_lds(spg_handle h) {
     return v;
 }
 
-// values per LDS segment of a global-path numeric workgroup: what the device
+// FP64 values per LDS segment of a global-path numeric workgroup: what the device
 // leaves beside the mask table and the staged entries, 0 if under 4 KB
-int wide_vals(spg_handle h, int eb) {
+int wide_vals(spg_handle h) {
     const int64_t left = (int64_t)h->max_lds - wide_lds(h) - WIDE_THREADS * 16 - WIDE_WIN_BYTES - 1024;
-    return left >= 4096 ? (int)((left & ~(int64_t)255) / eb) : 0;
+    return left >= 4096 ? (int)((left & ~(int64_t)255) / 8) : 0;
 }
 
 // small classes run in larger ones unless a class is forced
@@ -824,7 +824,7 @@ spg_status num_launch_all(spg_handle h, const void* a_vals, const void* b_vals, 
         a.slab = h->slab_num_words ? h->slab_num.as<uint32_t>() : nullptr;
         a.slab_words = h->slab_num_words;
         a.wide_lds = wide_lds(h);
-        a.wide_vals = wide_vals(h, eb);
+        a.wide_vals = wide_vals(h);
         a.lofs = h->lofs.as<int32_t>();
         a.lists = h->lists.as<int2>();
         a.dinv = dinv;

@@ -194,21 +194,31 @@ __host__ __device__ inline int sym_class(int64_t ub, int32_t cmin, int32_t cmax,
     return mode * NTIER + t;
 }
 
-// Numeric class of a row from its exact size n and occupied blocks: the
-// direct table when the row's block range is about as small as its block
-// count, else the two-level table; the hashed table for very wide, sparse
-// rows with few blocks, when it is the smaller.
-__host__ __device__ inline int num_class(int64_t ub, int32_t cmin, int32_t cmax, int64_t n, int64_t blocks,
-                                         const ClassCfg& c) {
-    if (n <= 0) return CLS_EMPTY;
-    int64_t words = row_words(cmin, cmax);
-    int eb = c.elem_bytes;
+// Bytes of one summed value in the numeric tables of tier t.  FP32 rows sum
+// in FP64 up to tier ACC64_TIER: an LDS atomic add of FP32 values takes 192
+// cycles of a compute unit per wavefront whatever the addresses (the lanes
+// go one after another), one of FP64 values 9 to 29 (27-point 61^3, FP32
+// numeric: 0.85 ms with FP32 sums).  Rows whose values need more LDS than
+// that tier has keep FP32 sums, which halve their tables: the alternative
+// for most of them is the global path.
+constexpr int ACC64_TIER = 6;
+__host__ __device__ inline int acc_bytes(int t, int elem_bytes) { return t <= ACC64_TIER ? 8 : elem_bytes; }
+
+// Numeric class of a row from its exact size n and occupied blocks, with eb
+// bytes per value: the direct table when the row's block range is about as
+// small as its block count, else the two-level table; the hashed table for
+// very wide, sparse rows with few blocks, when it is the smaller.
+__host__ __device__ inline int num_class_eb(int64_t ub, int64_t words, int64_t n, int64_t blocks, const ClassCfg& c,
+                                            int eb) {
     int64_t bd = num_direct_bytes(words, n, eb), bh = num_hashed_bytes(blocks, n, eb);
     int64_t b2 = num_twolevel_bytes(words, blocks, n, eb);
     if (c.force_class >= 0) {
         int fm = c.force_class / NTIER, ft = c.force_class % NTIER;
         if (ft == TIER_GLOBAL) return MODE_DIRECT * NTIER + TIER_GLOBAL;
-        int64_t need = fm == MODE_DIRECT ? bd : fm == MODE_HASHED ? bh : b2;
+        const int fb = acc_bytes(ft, c.elem_bytes);
+        int64_t need = fm == MODE_DIRECT   ? num_direct_bytes(words, n, fb)
+                       : fm == MODE_HASHED ? num_hashed_bytes(blocks, n, fb)
+                                           : num_twolevel_bytes(words, blocks, n, fb);
         if (need <= tier_bytes(ft) && tier_bytes(ft) <= c.lds_limit) return c.force_class;
     }
     int mode;
@@ -217,9 +227,19 @@ __host__ __device__ inline int num_class(int64_t ub, int32_t cmin, int32_t cmax,
     else if (blocks <= c.hash_max_blocks && bh < b2) mode = MODE_HASHED, bytes = bh;
     else mode = MODE_TWOLEVEL, bytes = b2;
     int t = pick_tier(bytes, ub, c);
+    // FP32 sums: in the tiers that have them
+    if (eb < 8 && t <= ACC64_TIER) t = ACC64_TIER + 1;
     // a tier raised for the row's work may hold the direct table (one lookup per product)
     if (t == TIER_GLOBAL || bd <= tier_bytes(t)) mode = MODE_DIRECT;
     return mode * NTIER + t;
+}
+__host__ __device__ inline int num_class(int64_t ub, int32_t cmin, int32_t cmax, int64_t n, int64_t blocks,
+                                         const ClassCfg& c) {
+    if (n <= 0) return CLS_EMPTY;
+    const int64_t words = row_words(cmin, cmax);
+    const int cls = num_class_eb(ub, words, n, blocks, c, 8);
+    if (c.elem_bytes == 8 || cls % NTIER <= ACC64_TIER) return cls;
+    return num_class_eb(ub, words, n, blocks, c, c.elem_bytes);
 }
 
 // Launch classes: a class with few rows runs in the next populated class of
@@ -372,7 +392,7 @@ struct NumArgs {
     uint32_t* slab;               // global path: masks and prefixes per workgroup
     int64_t slab_words;
     int32_t wide_lds;
-    int32_t wide_vals;            // global path: values per LDS segment (0 = global atomics only)
+    int32_t wide_vals;            // global path: FP64 values per LDS segment (0 = global atomics only)
     const int32_t* lofs;          // per row: first pair of its list, -1 if it has none
     const int2* lists;            // {block, mask} pairs in ascending block order
     const int32_t* count_dev;     // global path: device-side row count (or null)
