@@ -68,8 +68,13 @@ struct spg_handle_s {
 
     // scratch
     DevBuf binfo, rinfo, feats, sym_cls, num_cls, perm_sym, perm_num, desc_sym, desc_num, row_nnz, row_blocks,
-        tile_status, cursor,
         ovf_list, ctl, slab_sym, slab_retry, slab_num, mlp_w, bc, bhdr, lofs, lists, toff, titems, tfb, slab_paper;
+    // ctl holds what a symbolic call starts from zero, cleared by one launch:
+    // the control block, then these
+    int32_t *cursor_sym = nullptr, *cursor_num = nullptr;  // states of the two groupings
+    uint64_t* tile_status = nullptr;                       // of the row-pointer scan
+    Shard *shards_ana = nullptr, *shards_scan = nullptr;   // counters of the analysis and of the scan
+    size_t zero_bytes = 0;
     Control* hctl = nullptr;  // pinned host copy
     hipEvent_t ev_ctl = nullptr;  // marks the copy of the control block after the row-pointer scan
 
@@ -391,7 +396,22 @@ spg_status sym_prepare(spg_handle h) {
     const bool learned = h->binning == 1;
     const bool want_feats = learned || h->keep_features;
     const size_t M = (size_t)std::max(m, 1);
-    SPG_TRY(ensure(h, h->ctl, sizeof(Control)));
+    auto room = [](size_t bytes) { return (bytes + 63) & ~(size_t)63; };
+    const size_t zs[] = {room(sizeof(Control)),
+                         room(scatter_state_bytes(m)),
+                         room(scatter_state_bytes(m)),
+                         room((size_t)(scan_tiles(m) + 1) * 8),
+                         room(NSHARD * sizeof(Shard)),
+                         room(NSHARD * sizeof(Shard))};
+    h->zero_bytes = 0;
+    for (size_t z : zs) h->zero_bytes += z;
+    SPG_TRY(ensure(h, h->ctl, h->zero_bytes));
+    uint8_t* z = h->ctl.as<uint8_t>() + zs[0];
+    h->cursor_sym = reinterpret_cast<int32_t*>(z), z += zs[1];
+    h->cursor_num = reinterpret_cast<int32_t*>(z), z += zs[2];
+    h->tile_status = reinterpret_cast<uint64_t*>(z), z += zs[3];
+    h->shards_ana = reinterpret_cast<Shard*>(z), z += zs[4];
+    h->shards_scan = reinterpret_cast<Shard*>(z);
     SPG_TRY(ensure(h, h->binfo, (size_t)std::max(h->n, 1) * sizeof(int4)));
     SPG_TRY(ensure(h, h->rinfo, M * sizeof(RowInfo)));
     SPG_TRY(ensure(h, h->sym_cls, M));
@@ -402,9 +422,7 @@ spg_status sym_prepare(spg_handle h) {
     SPG_TRY(ensure(h, h->desc_num, M * sizeof(int4)));
     SPG_TRY(ensure(h, h->row_nnz, M * 4));
     SPG_TRY(ensure(h, h->row_blocks, M * 4));
-    SPG_TRY(ensure(h, h->tile_status, (size_t)(scan_tiles(std::max(m, h->n)) + 1) * 8));
     SPG_TRY(ensure(h, h->bhdr, (size_t)std::max(h->n, 1) * sizeof(int4)));
-    SPG_TRY(ensure(h, h->cursor, scatter_state_bytes(m)));
     SPG_TRY(ensure(h, h->lofs, M * 4));
     if (learned) SPG_TRY(ensure(h, h->ovf_list, M * 4));
     if (want_feats) SPG_TRY(ensure(h, h->feats, M * 12));
@@ -491,13 +509,14 @@ void sym_stage_analysis(spg_handle h) {
     const bool learned = h->binning == 1;
     const bool want_feats = learned || h->keep_features;
     Control* ctl = h->ctl.as<Control>();
-    launch_fill_u8(s, ctl, 0, sizeof(Control));
+    launch_zero(s, ctl, (int64_t)h->zero_bytes);
     if (h->m == 0) return;
     launch_b_rows(s, h->n, h->k, h->brp, h->bci, h->bnnz, h->binfo.as<int4>(), h->bc.as<int2>(), h->bhdr.as<int4>(),
                   ctl);
     launch_a_rowinfo(s, h->m, h->n, h->arp, h->aci, h->annz, h->binfo.as<int4>(), h->rinfo.as<RowInfo>(),
                      want_feats ? h->feats.as<float>() : nullptr, h->cfg, h->binning, h->sym_cls.as<uint8_t>(),
-                     h->row_nnz.as<int32_t>(), h->row_blocks.as<int32_t>(), h->lofs.as<int32_t>(), ctl);
+                     h->row_nnz.as<int32_t>(), h->row_blocks.as<int32_t>(), h->lofs.as<int32_t>(),
+                     h->shards_ana, ctl);
     if (learned) {
         rec(h, EV_MLP0);
         launch_mlp_classify(s, h->m, h->feats.as<float>(), h->mlp_w.as<float>(), h->rinfo.as<RowInfo>(), h->cfg,
@@ -506,7 +525,7 @@ void sym_stage_analysis(spg_handle h) {
     }
     // rows grouped by symbolic launch class (small classes merged); each
     // row's list placed (the total is read back)
-    launch_scatter(s, h->m, h->sym_cls.as<uint8_t>(), merging(h), ctl->sym_hist, h->cursor.as<int32_t>(),
+    launch_scatter(s, h->m, h->sym_cls.as<uint8_t>(), merging(h), ctl->sym_hist, h->cursor_sym,
                    h->perm_sym.as<int32_t>(), h->arp, nullptr, h->desc_sym.as<int4>(), h->lofs.as<int32_t>(), ctl,
                    h->list_cap);
     rec(h, EV_ANA1);
@@ -639,17 +658,16 @@ spg_status sym_stage_rows(spg_handle h, int32_t* c_row_ptr, bool read_back = fal
     }
     // row pointer and numeric classes
     rec(h, EV_SCAN0);
-    launch_fill_u8(s, h->tile_status.p, 0, (scan_tiles(m) + 1) * 8);
     launch_scan(s, m, h->row_nnz.as<int32_t>(), h->row_blocks.as<int32_t>(), h->rinfo.as<RowInfo>(), h->arp,
-                h->sym_cls.as<uint8_t>(), h->lofs.as<int32_t>(), c_row_ptr, h->tile_status.as<uint64_t>(), h->cfg,
-                h->num_cls.as<uint8_t>(), ctl);
+                h->sym_cls.as<uint8_t>(), h->lofs.as<int32_t>(), c_row_ptr, h->tile_status, h->cfg,
+                h->num_cls.as<uint8_t>(), h->shards_scan, ctl);
     rec(h, EV_SCAN1);
     if (read_back) {
         if (!h->ev_ctl) HIP_TRY(h, hipEventCreateWithFlags(&h->ev_ctl, hipEventDisableTiming));
         HIP_TRY(h, hipMemcpyAsync(h->hctl, h->ctl.p, sizeof(Control), hipMemcpyDeviceToHost, s));
         HIP_TRY(h, hipEventRecord(h->ev_ctl, s));
     }
-    launch_scatter(s, m, h->num_cls.as<uint8_t>(), merging(h), ctl->num_hist, h->cursor.as<int32_t>(),
+    launch_scatter(s, m, h->num_cls.as<uint8_t>(), merging(h), ctl->num_hist, h->cursor_num,
                    h->perm_num.as<int32_t>(), h->arp, c_row_ptr, h->desc_num.as<int4>());
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return hip_fail(h, e, "symbolic launch");
@@ -899,7 +917,7 @@ spg_status spg_destroy(spg_handle h) {
     (void)hipStreamSynchronize(h->stream);  // no launch of this handle still reads its buffers
     DevBuf* bufs[] = {&h->binfo, &h->rinfo, &h->feats, &h->sym_cls, &h->num_cls, &h->perm_sym, &h->perm_num,
                       &h->desc_sym, &h->desc_num,
-                      &h->row_nnz, &h->row_blocks, &h->tile_status, &h->cursor, &h->ovf_list, &h->ctl,
+                      &h->row_nnz, &h->row_blocks, &h->ovf_list, &h->ctl,
                       &h->slab_sym, &h->slab_retry, &h->slab_num, &h->mlp_w, &h->bc, &h->bhdr,
                       &h->lofs, &h->lists, &h->toff, &h->titems, &h->tfb, &h->slab_paper};
     for (DevBuf* b : bufs) cache_put(h->device, *b);  // idle: the stream has finished

@@ -89,12 +89,6 @@ __host__ __device__ inline int64_t tier_smem_bytes(int t) {
     return (int64_t)tier_rows(t) * (tier_bytes(t) + stage_bytes(tier_threads(t)));
 }
 
-__host__ __device__ inline int64_t pow2ceil64(int64_t x) {
-    int64_t p = 1;
-    while (p < x) p <<= 1;
-    return p;
-}
-
 // Runtime knobs of the class choice (copied into kernels by value).
 struct ClassCfg {
     int32_t work_per_lane;    // products per lane that size a row's thread group
@@ -111,59 +105,60 @@ struct ClassCfg {
 //   w = largest referenced B-row length
 using RowInfo = int4;
 
-// Table sizes, shared by the classifier and the kernels so both agree.
-__host__ __device__ inline int64_t row_words(int32_t cmin, int32_t cmax) {
-    return (int64_t)(cmax >> 5) - (int64_t)(cmin >> 5) + 1;
-}
+// Table sizes, shared by the classifier and the kernels so both agree.  All
+// of it is 32-bit arithmetic without loops (it runs once or twice per row in
+// the analysis and scan kernels; with 64-bit loops a scan of 4096 rows took
+// 20 us): a row spans at most 2^26 words, and counts past SIZE_CAP stand for
+// "more than any LDS limit" whatever their exact value.
+constexpr int32_t SIZE_CAP = 1 << 24;
+__host__ __device__ inline int32_t row_words(int32_t cmin, int32_t cmax) { return (cmax >> 5) - (cmin >> 5) + 1; }
+__host__ __device__ inline int32_t size_cap(int64_t x) { return x < SIZE_CAP ? (int32_t)x : SIZE_CAP; }
+__host__ __device__ inline int32_t pow2ceil32(int32_t x) { return x <= 1 ? 1 : 1 << (32 - __builtin_clz((uint32_t)(x - 1))); }
 // Slots of a symbolic hashed table.  The table overflows (the row is retried
 // on the global path) above three-quarter occupancy: a learned estimate gets
 // 2x slots, a guaranteed upper bound 4/3x, enough never to reach that mark.
-__host__ __device__ inline int64_t sym_hash_slots(int64_t est_blocks, bool bound = false) {
-    const int64_t need = bound ? (est_blocks * 4 + 2) / 3 : est_blocks * 2;
-    return pow2ceil64(need > 16 ? need : 16);
+__host__ __device__ inline int32_t sym_hash_slots(int32_t est_blocks, bool bound = false) {
+    const int32_t need = bound ? (est_blocks * 4 + 2) / 3 : est_blocks * 2;
+    return pow2ceil32(need > 16 ? need : 16);
 }
-__host__ __device__ inline int64_t num_hash_slots(int64_t blocks) {
-    return pow2ceil64(blocks * 2 > 16 ? blocks * 2 : 16);
+__host__ __device__ inline int32_t num_hash_slots(int32_t blocks) {
+    return pow2ceil32(blocks * 2 > 16 ? blocks * 2 : 16);
 }
-__host__ __device__ inline int64_t align8(int64_t b) { return (b + 7) & ~(int64_t)7; }
-__host__ __device__ inline int64_t num_direct_bytes(int64_t words, int64_t n, int eb) {
+__host__ __device__ inline int32_t align8(int32_t b) { return (b + 7) & ~7; }
+__host__ __device__ inline int32_t num_direct_bytes(int32_t words, int32_t n, int eb) {
     return align8(words * 8) + n * eb;
 }
 // hashed numeric table: 16-byte slots {block, mask, prefix, -}
-__host__ __device__ inline int64_t num_hashed_bytes(int64_t blocks, int64_t n, int eb) {
+__host__ __device__ inline int32_t num_hashed_bytes(int32_t blocks, int32_t n, int eb) {
     return num_hash_slots(blocks) * 16 + n * eb;
 }
 // two-level numeric table: a {bits, first index} pair per 32 words of the
 // row's block range (which blocks are occupied, and the list index of the
 // first of them), then {mask, prefix} per occupied block
-__host__ __device__ inline int64_t twolevel_words(int64_t words) { return (words + 31) / 32; }
-__host__ __device__ inline int64_t num_twolevel_bytes(int64_t words, int64_t blocks, int64_t n, int eb) {
+__host__ __device__ inline int32_t twolevel_words(int32_t words) { return (words + 31) / 32; }
+__host__ __device__ inline int32_t num_twolevel_bytes(int32_t words, int32_t blocks, int32_t n, int eb) {
     return align8(twolevel_words(words) * 8 + blocks * 8) + n * eb;
 }
 // A row's list capacity: its compressed-B run count bounds its occupied
 // blocks, and so does the width of its column range in words.
-__host__ __device__ inline int32_t list_capacity(int64_t runs, int64_t words) {
-    const int64_t c = runs < words ? runs : words;
-    return c > INT32_MAX ? INT32_MAX : (int32_t)c;
+__host__ __device__ inline int32_t list_capacity(int64_t runs, int32_t words) {
+    return runs < words ? (int32_t)runs : words;
 }
 
 // Smallest LDS tier that holds `bytes`, raised until its thread group gives
 // at most work_per_lane products per lane; TIER_GLOBAL if it does not fit.
-__host__ __device__ inline int pick_tier(int64_t bytes, int64_t work, const ClassCfg& c) {
-    if (bytes > c.lds_limit) return TIER_GLOBAL;
-    int t = 0;
-    while (t < TIER_GLOBAL - 1 && tier_bytes(t) < bytes) ++t;
-    if (tier_bytes(t) < bytes) return TIER_GLOBAL;
-    while (t < TIER_GLOBAL - 1 && (int64_t)tier_threads(t) * c.work_per_lane < work &&
-           tier_bytes(t + 1) <= c.lds_limit)
-        ++t;
+__host__ __device__ inline int pick_tier(int32_t bytes, int64_t work, const ClassCfg& c) {
+    if (bytes > c.lds_limit || bytes > tier_bytes(TIER_GLOBAL - 1)) return TIER_GLOBAL;
+    int t = bytes <= 256 ? 0 : 24 - __builtin_clz((uint32_t)(bytes - 1));
+    const int32_t w = work < INT32_MAX ? (int32_t)work : INT32_MAX;
+    while (t < TIER_GLOBAL - 1 && tier_threads(t) * c.work_per_lane < w && tier_bytes(t + 1) <= c.lds_limit) ++t;
     return t;
 }
 
 // Bytes per occupied block of the symbolic two-level table: its mask and its
 // id, kept as a 16-bit offset from the row's first block when the row's range
 // spans at most 2^16 blocks.
-__host__ __device__ inline int sym_block_bytes(int64_t words) { return words <= 65536 ? 6 : 8; }
+__host__ __device__ inline int sym_block_bytes(int32_t words) { return words <= 65536 ? 6 : 8; }
 
 // Symbolic class of a row from its products, column range and an estimate
 // of its occupied blocks (an upper bound: the compressed-B runs its products
@@ -171,21 +166,21 @@ __host__ __device__ inline int sym_block_bytes(int64_t words) { return words <= 
 __host__ __device__ inline int sym_class(int64_t ub, int32_t cmin, int32_t cmax, int64_t est_blocks,
                                          const ClassCfg& c, bool bound = false) {
     if (ub <= 0) return CLS_EMPTY;
-    int64_t words = row_words(cmin, cmax);
-    int64_t est = est_blocks < words ? est_blocks : words;
+    const int32_t words = row_words(cmin, cmax);
+    int32_t est = est_blocks < words ? (int32_t)est_blocks : words;
     if (est < 1) est = 1;
     // direct: a mask per word; hashed: keys and masks; two-level: {bits,
     // prefix} per 32 words, a mask and the block id per (estimated) occupied block
-    int64_t bd = words * 4, bh = sym_hash_slots(est, bound) * 8;
-    int64_t b2 = align8(twolevel_words(words) * 8) + est * sym_block_bytes(words);
+    const int32_t bd = words * 4, bh = sym_hash_slots(est, bound) * 8;
+    const int32_t b2 = align8(twolevel_words(words) * 8) + est * sym_block_bytes(words);
     if (c.force_class >= 0) {
         int fm = c.force_class / NTIER, ft = c.force_class % NTIER;
         if (ft == TIER_GLOBAL) return MODE_DIRECT * NTIER + TIER_GLOBAL;
-        int64_t need = fm == MODE_DIRECT ? bd : fm == MODE_HASHED ? bh : b2;
+        int32_t need = fm == MODE_DIRECT ? bd : fm == MODE_HASHED ? bh : b2;
         if (need <= tier_bytes(ft) && tier_bytes(ft) <= c.lds_limit) return c.force_class;
     }
     int mode = MODE_DIRECT;
-    int64_t bytes = bd;
+    int32_t bytes = bd;
     if (b2 < bytes) mode = MODE_TWOLEVEL, bytes = b2;
     if (bh < bytes) mode = MODE_HASHED, bytes = bh;
     int t = pick_tier(bytes, ub, c);
@@ -208,21 +203,21 @@ __host__ __device__ inline int acc_bytes(int t, int elem_bytes) { return t <= AC
 // bytes per value: the direct table when the row's block range is about as
 // small as its block count, else the two-level table; the hashed table for
 // very wide, sparse rows with few blocks, when it is the smaller.
-__host__ __device__ inline int num_class_eb(int64_t ub, int64_t words, int64_t n, int64_t blocks, const ClassCfg& c,
+__host__ __device__ inline int num_class_eb(int64_t ub, int32_t words, int32_t n, int32_t blocks, const ClassCfg& c,
                                             int eb) {
-    int64_t bd = num_direct_bytes(words, n, eb), bh = num_hashed_bytes(blocks, n, eb);
-    int64_t b2 = num_twolevel_bytes(words, blocks, n, eb);
+    const int32_t bd = num_direct_bytes(words, n, eb), bh = num_hashed_bytes(blocks, n, eb);
+    const int32_t b2 = num_twolevel_bytes(words, blocks, n, eb);
     if (c.force_class >= 0) {
         int fm = c.force_class / NTIER, ft = c.force_class % NTIER;
         if (ft == TIER_GLOBAL) return MODE_DIRECT * NTIER + TIER_GLOBAL;
         const int fb = acc_bytes(ft, c.elem_bytes);
-        int64_t need = fm == MODE_DIRECT   ? num_direct_bytes(words, n, fb)
+        int32_t need = fm == MODE_DIRECT   ? num_direct_bytes(words, n, fb)
                        : fm == MODE_HASHED ? num_hashed_bytes(blocks, n, fb)
                                            : num_twolevel_bytes(words, blocks, n, fb);
         if (need <= tier_bytes(ft) && tier_bytes(ft) <= c.lds_limit) return c.force_class;
     }
     int mode;
-    int64_t bytes;
+    int32_t bytes;
     if (words <= 2 * blocks + 8) mode = MODE_DIRECT, bytes = bd;
     else if (blocks <= c.hash_max_blocks && bh < b2) mode = MODE_HASHED, bytes = bh;
     else mode = MODE_TWOLEVEL, bytes = b2;
@@ -236,10 +231,10 @@ __host__ __device__ inline int num_class_eb(int64_t ub, int64_t words, int64_t n
 __host__ __device__ inline int num_class(int64_t ub, int32_t cmin, int32_t cmax, int64_t n, int64_t blocks,
                                          const ClassCfg& c) {
     if (n <= 0) return CLS_EMPTY;
-    const int64_t words = row_words(cmin, cmax);
-    const int cls = num_class_eb(ub, words, n, blocks, c, 8);
+    const int32_t words = row_words(cmin, cmax), nc = size_cap(n), bc = size_cap(blocks);
+    const int cls = num_class_eb(ub, words, nc, bc, c, 8);
     if (c.elem_bytes == 8 || cls % NTIER <= ACC64_TIER) return cls;
-    return num_class_eb(ub, words, n, blocks, c, c.elem_bytes);
+    return num_class_eb(ub, words, nc, bc, c, c.elem_bytes);
 }
 
 // Launch classes: a class with few rows runs in the next populated class of
@@ -249,24 +244,25 @@ __host__ __device__ inline int num_class(int64_t ub, int32_t cmin, int32_t cmax,
 // with its tail is saved.  Merges chain upwards.  remap gets the launch class
 // of every class and merged the row counts per launch class.  The host and
 // the grouping kernel both evaluate it on the same histogram.
-__host__ __device__ inline void merge_classes(const int32_t* hist, uint8_t* remap, int32_t* merged, bool enable) {
-    for (int c = 0; c < NCLS; ++c) remap[c] = (uint8_t)c, merged[c] = hist[c];
+__host__ __device__ inline void merge_classes_mode(const int32_t* hist, uint8_t* remap, int32_t* merged, int mode,
+                                                   bool enable) {
+    const int c0 = mode * NTIER;
+    for (int t = 0; t < NTIER; ++t) remap[c0 + t] = (uint8_t)(c0 + t), merged[c0 + t] = hist[c0 + t];
     if (!enable) return;
-    for (int mode = 0; mode < 3; ++mode) {
-        for (int t = 0; t < TIER_GLOBAL; ++t) {
-            const int c = mode * NTIER + t;
-            if (merged[c] == 0) continue;
-            int u = t + 1;
-            while (u < TIER_GLOBAL && merged[mode * NTIER + u] == 0) ++u;
-            if (u >= TIER_GLOBAL || tier_threads(u) > 4 * tier_threads(t)) continue;
-            const int d = mode * NTIER + u;
-            if ((int64_t)merged[c] * 8 > merged[d]) continue;
-            merged[d] += merged[c];
-            merged[c] = 0;
-            for (int e = 0; e < NCLS; ++e)
-                if (remap[e] == c) remap[e] = (uint8_t)d;
-        }
+    for (int t = 0; t < TIER_GLOBAL; ++t) {
+        if (merged[c0 + t] == 0) continue;
+        int u = t + 1;
+        while (u < TIER_GLOBAL && merged[c0 + u] == 0) ++u;
+        if (u >= TIER_GLOBAL || tier_threads(u) > 4 * tier_threads(t)) continue;
+        if ((int64_t)merged[c0 + t] * 8 > merged[c0 + u]) continue;
+        merged[c0 + u] += merged[c0 + t];
+        merged[c0 + t] = 0;
+        for (int e = 0; e < NTIER; ++e)
+            if (remap[c0 + e] == c0 + t) remap[c0 + e] = (uint8_t)(c0 + u);
     }
+}
+inline void merge_classes(const int32_t* hist, uint8_t* remap, int32_t* merged, bool enable) {
+    for (int mode = 0; mode < 3; ++mode) merge_classes_mode(hist, remap, merged, mode, enable);
 }
 
 // Device-side control block: counters and histograms the host reads back
@@ -287,7 +283,6 @@ struct Control {
     int64_t num_c_nnz[NCLS];
     int64_t num_products[NCLS];
     int32_t tile_counter;         // dynamic tile id of the row-pointer scan
-    int64_t bc_total;             // runs of compressed B
     int64_t list_total;           // list pairs reserved by the grouping of the symbolic rows
     int32_t tile_fallback;        // tiled global path: rows left to the segment path
     int32_t b_tile_unordered;     // tiled global path: a B row's entries are not grouped by tile
@@ -295,15 +290,38 @@ struct Control {
     int32_t tile_light;           // tiled global path: rows of at most TILE_G entries (one unit per row)
     int32_t a_missing_diag;       // square A: rows without a stored diagonal entry
     int64_t max_products;         // most products of one row
+    int32_t done[2];              // shards whose workgroups have all added theirs (0 analysis, 1 scan)
     // symbolic grouping (tier-major: the three modes of a tier are adjacent):
     // rows and first slot of every launch class after the class merge
     int32_t sym_cnt[NCLS];
     int32_t sym_off[NCLS];
 };
 
+// Counters of the analysis and the scan kernels: thousands of workgroups that
+// add to one address take their turns there (about 20 ns each: 4096
+// workgroups with five counters were 0.1 to 0.2 ms, whatever the rows), so
+// each adds to one of NSHARD copies, and the last workgroup to finish sums
+// them into the control block.
+constexpr int NSHARD = 32;
+constexpr int NCOUNT = 128;
+constexpr int CNT_HIST = 0, CNT_ANNZ = 30, CNT_CNNZ = 60, CNT_PROD = 90;  // per class
+constexpr int CNT_ROWS = 120;   // analysis: empty rows; scan: mispredicted rows
+constexpr int CNT_NODIAG = 121;
+constexpr int CNT_PRODUCTS = 122;
+constexpr int CNT_MAX = 123;    // from here on maxima instead of sums
+constexpr int CNT_WORDS = 123, CNT_MAXPROD = 124, CNT_WGLOB = 125;
+struct Shard {
+    unsigned long long f[NCOUNT];
+    int32_t done;               // its workgroups that have added theirs
+    int32_t pad[31];
+};
+static_assert(NCLS == 30, "the counter layout above");
+
 // ---- launch wrappers (spg_rows.hip) ----
 void launch_fill_i32(hipStream_t s, int32_t* p, int32_t v, int64_t n);
 void launch_fill_u8(hipStream_t s, void* p, uint8_t v, int64_t bytes);
+// p 16-byte aligned, bytes a multiple of 16
+void launch_zero(hipStream_t s, void* p, int64_t bytes);
 // B rows in one pass: validation, binfo {length, smallest column, largest
 // column, runs} and compressed B (section 2.2.1): per row its runs of entries
 // sharing a 32-column block as {block, OR of the column bits}, stored from the
@@ -313,7 +331,8 @@ void launch_b_rows(hipStream_t s, int32_t n, int32_t k, const int32_t* brp, cons
                    int4* binfo, int2* bc, int4* bhdr, Control* ctl);
 void launch_a_rowinfo(hipStream_t s, int32_t m, int32_t n, const int32_t* arp, const int32_t* aci, int64_t annz,
                       const int4* binfo, RowInfo* rinfo, float* feats, ClassCfg cfg, int binning,
-                      uint8_t* sym_cls, int32_t* row_nnz, int32_t* row_blocks, int32_t* lofs, Control* ctl);
+                      uint8_t* sym_cls, int32_t* row_nnz, int32_t* row_blocks, int32_t* lofs, Shard* shards,
+                      Control* ctl);
 void launch_mlp_classify(hipStream_t s, int32_t m, const float* feats, const float* w, const RowInfo* rinfo,
                          ClassCfg cfg, float margin, uint8_t* sym_cls, Control* ctl);
 // groups rows by class; offsets come from the class histogram in device memory.
@@ -324,14 +343,14 @@ void launch_mlp_classify(hipStream_t s, int32_t m, const float* feats, const flo
 // gets the same offset.
 // With merge, rows are grouped by their launch class (merge_classes).
 // Each class's rows come in ascending row order up to the order inside a
-// chunk of 2048 rows.  state (scatter_state_bytes(m) bytes) is cleared here.
+// chunk of 2048 rows.  state: scatter_state_bytes(m) zeroed bytes.
 size_t scatter_state_bytes(int32_t m);
 void launch_scatter(hipStream_t s, int32_t m, const uint8_t* cls, int merge, const int32_t* hist, int32_t* state,
                     int32_t* perm, const int32_t* arp, const int32_t* crp, int4* desc, int32_t* lofs = nullptr,
                     Control* ctl = nullptr, int64_t list_limit = 0);
 void launch_scan(hipStream_t s, int32_t m, const int32_t* row_nnz, const int32_t* row_blocks, const RowInfo* rinfo,
                  const int32_t* arp, const uint8_t* sym_cls, const int32_t* lofs, int32_t* c_row_ptr,
-                 uint64_t* tile_status, ClassCfg cfg, uint8_t* num_cls, Control* ctl);
+                 uint64_t* tile_status, ClassCfg cfg, uint8_t* num_cls, Shard* shards, Control* ctl);
 void launch_export_rows(hipStream_t s, int32_t m, const float* feats, const int32_t* row_blocks,
                         const int32_t* row_nnz_in, float* x, float* y, int32_t* row_nnz_out);
 int64_t scan_tiles(int32_t m);
@@ -518,7 +537,7 @@ int launch_num_tiled(hipStream_t s, const TileArgs& a, int elem_bytes, int n_cu)
 int launch_sym_class(hipStream_t s, const SymArgs& a, int grid_cap);
 // Launch offsets of the symbolic grouping: tier-major, so that the three
 // table modes of one tier are adjacent (one persistent launch takes them).
-__host__ __device__ inline void sym_class_offsets(const int32_t* rows, int32_t* off) {
+inline void sym_class_offsets(const int32_t* rows, int32_t* off) {
     int32_t run = 0;
     for (int t = 0; t < NTIER; ++t)
         for (int md = 0; md < 3; ++md) {

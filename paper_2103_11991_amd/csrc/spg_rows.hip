@@ -26,7 +26,6 @@ constexpr int AN_LANES = 4;         // lanes per row in the row analysis passes
 constexpr int AN_LOADS = 8;         // independent entry loads per lane and round trip there
 constexpr int SCAN_THREADS = 256;
 constexpr int SCAN_ITEMS = 8;
-constexpr int SCAN_TILE = SCAN_THREADS * SCAN_ITEMS;
 
 __global__ void k_fill_i32(int32_t* p, int32_t v, int64_t n) {
     for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
@@ -36,6 +35,87 @@ __global__ void k_fill_i32(int32_t* p, int32_t v, int64_t n) {
 __global__ void k_fill_u8(uint8_t* p, uint8_t v, int64_t n) {
     for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
         p[i] = v;
+}
+
+__global__ void k_zero(uint4* p, int64_t n16) {
+    for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n16; i += (int64_t)gridDim.x * blockDim.x)
+        p[i] = make_uint4(0, 0, 0, 0);
+}
+
+// Every vector memory access of this thread has completed.
+__device__ inline void wait_mem() { __builtin_amdgcn_s_waitcnt(0); }
+
+// Adds the workgroup's counters (acc, NCOUNT in LDS, complete and
+// synchronised) to its shard.
+__device__ inline void add_counts(const unsigned long long* acc, Shard* shards) {
+    const int t = threadIdx.x, s = blockIdx.x % NSHARD;
+    if (t < NCOUNT && acc[t]) {
+        if (t < CNT_MAX) atomicAdd(&shards[s].f[t], acc[t]);
+        else atomicMax(&shards[s].f[t], acc[t]);
+    }
+}
+
+// After add_counts and this thread's other stores: true in every thread of
+// the workgroup that finishes last, whose acc then holds the totals of the
+// whole grid.
+__device__ inline bool sum_counts(unsigned long long* acc, Shard* shards, int32_t* top, int* sh) {
+    const int t = threadIdx.x, s = blockIdx.x % NSHARD;
+    wait_mem();  // the counters are out before the workgroup counts as done
+    __syncthreads();
+    if (t == 0) {
+        *sh = 0;
+        const int members = ((int)gridDim.x - s + NSHARD - 1) / NSHARD;
+        if (members == 1 || atomicAdd(&shards[s].done, 1) == members - 1) {
+            const int used = (int)gridDim.x < NSHARD ? (int)gridDim.x : NSHARD;
+            *sh = atomicAdd(top, 1) == used - 1;
+        }
+    }
+    __syncthreads();
+    if (!*sh) return false;
+    if (t < NCOUNT) {
+        unsigned long long v[NSHARD], r = 0;
+#pragma unroll
+        for (int u = 0; u < NSHARD; ++u)
+            v[u] = __hip_atomic_load(&shards[u].f[t], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+#pragma unroll
+        for (int u = 0; u < NSHARD; ++u) r = t < CNT_MAX ? r + v[u] : max(r, v[u]);
+        acc[t] = r;
+    }
+    __syncthreads();
+    return true;
+}
+
+// Rows of the two analysis passes are dealt to the workgroups CHUNK
+// consecutive rows at a time, chunk c to workgroup c mod grid, and a row of
+// more than long_row entries is walked by a whole wavefront, not by its few
+// lanes: the hub rows of a power-law matrix (low row indices) would otherwise
+// sit in a few workgroups that walk them in hundreds of dependent round trips
+// while the rest of the grid is done (R-MAT scale 18: 0.67 and 0.75 ms for
+// the two passes, nearly all of it that).
+// Lanes per row L: with at least SHORT_MIN_ROWS rows of at most SHORT_ROWS
+// entries on average every row gets one lane, which takes eight of its
+// entries at a time with two 16-byte loads: several lanes per row leave most
+// of them idle there while every instruction is paid for (2.1M rows of 1
+// entry of B: 94 us with 8 lanes, 26 with one; of 7 entries of A: 113 us with
+// 4 lanes, 72 with one).  Longer rows read better coalesced with several (1M
+// rows of 27 entries of B: 138 us with one lane, 102 with eight), and below
+// SHORT_MIN_ROWS the chip is not full (4096 rows of A: 9 us against 16).
+constexpr int SHORT_ROWS = 8;
+constexpr int SHORT_MIN_ROWS = 1 << 17;
+template <int L>
+constexpr int long_row() {
+    return L == 8 ? 128 : 64;
+}
+// A chunk is a wavefront's rows: neighbouring rows share what they gather and
+// the cache lines that they write.  One row where a single pass covers all
+// (m up to 131072): everything is in cache then, and the hub rows spread best
+// (R-MAT scale 13: 51 us with chunks of 16 rows).
+// The row of thread group `g` of the workgroup's 256 / L in pass `pass`:
+template <int L>
+__device__ inline int64_t dealt_row(int64_t pass, int64_t passes, int g) {
+    const int C = passes == 1 ? 1 : 64 / L, per = 256 / L / C;
+    const int64_t chunk = (pass * per + g / C) * gridDim.x + blockIdx.x;
+    return chunk * C + g % C;
 }
 
 // Reductions over aligned groups of AN_LANES = 4 lanes with DPP: swaps of
@@ -70,120 +150,221 @@ __device__ inline float log2p1(int64_t v) { return log2f(1.0f + (float)v); }
 // bound on the row's occupied blocks (binning 0: its products, 2: the
 // compressed-B runs it reads, 3: the exact count of a previous run) or
 // features only (binning 1, learned: classified by k_mlp_classify).
+struct RowSums {
+    int64_t ub = 0, rs = 0;  // products; compressed-B runs (a bound on occupied blocks)
+    int mx = 0, cmin = INT_MAX, cmax = -1, bad = 0, diag = 0;
+};
+
+// Entries q..q+7 of an index array of `total` (those past its end: the last
+// one), with two 16-byte loads (dword-aligned) unless they reach past it.
+struct __attribute__((packed, aligned(4))) I4 {
+    int x, y, z, w;
+};
+__device__ inline void load8(int* c, const int32_t* __restrict__ p, int32_t q, int64_t total) {
+    if (q + (int64_t)8 <= total) {
+        const I4 a = *reinterpret_cast<const I4*>(p + q), b = *reinterpret_cast<const I4*>(p + q + 4);
+        c[0] = a.x, c[1] = a.y, c[2] = a.z, c[3] = a.w;
+        c[4] = b.x, c[5] = b.y, c[6] = b.z, c[7] = b.w;
+    } else {
+#pragma unroll
+        for (int u = 0; u < 8; ++u) c[u] = p[min((int64_t)q + u, total - 1)];
+    }
+}
+
+// U entries of a row at p0, p0 + step, ... per lane (STEP1: eight at p0 on): independent index loads,
+// then their gathers.  Every load is unconditional (indices clamped into the
+// row, and to B's first row for entries that are past the row's end or
+// invalid; n > 0 whenever the row has an entry that can be valid) and its
+// value is discarded afterwards where it does not count: a load under a
+// condition with a default in the other branch makes the compiler wait for
+// it before the next one is issued.
+template <int U, bool STEP1 = false>
+__device__ inline void row_entries(RowSums& r, const int32_t* __restrict__ aci, int64_t annz,
+                                   const int4* __restrict__ binfo, int32_t n, int64_t row, int32_t p0, int step,
+                                   int32_t e) {
+    int jj[U];
+    if constexpr (STEP1) {
+        static_assert(U == 8, "load8");
+        load8(jj, aci, p0, annz);
+    } else {
+#pragma unroll
+        for (int u = 0; u < U; ++u) jj[u] = aci[min(p0 + u * step, e - 1)];
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        const bool in_row = p0 + u * step < e;
+        if (in_row && (jj[u] < 0 || jj[u] >= n)) r.bad = ERR_A_COL;
+        if (!in_row || jj[u] < 0 || jj[u] >= n) jj[u] = -1;
+        r.diag |= jj[u] == row;  // a stored diagonal entry (square A)
+    }
+    if (n <= 0) return;  // every entry is invalid: nothing to gather
+    int4 bb[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) bb[u] = binfo[max(jj[u], 0)];
+    int ub = 0, rs = 0;  // U rows of B: below 2^34 in all, so 64 bits only where a row is that long
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        if (jj[u] < 0) continue;
+        if (bb[u].x >= 1 << 26) {
+            r.ub += bb[u].x, r.rs += bb[u].w;
+        } else {
+            ub += bb[u].x, rs += bb[u].w;
+        }
+        r.mx = max(r.mx, bb[u].x);
+        r.cmin = min(r.cmin, bb[u].y);
+        r.cmax = max(r.cmax, bb[u].z);
+    }
+    r.ub += ub, r.rs += rs;
+}
+
+template <typename T, typename Op>
+__device__ inline T wave_reduce(T v, Op op) {
+    for (int d = 32; d > 0; d >>= 1) v = op(v, (T)__shfl_xor(v, d, 64));
+    return v;
+}
+
+template <int L>
 __global__ __launch_bounds__(256) void k_a_rowinfo(int32_t m, int32_t n, const int32_t* __restrict__ arp,
                                                    const int32_t* __restrict__ aci, int64_t annz,
                                                    const int4* __restrict__ binfo, RowInfo* __restrict__ rinfo,
                                                    float* __restrict__ feats, ClassCfg cfg, int binning,
                                                    uint8_t* __restrict__ sym_cls, int32_t* __restrict__ row_nnz,
                                                    int32_t* __restrict__ row_blocks, int32_t* __restrict__ lofs,
-                                                   Control* ctl) {
-    __shared__ int32_t hist[NCLS];
-    __shared__ int32_t empties, nodiag;
-    __shared__ unsigned long long prod_sum, wmax_all, wmax_glob, pmax;
-    if (threadIdx.x < NCLS) hist[threadIdx.x] = 0;
-    if (threadIdx.x == 0) empties = 0, nodiag = 0, prod_sum = 0, wmax_all = 0, wmax_glob = 0, pmax = 0;
+                                                   Shard* shards, Control* ctl) {
+    constexpr int GROUPS = 256 / L;
+    static_assert(L == 1 || L == AN_LANES, "one lane, or the quad that the reductions cover");
+    __shared__ unsigned long long acc[NCOUNT];
+    __shared__ int32_t longs[GROUPS];
+    __shared__ int nlong[2], sh;  // by pass parity: a wavefront may be a pass ahead of another's reading
+    if (threadIdx.x < NCOUNT) acc[threadIdx.x] = 0;
+    if (threadIdx.x < 2) nlong[threadIdx.x] = 0;
     __syncthreads();
-    const int lane = (int)(threadIdx.x % AN_LANES);
-    const int64_t rows_per_block = blockDim.x / AN_LANES;
-    // grid-stride: few workgroups, one flush of the counters each
-    for (int64_t rb = blockIdx.x * rows_per_block; rb < m; rb += (int64_t)gridDim.x * rows_per_block) {
-        const int64_t row = rb + threadIdx.x / AN_LANES;
-        int64_t ub = 0, rs = 0;  // products; compressed-B runs (a bound on occupied blocks)
-        int mx = 0, cmin = INT_MAX, cmax = -1, bad = 0, len = 0, diag = 0;
-        if (row < m) {
-            int32_t s = arp[row], e = arp[row + 1];
-            if (s < 0 || e < s || (int64_t)e > annz || (row == 0 && s != 0) || (row == m - 1 && (int64_t)e != annz)) {
-                bad = ERR_A_ROWPTR;
-            } else {
-                len = e - s;
-                // independent index loads, then their gathers.  Every load is
-                // unconditional (indices clamped into the row, and to B's
-                // first row for entries that are past the row's end or
-                // invalid; n > 0 whenever the row has an entry that can be
-                // valid) and its value is discarded afterwards where it does
-                // not count: a load under a condition with a default in the
-                // other branch makes the compiler wait for it before the
-                // next one is issued.
-                for (int32_t p0 = s + lane; p0 < e; p0 += AN_LOADS * AN_LANES) {
-                    int jj[AN_LOADS];
-    #pragma unroll
-                    for (int u = 0; u < AN_LOADS; ++u) jj[u] = aci[min(p0 + u * AN_LANES, e - 1)];
-    #pragma unroll
-                    for (int u = 0; u < AN_LOADS; ++u) {
-                        const bool in_row = p0 + u * AN_LANES < e;
-                        if (in_row && (jj[u] < 0 || jj[u] >= n)) bad = ERR_A_COL;
-                        if (!in_row || jj[u] < 0 || jj[u] >= n) jj[u] = -1;
-                        diag |= jj[u] == row;  // a stored diagonal entry (square A)
-                    }
-                    if (n <= 0) continue;  // every entry is invalid: nothing to gather
-                    int4 bb[AN_LOADS];
-    #pragma unroll
-                    for (int u = 0; u < AN_LOADS; ++u) bb[u] = binfo[max(jj[u], 0)];
-    #pragma unroll
-                    for (int u = 0; u < AN_LOADS; ++u) {
-                        if (jj[u] < 0) continue;
-                        ub += bb[u].x;
-                        rs += bb[u].w;
-                        mx = max(mx, bb[u].x);
-                        cmin = min(cmin, bb[u].y);
-                        cmax = max(cmax, bb[u].z);
-                    }
-                }
-            }
+    // a lane's counts over its rows, added to the workgroup's counters at the
+    // end (classes once per run of equal ones): an LDS atomic per row and
+    // counter is sixteen lanes of a wavefront on one address each time
+    int n_empty = 0, n_nodiag = 0, cur = CLS_EMPTY, n_cur = 0;
+    int64_t t_prod = 0;
+    int32_t t_pmax = 0, t_words = 0, t_wglob = 0;
+    auto finish_row = [&](int64_t row, int len, const RowSums& r) {
+        const int64_t ub = r.bad ? 0 : r.ub;
+        const int32_t ubc = ub > INT_MAX ? INT_MAX : (int32_t)ub;
+        const int cmin = ub == 0 ? 0 : r.cmin, cmax = ub == 0 ? 0 : r.cmax;
+        if (m == n && !r.diag) ++n_nodiag;
+        rinfo[row] = make_int4(cmin, cmax, ubc, r.mx);
+        if (feats) {
+            feats[row * 3 + 0] = log2p1(len);
+            feats[row * 3 + 1] = log2p1(ub);
+            feats[row * 3 + 2] = log2p1(r.mx);
         }
-        ub = rowq_sum64(ub);
-        rs = rowq_sum64(rs);
-        mx = rowq_max(mx);
-        cmin = rowq_min(cmin);
-        cmax = rowq_max(cmax);
-        int anybad = rowq_or(bad);
-        diag = rowq_or(diag);
-        if (bad) atomicOr(&ctl->err, bad);
-        if (row < m && lane == 0 && m == n && !diag) atomicAdd(&nodiag, 1);
-        if (row < m && lane == 0) {
-            if (anybad) ub = 0;
-            int32_t ubc = ub > INT_MAX ? INT_MAX : (int32_t)ub;
-            if (ub == 0) cmin = 0, cmax = 0;
-            rinfo[row] = make_int4(cmin, cmax, ubc, mx);
-            if (feats) {
-                feats[row * 3 + 0] = log2p1(len);
-                feats[row * 3 + 1] = log2p1(ub);
-                feats[row * 3 + 2] = log2p1(mx);
+        if (ub == 0) {
+            row_nnz[row] = 0;
+            row_blocks[row] = 0;
+            sym_cls[row] = CLS_EMPTY;
+            ++n_empty;
+            return;
+        }
+        const int32_t words = row_words(cmin, cmax);
+        lofs[row] = list_capacity(r.rs, words);
+        t_words = max(t_words, words);
+        t_prod += ub;
+        t_pmax = max(t_pmax, ubc);
+        if (binning != 1) {
+            // binning 3 (ideal estimate): the row's exact occupied blocks, left in
+            // row_blocks by a previous symbolic run of the same matrices
+            const int64_t est = binning == 2 ? r.rs : binning == 3 ? (int64_t)row_blocks[row] : ub;
+            const int cls = sym_class(ub, cmin, cmax, est, cfg, true);
+            sym_cls[row] = (uint8_t)cls;
+            if (cls != cur) {
+                if (n_cur) atomicAdd(&acc[CNT_HIST + cur], (unsigned long long)n_cur);
+                cur = cls, n_cur = 0;
             }
-            int cls = CLS_EMPTY;
-            if (ub == 0) {
-                row_nnz[row] = 0;
-                row_blocks[row] = 0;
-                atomicAdd(&empties, 1);
-                sym_cls[row] = CLS_EMPTY;
-            } else {
-                int64_t words = row_words(cmin, cmax);
-                lofs[row] = list_capacity(rs, words);
-                atomicMax(&wmax_all, (unsigned long long)words);
-                atomicAdd(&prod_sum, (unsigned long long)ub);
-                atomicMax(&pmax, (unsigned long long)ub);
-                if (binning != 1) {
-                    // binning 3 (ideal estimate): the row's exact occupied blocks, left in
-                    // row_blocks by a previous symbolic run of the same matrices
-                    const int64_t est = binning == 2 ? rs : binning == 3 ? (int64_t)row_blocks[row] : ub;
-                    cls = sym_class(ub, cmin, cmax, est, cfg, true);
-                    sym_cls[row] = (uint8_t)cls;
-                    atomicAdd(&hist[cls], 1);
-                    if (cls % NTIER == TIER_GLOBAL) atomicMax(&wmax_glob, (unsigned long long)words);
-                }
+            ++n_cur;
+            if (cls % NTIER == TIER_GLOBAL) t_wglob = max(t_wglob, words);
+        }
+    };
+    const int lane = (int)(threadIdx.x % L), wl = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    const int64_t passes = ((int64_t)m + (int64_t)gridDim.x * GROUPS - 1) / ((int64_t)gridDim.x * GROUPS);
+    for (int64_t pass = 0; pass < passes; ++pass) {
+        const int64_t row = dealt_row<L>(pass, passes, threadIdx.x / L);
+        RowSums r;
+        int32_t s = 0, e = 0;
+        if (row < m) {
+            s = arp[row], e = arp[row + 1];
+            if (s < 0 || e < s || (int64_t)e > annz || (row == 0 && s != 0) || (row == m - 1 && (int64_t)e != annz))
+                r.bad = ERR_A_ROWPTR, s = e = 0;
+        }
+        const int len = e - s;
+        const bool put_off = len > long_row<L>();
+        if (put_off) {
+            if (lane == 0) longs[atomicAdd(&nlong[pass & 1], 1)] = (int32_t)row;
+            e = s;
+        }
+        // as many loads per round trip as the wavefront's longest row needs
+        if constexpr (L == 1) {
+            for (int32_t p0 = s; p0 < e; p0 += 8) row_entries<8, true>(r, aci, annz, binfo, n, row, p0, 1, e);
+        } else if (!__any(e - s > 2 * L)) {
+            if (s < e) row_entries<2>(r, aci, annz, binfo, n, row, s + lane, L, e);
+        } else {
+            for (int32_t p0 = s + lane; p0 < e; p0 += AN_LOADS * L)
+                row_entries<AN_LOADS>(r, aci, annz, binfo, n, row, p0, L, e);
+        }
+        if (r.bad) atomicOr(&ctl->err, r.bad);
+        if constexpr (L > 1) {
+            r.ub = rowq_sum64(r.ub);
+            r.rs = rowq_sum64(r.rs);
+            r.mx = rowq_max(r.mx);
+            r.cmin = rowq_min(r.cmin);
+            r.cmax = rowq_max(r.cmax);
+            r.bad = rowq_or(r.bad);
+            r.diag = rowq_or(r.diag);
+        }
+        if (row < m && lane == 0 && !put_off) finish_row(row, len, r);
+        __syncthreads();
+        const int nl = nlong[pass & 1];
+        if (nl > 0) {  // uniform; the pass's long rows, a wavefront each
+            for (int l = wv; l < nl; l += 4) {
+                const int64_t lrow = longs[l];
+                const int32_t ls = arp[lrow], le = arp[lrow + 1];
+                RowSums q;
+                for (int32_t p0 = ls + wl; p0 < le; p0 += AN_LOADS * 64)
+                    row_entries<AN_LOADS>(q, aci, annz, binfo, n, lrow, p0, 64, le);
+                auto add = [](auto x, auto y) { return x + y; };
+                auto hi = [](auto x, auto y) { return x > y ? x : y; };
+                if (q.bad) atomicOr(&ctl->err, q.bad);
+                q.ub = wave_reduce((long long)q.ub, add);
+                q.rs = wave_reduce((long long)q.rs, add);
+                q.mx = wave_reduce(q.mx, hi);
+                q.cmin = wave_reduce(q.cmin, [](auto x, auto y) { return x < y ? x : y; });
+                q.cmax = wave_reduce(q.cmax, hi);
+                q.bad = __any(q.bad) ? ERR_A_COL : 0;
+                q.diag = __any(q.diag);
+                if (wl == 0) finish_row(lrow, le - ls, q);
             }
+            __syncthreads();
+            if (threadIdx.x == 0) nlong[pass & 1] = 0;
+            __syncthreads();
         }
     }
+    if (n_cur) atomicAdd(&acc[CNT_HIST + cur], (unsigned long long)n_cur);
+    if (n_empty) atomicAdd(&acc[CNT_ROWS], (unsigned long long)n_empty);
+    if (n_nodiag) atomicAdd(&acc[CNT_NODIAG], (unsigned long long)n_nodiag);
+    if (t_prod) {
+        atomicAdd(&acc[CNT_PRODUCTS], (unsigned long long)t_prod);
+        atomicMax(&acc[CNT_MAXPROD], (unsigned long long)t_pmax);
+        atomicMax(&acc[CNT_WORDS], (unsigned long long)t_words);
+        if (t_wglob) atomicMax(&acc[CNT_WGLOB], (unsigned long long)t_wglob);
+    }
     __syncthreads();
-    // one global update per workgroup
-    if (threadIdx.x < NCLS && hist[threadIdx.x]) atomicAdd(&ctl->sym_hist[threadIdx.x], hist[threadIdx.x]);
+    add_counts(acc, shards);
+    if (!sum_counts(acc, shards, &ctl->done[0], &sh)) return;
+    if (threadIdx.x < NCLS) ctl->sym_hist[threadIdx.x] = (int32_t)acc[CNT_HIST + threadIdx.x];
     if (threadIdx.x == 0) {
-        if (empties) atomicAdd(&ctl->empty_rows, empties);
-        if (nodiag) atomicAdd(&ctl->a_missing_diag, nodiag);
-        if (prod_sum) atomicAdd((unsigned long long*)&ctl->products, prod_sum);
-        if (wmax_all) atomicMax((unsigned long long*)&ctl->max_words_all, wmax_all);
-        if (pmax) atomicMax((unsigned long long*)&ctl->max_products, pmax);
-        if (wmax_glob) atomicMax((unsigned long long*)&ctl->max_words_sym_global, wmax_glob);
+        ctl->empty_rows = (int32_t)acc[CNT_ROWS];
+        ctl->a_missing_diag = (int32_t)acc[CNT_NODIAG];
+        ctl->products = (int64_t)acc[CNT_PRODUCTS];
+        ctl->max_words_all = (int64_t)acc[CNT_WORDS];
+        ctl->max_products = (int64_t)acc[CNT_MAXPROD];
+        ctl->max_words_sym_global = (int64_t)acc[CNT_WGLOB];
     }
 }
 
@@ -321,22 +502,29 @@ __global__ __launch_bounds__(256) void k_scatter(int32_t m, const uint8_t* __res
     __shared__ int64_t wsum[4];
     __shared__ int64_t lbase;
     __shared__ uint8_t remap[NCLS];
+    __shared__ int32_t merged[NCLS];
     __shared__ int32_t chunk_sh;
     int32_t* ticket = state;
     uint64_t* status = reinterpret_cast<uint64_t*>(state + 16);
-    if (threadIdx.x == 0) {
-        int32_t h[NCLS], merged[NCLS];
-        for (int c = 0; c < NCLS; ++c) h[c] = hist[c];
-        merge_classes(h, remap, merged, merge != 0);
-        if (lofs) {
-            // symbolic rows tier-major (a persistent launch per tier takes its
-            // three modes as one range); the first workgroup publishes the ranges
-            sym_class_offsets(merged, off);
-            if (blockIdx.x == 0)
-                for (int c = 0; c < NCLS; ++c) ctl->sym_cnt[c] = merged[c], ctl->sym_off[c] = off[c];
-        } else {
-            int32_t run = 0;
-            for (int c = 0; c < NCLS; ++c) off[c] = run, run += merged[c];
+    // the class merge, a lane per table mode (in LDS: the arrays are indexed
+    // by loop-carried values, which in registers would mean scratch memory)
+    if (threadIdx.x < 3) merge_classes_mode(hist, remap, merged, threadIdx.x, merge != 0);
+    __syncthreads();
+    if (threadIdx.x < 64) {
+        // first slot of every class, in class order; symbolic rows tier-major
+        // (a persistent launch takes a tier's three modes as one range) and
+        // published by the first workgroup
+        const int l = threadIdx.x;
+        const int c = l < NCLS ? (lofs ? l % 3 * NTIER + l / 3 : l) : 0;
+        const int32_t v = l < NCLS ? merged[c] : 0;
+        int32_t x = v;
+        for (int d = 1; d < 32; d <<= 1) {
+            const int32_t y = __shfl_up(x, d, 64);
+            if (l >= d) x += y;
+        }
+        if (l < NCLS) {
+            off[c] = x - v;
+            if (lofs && blockIdx.x == 0) ctl->sym_cnt[c] = v, ctl->sym_off[c] = x - v;
         }
     }
     const int64_t nchunks = ((int64_t)m + SCATTER_CHUNK - 1) / SCATTER_CHUNK;
@@ -450,6 +638,7 @@ __global__ __launch_bounds__(256) void k_scatter(int32_t m, const uint8_t* __res
 // row's numeric class (its exact size is now known; rows without a list take
 // the global path) and counts rows whose symbolic class differed from the
 // class their true size asks for.
+template <int ITEMS>
 __global__ __launch_bounds__(SCAN_THREADS) void k_scan(int32_t m, const int32_t* __restrict__ row_nnz,
                                                        const int32_t* __restrict__ row_blocks,
                                                        const RowInfo* __restrict__ rinfo,
@@ -457,30 +646,28 @@ __global__ __launch_bounds__(SCAN_THREADS) void k_scan(int32_t m, const int32_t*
                                                        const uint8_t* __restrict__ sym_cls,
                                                        const int32_t* __restrict__ lofs,
                                                        int32_t* __restrict__ c_row_ptr, uint64_t* tile_status,
-                                                       ClassCfg cfg, uint8_t* __restrict__ num_cls, Control* ctl) {
+                                                       ClassCfg cfg, uint8_t* __restrict__ num_cls, Shard* shards,
+                                                       Control* ctl) {
     __shared__ int32_t tile_sh;
     __shared__ int64_t wsum[SCAN_THREADS / 64];
     __shared__ int64_t tile_prefix;
-    __shared__ int32_t hist[NCLS];
-    __shared__ unsigned long long s_annz[NCLS], s_cnnz[NCLS], s_prod[NCLS];
-    __shared__ int32_t mispred;
-    __shared__ unsigned long long wmax_glob;
-    if (threadIdx.x == 0) tile_sh = atomicAdd(&ctl->tile_counter, 1), mispred = 0, wmax_glob = 0;
-    if (threadIdx.x < NCLS) hist[threadIdx.x] = 0, s_annz[threadIdx.x] = 0, s_cnnz[threadIdx.x] = 0,
-                                    s_prod[threadIdx.x] = 0;
+    __shared__ unsigned long long acc[NCOUNT];
+    __shared__ int sh;
+    if (threadIdx.x == 0) tile_sh = atomicAdd(&ctl->tile_counter, 1);
+    if (threadIdx.x < NCOUNT) acc[threadIdx.x] = 0;
     __syncthreads();
     const int tile = tile_sh;
-    const int64_t r0 = (int64_t)tile * SCAN_TILE + threadIdx.x * SCAN_ITEMS;
-    int64_t v[SCAN_ITEMS];
+    const int64_t r0 = ((int64_t)tile * SCAN_THREADS + threadIdx.x) * ITEMS;
+    int64_t v[ITEMS];
     int64_t run = 0;
     // every row's inputs first, as unconditional loads (a row past the end
     // reads the last row's, unused; arp has m + 1 entries): a load under a
     // condition would be waited for before the next one is issued
-    int32_t nz[SCAN_ITEMS], bl[SCAN_ITEMS], lo[SCAN_ITEMS], ap[SCAN_ITEMS + 1];
-    RowInfo rf[SCAN_ITEMS];
-    uint8_t sc[SCAN_ITEMS];
+    int32_t nz[ITEMS], bl[ITEMS], lo[ITEMS], ap[ITEMS + 1];
+    RowInfo rf[ITEMS];
+    uint8_t sc[ITEMS];
 #pragma unroll
-    for (int t = 0; t < SCAN_ITEMS; ++t) {
+    for (int t = 0; t < ITEMS; ++t) {
         const int64_t rr = r0 + t < m ? r0 + t : m - 1;
         nz[t] = row_nnz[rr];
         rf[t] = rinfo[rr];
@@ -489,20 +676,20 @@ __global__ __launch_bounds__(SCAN_THREADS) void k_scan(int32_t m, const int32_t*
         sc[t] = sym_cls[rr];
     }
 #pragma unroll
-    for (int t = 0; t <= SCAN_ITEMS; ++t) ap[t] = arp[r0 + t < m ? r0 + t : m];
+    for (int t = 0; t <= ITEMS; ++t) ap[t] = arp[r0 + t < m ? r0 + t : m];
     // the thread's consecutive rows of one class are counted in registers and
     // added to the workgroup's counters once per run of equal classes
     int cur = CLS_EMPTY, n_cur = 0, miss = 0;
     unsigned long long a_cur = 0, c_cur = 0, p_cur = 0;
     auto flush = [&]() {
         if (cur == CLS_EMPTY) return;
-        atomicAdd(&hist[cur], n_cur);
-        atomicAdd(&s_annz[cur], a_cur);
-        atomicAdd(&s_cnnz[cur], c_cur);
-        atomicAdd(&s_prod[cur], p_cur);
+        atomicAdd(&acc[CNT_HIST + cur], (unsigned long long)n_cur);
+        atomicAdd(&acc[CNT_ANNZ + cur], a_cur);
+        atomicAdd(&acc[CNT_CNNZ + cur], c_cur);
+        atomicAdd(&acc[CNT_PROD + cur], p_cur);
     };
 #pragma unroll
-    for (int t = 0; t < SCAN_ITEMS; ++t) {
+    for (int t = 0; t < ITEMS; ++t) {
         int64_t r = r0 + t;
         int64_t c = 0;
         if (r < m) {
@@ -522,7 +709,7 @@ __global__ __launch_bounds__(SCAN_THREADS) void k_scan(int32_t m, const int32_t*
                 a_cur += (unsigned long long)(ap[t + 1] - ap[t]);
                 c_cur += (unsigned long long)c;
                 p_cur += (unsigned long long)ri.z;
-                if (nc % NTIER == TIER_GLOBAL) atomicMax(&wmax_glob, (unsigned long long)row_words(ri.x, ri.y));
+                if (nc % NTIER == TIER_GLOBAL) atomicMax(&acc[CNT_WGLOB], (unsigned long long)row_words(ri.x, ri.y));
                 // the class the exact size asks for, under the same sizing rule as the estimate's
                 miss += sym_class(ri.z, ri.x, ri.y, blocks, cfg, cfg.bound_est != 0) != sc[t];
             }
@@ -531,7 +718,7 @@ __global__ __launch_bounds__(SCAN_THREADS) void k_scan(int32_t m, const int32_t*
         v[t] = run;
     }
     flush();
-    if (miss) atomicAdd(&mispred, miss);
+    if (miss) atomicAdd(&acc[CNT_ROWS], (unsigned long long)miss);
     // block scan of the per-thread totals
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
     int64_t x = run;
@@ -547,34 +734,44 @@ __global__ __launch_bounds__(SCAN_THREADS) void k_scan(int32_t m, const int32_t*
         agg += wsum[u];
     }
     const int64_t thread_excl = wpre + x - run;
-    // decoupled look-back: publish the aggregate, then add predecessors
-    if (threadIdx.x == 0) {
-        int64_t prefix = 0;
-        if (tile == 0) {
-            __hip_atomic_store(&tile_status[0], ST_PRE | (uint64_t)agg, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        } else {
-            __hip_atomic_store(&tile_status[tile], ST_AGG | (uint64_t)agg, __ATOMIC_RELAXED,
+    add_counts(acc, shards);
+    // decoupled look-back: publish the aggregate, then add predecessors, 64
+    // tiles of them at a time by the first wavefront (one by one, a round
+    // trip each, it was most of this kernel at a few hundred tiles)
+    if (threadIdx.x < 64) {
+        if (threadIdx.x == 0)
+            __hip_atomic_store(&tile_status[tile], (tile == 0 ? ST_PRE : ST_AGG) | (uint64_t)agg, __ATOMIC_RELAXED,
                                __HIP_MEMORY_SCOPE_AGENT);
-            // tiles are numbered in the order they started, so every predecessor
-            // is resident or finished and each wait below ends
-            for (int t = tile - 1; t >= 0; --t) {
-                uint64_t st;
+        int64_t prefix = 0;
+        // tiles are numbered in the order they started, so every predecessor
+        // is resident or finished and each wait below ends
+        for (int t0 = tile - 1; t0 >= 0; t0 -= 64) {
+            const int t = t0 - lane;
+            uint64_t st = ST_PRE;  // past the first tile: nothing before
+            if (t >= 0) {
                 do {
                     st = __hip_atomic_load(&tile_status[t], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                 } while ((st >> 62) == 0);
-                prefix += (int64_t)(st & ST_VAL);
-                if ((st >> 62) == 2) break;
             }
-            __hip_atomic_store(&tile_status[tile], ST_PRE | (uint64_t)(prefix + agg), __ATOMIC_RELAXED,
-                               __HIP_MEMORY_SCOPE_AGENT);
+            const uint64_t pre = __ballot((st >> 62) == 2);
+            const int last = pre ? __builtin_ctzll(pre) : 63;  // the nearest tile whose prefix is known
+            int64_t v = lane <= last ? (int64_t)(st & ST_VAL) : 0;
+            for (int d = 32; d > 0; d >>= 1) v += __shfl_xor(v, d, 64);
+            prefix += v;
+            if (pre) break;
         }
-        tile_prefix = prefix;
+        if (threadIdx.x == 0) {
+            if (tile > 0)
+                __hip_atomic_store(&tile_status[tile], ST_PRE | (uint64_t)(prefix + agg), __ATOMIC_RELAXED,
+                                   __HIP_MEMORY_SCOPE_AGENT);
+            tile_prefix = prefix;
+        }
     }
     __syncthreads();
     const int64_t base = tile_prefix + thread_excl;
     bool ovf = false;
 #pragma unroll
-    for (int t = 0; t < SCAN_ITEMS; ++t) {
+    for (int t = 0; t < ITEMS; ++t) {
         int64_t r = r0 + t;
         if (r < m) {
             int64_t val = base + v[t];
@@ -585,15 +782,17 @@ __global__ __launch_bounds__(SCAN_THREADS) void k_scan(int32_t m, const int32_t*
     }
     if (tile == 0 && threadIdx.x == 0) c_row_ptr[0] = 0;
     if (ovf) atomicOr(&ctl->err, ERR_NNZ_OVERFLOW);
-    __syncthreads();
-    if (threadIdx.x < NCLS && hist[threadIdx.x]) {
-        atomicAdd(&ctl->num_hist[threadIdx.x], hist[threadIdx.x]);
-        atomicAdd((unsigned long long*)&ctl->num_a_nnz[threadIdx.x], s_annz[threadIdx.x]);
-        atomicAdd((unsigned long long*)&ctl->num_c_nnz[threadIdx.x], s_cnnz[threadIdx.x]);
-        atomicAdd((unsigned long long*)&ctl->num_products[threadIdx.x], s_prod[threadIdx.x]);
+    if (!sum_counts(acc, shards, &ctl->done[1], &sh)) return;
+    if (threadIdx.x < NCLS) {
+        ctl->num_hist[threadIdx.x] = (int32_t)acc[CNT_HIST + threadIdx.x];
+        ctl->num_a_nnz[threadIdx.x] = (int64_t)acc[CNT_ANNZ + threadIdx.x];
+        ctl->num_c_nnz[threadIdx.x] = (int64_t)acc[CNT_CNNZ + threadIdx.x];
+        ctl->num_products[threadIdx.x] = (int64_t)acc[CNT_PROD + threadIdx.x];
     }
-    if (threadIdx.x == 0 && mispred) atomicAdd(&ctl->mispredicted, mispred);
-    if (threadIdx.x == 0 && wmax_glob) atomicMax((unsigned long long*)&ctl->max_words_num_global, wmax_glob);
+    if (threadIdx.x == 0) {
+        ctl->mispredicted = (int32_t)acc[CNT_ROWS];
+        ctl->max_words_num_global = (int64_t)acc[CNT_WGLOB];
+    }
 }
 
 __global__ void k_export_rows(int32_t m, const float* __restrict__ feats, const int32_t* __restrict__ row_blocks,
@@ -661,102 +860,228 @@ __device__ inline int row8_reduce(int v, Op op) {
 // run's bits, and the lane holding a run's last entry writes it at the run's
 // index (runs begun before it in the row).  A malformed row gets length and
 // runs 0 and raises the error flag, on which every later kernel exits.
+struct BRow {
+    int bad = 0;
+    int done = 0;          // runs begun in earlier chunks
+    int mn = INT_MAX, mx = -1;
+    uint32_t carry = 0;    // bits of the run still open at the end of the last chunk
+    int last_blk = -1;     // block of the last chunk's final entry
+};
+
+// U chunks of the row from entry Q0 on.  Unconditional loads, indices clamped
+// into the row (a load under a condition would be waited for before the next
+// one is issued); entries past the row's end are not used.
+template <int U>
+__device__ inline void b_chunks(BRow& r, const int32_t* __restrict__ bci, int2* __restrict__ bc, int32_t k, int32_t s,
+                                int32_t e, int32_t Q0, int sl, int shift) {
+    constexpr int L = ROW_LANES;
+    static_assert(L == 8, "the DPP shifts and swizzles below assume 8-lane groups");
+    int cc[U], nx[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        const int32_t q = Q0 + u * L + sl;
+        cc[u] = bci[min(q, e - 1)];
+        nx[u] = bci[min(q + 1, e - 1)];
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        const int32_t q0 = Q0 + u * L;
+        if (q0 >= e) break;  // uniform in the row's lanes
+        const int32_t q = q0 + sl;
+        const bool v = q < e;
+        const int c = cc[u];
+        if (v) {
+            if (c < 0 || c >= k) r.bad = ERR_B_COL;
+            r.mn = min(r.mn, c);
+            r.mx = max(r.mx, c);
+        }
+        const int blk = v ? c >> 5 : -1;
+        // neighbours inside the 8-lane group: DPP row shifts (a group is an
+        // aligned half of a 16-lane row; the lanes whose neighbour lies
+        // outside the group take it from elsewhere)
+        int prev = __builtin_amdgcn_mov_dpp(blk, 0x111, 0xf, 0xf, false);  // row_shr:1
+        if (sl == 0) prev = r.last_blk;
+        int next = __builtin_amdgcn_mov_dpp(blk, 0x101, 0xf, 0xf, false);  // row_shl:1
+        if (sl == L - 1) next = q + 1 < e ? nx[u] >> 5 : -1;
+        const int start = v && blk != prev;
+        const bool last = v && (q + 1 >= e || next != blk);
+        // segmented inclusive OR of the column bits, segments begin at run starts
+        uint32_t m = v ? 1u << (c & 31) : 0u;
+        int f = start;
+        const auto seg_step = [&](uint32_t mu, int fu, int d) {
+            if (sl >= d && !f) {
+                m |= mu;
+                f = fu;
+            }
+        };
+        seg_step((uint32_t)__builtin_amdgcn_mov_dpp((int)m, 0x111, 0xf, 0xf, false),
+                 __builtin_amdgcn_mov_dpp(f, 0x111, 0xf, 0xf, false), 1);  // row_shr:1
+        seg_step((uint32_t)__builtin_amdgcn_mov_dpp((int)m, 0x112, 0xf, 0xf, false),
+                 __builtin_amdgcn_mov_dpp(f, 0x112, 0xf, 0xf, false), 2);  // row_shr:2
+        seg_step((uint32_t)__builtin_amdgcn_mov_dpp((int)m, 0x114, 0xf, 0xf, false),
+                 __builtin_amdgcn_mov_dpp(f, 0x114, 0xf, 0xf, false), 4);  // row_shr:4
+        if (!f) m |= r.carry;
+        const uint64_t starts = (__ballot(start) >> shift) & ((1ull << L) - 1);
+        const int idx = r.done + __popcll(starts & ((2ull << sl) - 1)) - 1;
+        if (last) bc[s + idx] = make_int2(blk, (int)m);
+        r.done += __popcll(starts);
+        // lane 7 of each group to the whole group: swizzle lane -> (lane & 0x18) | 7
+        r.carry = (uint32_t)__builtin_amdgcn_ds_swizzle((int)m, 0xF8);
+        r.last_blk = __builtin_amdgcn_ds_swizzle(blk, 0xF8);
+    }
+}
+
+// A row by one lane, eight entries at a time; its runs are written as they end.
+__device__ inline void b_lane(BRow& r, const int32_t* __restrict__ bci, int64_t bnnz, int2* __restrict__ bc, int32_t k,
+                              int32_t s, int32_t e) {
+    int blk = -1;
+    uint32_t m = 0;  // the open run
+    int2* out = bc + s;
+    for (int32_t q = s; q < e; q += 8) {
+        int c[8];
+        load8(c, bci, q, bnnz);
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+            if (q + u >= e) break;
+            if ((unsigned)c[u] >= (unsigned)k) r.bad = ERR_B_COL;
+            r.mn = min(r.mn, c[u]);
+            r.mx = max(r.mx, c[u]);
+            const int b = c[u] >> 5;
+            if (b != blk) {
+                if (m) out[r.done++] = make_int2(blk, (int)m);
+                blk = b, m = 0;
+            }
+            m |= 1u << (c[u] & 31);
+        }
+    }
+    if (m) out[r.done++] = make_int2(blk, (int)m);
+}
+
+// 64 U entries of a row from Q0 on by a whole wavefront, as b_chunks.
+template <int U>
+__device__ inline void b_wave(BRow& r, const int32_t* __restrict__ bci, int2* __restrict__ bc, int32_t k, int32_t s,
+                              int32_t e, int32_t Q0, int wl) {
+    int cc[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) cc[u] = bci[min(Q0 + u * 64 + wl, e - 1)];
+    const int after = bci[min(Q0 + U * 64, e - 1)];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        const int32_t q = Q0 + u * 64 + wl;
+        if (Q0 + u * 64 >= e) break;  // uniform
+        const bool v = q < e;
+        const int c = cc[u];
+        if (v) {
+            if (c < 0 || c >= k) r.bad = ERR_B_COL;
+            r.mn = min(r.mn, c);
+            r.mx = max(r.mx, c);
+        }
+        const int blk = v ? c >> 5 : -1;
+        int prev = __shfl_up(blk, 1, 64);
+        if (wl == 0) prev = r.last_blk;
+        int next = __shfl_down(blk, 1, 64);
+        const int nx = u + 1 < U ? __builtin_amdgcn_readlane(cc[u + 1 < U ? u + 1 : u], 0) : after;
+        if (wl == 63) next = q + 1 < e ? nx >> 5 : -1;
+        const bool start = v && blk != prev;
+        const bool last = v && (q + 1 >= e || next != blk);
+        const uint64_t starts = __ballot(start);
+        // segmented inclusive OR over the wavefront: DPP shifts inside rows of
+        // 16 lanes, then broadcasts of lanes 15 and 31 into the rows after
+        uint32_t m = v ? 1u << (c & 31) : 0u;
+        int f = start;
+        const auto seg_step = [&](int mu, int fu, bool has) {
+            if (has && !f) m |= (uint32_t)mu, f = fu;
+        };
+        const int l16 = wl & 15;
+        seg_step(__builtin_amdgcn_mov_dpp((int)m, 0x111, 0xf, 0xf, false),
+                 __builtin_amdgcn_mov_dpp(f, 0x111, 0xf, 0xf, false), l16 >= 1);  // row_shr:1
+        seg_step(__builtin_amdgcn_mov_dpp((int)m, 0x112, 0xf, 0xf, false),
+                 __builtin_amdgcn_mov_dpp(f, 0x112, 0xf, 0xf, false), l16 >= 2);  // row_shr:2
+        seg_step(__builtin_amdgcn_mov_dpp((int)m, 0x114, 0xf, 0xf, false),
+                 __builtin_amdgcn_mov_dpp(f, 0x114, 0xf, 0xf, false), l16 >= 4);  // row_shr:4
+        seg_step(__builtin_amdgcn_mov_dpp((int)m, 0x118, 0xf, 0xf, false),
+                 __builtin_amdgcn_mov_dpp(f, 0x118, 0xf, 0xf, false), l16 >= 8);  // row_shr:8
+        seg_step(__builtin_amdgcn_update_dpp(0, (int)m, 0x142, 0xa, 0xf, false),
+                 __builtin_amdgcn_update_dpp(0, f, 0x142, 0xa, 0xf, false), (wl & 16) != 0);  // row_bcast:15
+        seg_step(__builtin_amdgcn_update_dpp(0, (int)m, 0x143, 0xc, 0xf, false),
+                 __builtin_amdgcn_update_dpp(0, f, 0x143, 0xc, 0xf, false), wl >= 32);  // row_bcast:31
+        if (!f) m |= r.carry;
+        const int idx = r.done + __popcll(starts & ((2ull << wl) - 1)) - 1;
+        if (last) bc[s + idx] = make_int2(blk, (int)m);
+        r.done += __popcll(starts);
+        r.carry = (uint32_t)__builtin_amdgcn_readlane((int)m, 63);
+        r.last_blk = __builtin_amdgcn_readlane(blk, 63);
+    }
+}
+
+template <int L>
 __global__ __launch_bounds__(256) void k_b_rows(int32_t n, int32_t k, const int32_t* __restrict__ brp,
                                                 const int32_t* __restrict__ bci, int64_t bnnz, int4* __restrict__ binfo,
                                                 int2* __restrict__ bc, int4* __restrict__ bhdr, Control* ctl) {
-    constexpr int L = ROW_LANES;
-    static_assert(L == 8, "the DPP shifts and swizzles below assume 8-lane groups");
-    __shared__ unsigned long long runs_sum;
-    if (threadIdx.x == 0) runs_sum = 0;
+    constexpr int GROUPS = 256 / L;
+    static_assert(L == 1 || L == ROW_LANES, "one lane, or the group that b_chunks covers");
+    __shared__ int32_t longs[GROUPS];
+    __shared__ int nlong[2];  // by pass parity: a wavefront may be a pass ahead of another's reading
+    if (threadIdx.x < 2) nlong[threadIdx.x] = 0;
     __syncthreads();
-    const int sl = threadIdx.x % L;
-    const int shift = (threadIdx.x & 63) & ~(L - 1);
-    const int64_t stride = (int64_t)gridDim.x * blockDim.x / L;
-    for (int64_t j = (blockIdx.x * (int64_t)blockDim.x + threadIdx.x) / L; j < n; j += stride) {
-        const int32_t s = brp[j], e = brp[j + 1];
-        int bad = 0;
-        if (s < 0 || e < s || (int64_t)e > bnnz || (j == 0 && s != 0) || (j == n - 1 && (int64_t)e != bnnz))
-            bad = ERR_B_ROWPTR;
-        int done = 0;          // runs begun in earlier chunks
-        int mn = INT_MAX, mx = -1;
-        uint32_t carry = 0;    // bits of the run still open at the end of the last chunk
-        int last_blk = -1;     // block of the last chunk's final entry
-        // four chunks' entries (and the entry after each chunk) are loaded at once
-        for (int32_t Q0 = s; !bad && Q0 < e; Q0 += 4 * L) {
-            // unconditional loads, indices clamped into the row (a load under
-            // a condition would be waited for before the next one is issued);
-            // entries past the row's end are not used
-            int cc[4], nx[4];
-#pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                const int32_t q = Q0 + u * L + sl;
-                cc[u] = bci[min(q, e - 1)];
-                nx[u] = bci[min(q + 1, e - 1)];
-            }
-#pragma unroll
-            for (int u = 0; u < 4; ++u) {
-            const int32_t q0 = Q0 + u * L;
-            if (q0 >= e) break;  // uniform in the row's lanes
-            const int32_t q = q0 + sl;
-            const bool v = q < e;
-            const int c = cc[u];
-            if (v) {
-                if (c < 0 || c >= k) bad = ERR_B_COL;
-                mn = min(mn, c);
-                mx = max(mx, c);
-            }
-            const int blk = v ? c >> 5 : -1;
-            // neighbours inside the 8-lane group: DPP row shifts (a group is an
-            // aligned half of a 16-lane row; the lanes whose neighbour lies
-            // outside the group take it from elsewhere)
-            int prev = __builtin_amdgcn_mov_dpp(blk, 0x111, 0xf, 0xf, false);  // row_shr:1
-            if (sl == 0) prev = last_blk;
-            int next = __builtin_amdgcn_mov_dpp(blk, 0x101, 0xf, 0xf, false);  // row_shl:1
-            if (sl == L - 1) next = q + 1 < e ? nx[u] >> 5 : -1;
-            const int start = v && blk != prev;
-            const bool last = v && (q + 1 >= e || next != blk);
-            // segmented inclusive OR of the column bits, segments begin at run starts
-            uint32_t m = v ? 1u << (c & 31) : 0u;
-            int f = start;
-            const auto seg_step = [&](uint32_t mu, int fu, int d) {
-                if (sl >= d && !f) {
-                    m |= mu;
-                    f = fu;
-                }
-            };
-            seg_step((uint32_t)__builtin_amdgcn_mov_dpp((int)m, 0x111, 0xf, 0xf, false),
-                     __builtin_amdgcn_mov_dpp(f, 0x111, 0xf, 0xf, false), 1);  // row_shr:1
-            seg_step((uint32_t)__builtin_amdgcn_mov_dpp((int)m, 0x112, 0xf, 0xf, false),
-                     __builtin_amdgcn_mov_dpp(f, 0x112, 0xf, 0xf, false), 2);  // row_shr:2
-            seg_step((uint32_t)__builtin_amdgcn_mov_dpp((int)m, 0x114, 0xf, 0xf, false),
-                     __builtin_amdgcn_mov_dpp(f, 0x114, 0xf, 0xf, false), 4);  // row_shr:4
-            if (!f) m |= carry;
-            const uint64_t starts = (__ballot(start) >> shift) & ((1ull << L) - 1);
-            const int idx = done + __popcll(starts & ((2ull << sl) - 1)) - 1;
-            if (last) bc[s + idx] = make_int2(blk, (int)m);
-            done += __popcll(starts);
-            // lane 7 of each group to the whole group: swizzle lane -> (lane & 0x18) | 7
-            carry = (uint32_t)__builtin_amdgcn_ds_swizzle((int)m, 0xF8);
-            last_blk = __builtin_amdgcn_ds_swizzle(blk, 0xF8);
-            }
-            bad = row8_reduce(bad, [](int x, int y) { return x | y; });
+    const int sl = threadIdx.x % L, wl = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    const int shift = wl & ~(L - 1);
+    auto finish_row = [&](int64_t j, int32_t s, int32_t e, const BRow& r) {
+        if (r.bad) {
+            atomicOr(&ctl->err, r.bad);
+            binfo[j] = make_int4(0, INT_MAX, -1, 0);
+            bhdr[j] = make_int4(0, 0, 0, 0);
+        } else {
+            binfo[j] = make_int4(e - s, r.mn, r.mx, r.done);
+            bhdr[j] = make_int4(s, e - s, s, r.done);
         }
-        mn = row8_reduce(mn, [](int x, int y) { return min(x, y); });
-        mx = row8_reduce(mx, [](int x, int y) { return max(x, y); });
-        if (sl == 0) {
-            if (bad) {
-                atomicOr(&ctl->err, bad);
-                binfo[j] = make_int4(0, INT_MAX, -1, 0);
-                bhdr[j] = make_int4(0, 0, 0, 0);
+    };
+    const int64_t passes = ((int64_t)n + (int64_t)gridDim.x * GROUPS - 1) / ((int64_t)gridDim.x * GROUPS);
+    for (int64_t pass = 0; pass < passes; ++pass) {
+        const int64_t j = dealt_row<L>(pass, passes, threadIdx.x / L);
+        BRow r;
+        int32_t s = 0, e = 0;
+        if (j < n) {
+            s = brp[j], e = brp[j + 1];
+            if (s < 0 || e < s || (int64_t)e > bnnz || (j == 0 && s != 0) || (j == n - 1 && (int64_t)e != bnnz))
+                r.bad = ERR_B_ROWPTR;
+        }
+        const bool put_off = !r.bad && e - s > long_row<L>();
+        if (put_off && sl == 0) longs[atomicAdd(&nlong[pass & 1], 1)] = (int32_t)j;
+        const int32_t len = r.bad || put_off ? 0 : e - s;
+        if constexpr (L == 1) {
+            if (len > 0) b_lane(r, bci, bnnz, bc, k, s, e);
+        } else {
+            // one chunk's loads where no row of the wavefront has more
+            if (!__any(len > L)) {
+                if (len > 0) b_chunks<1>(r, bci, bc, k, s, e, s, sl, shift);
             } else {
-                binfo[j] = make_int4(e - s, mn, mx, done);
-                bhdr[j] = make_int4(s, e - s, s, done);
-                if (done) atomicAdd(&runs_sum, (unsigned long long)done);
+                for (int32_t Q0 = s; Q0 < s + len; Q0 += 4 * L) b_chunks<4>(r, bci, bc, k, s, e, Q0, sl, shift);
             }
+            r.bad = row8_reduce(r.bad, [](int x, int y) { return x | y; });
+            r.mn = row8_reduce(r.mn, [](int x, int y) { return min(x, y); });
+            r.mx = row8_reduce(r.mx, [](int x, int y) { return max(x, y); });
+        }
+        if (sl == 0 && j < n && !put_off) finish_row(j, s, e, r);
+        __syncthreads();
+        const int nl = nlong[pass & 1];
+        if (nl > 0) {
+            // uniform; the pass's long rows, a wavefront each
+            for (int l = wv; l < nl; l += 4) {
+                const int64_t lj = longs[l];
+                const int32_t ls = brp[lj], le = brp[lj + 1];
+                BRow q;
+                for (int32_t Q0 = ls; Q0 < le; Q0 += 8 * 64) b_wave<8>(q, bci, bc, k, ls, le, Q0, wl);
+                q.bad = __any(q.bad) ? ERR_B_COL : 0;
+                q.mn = wave_reduce(q.mn, [](auto x, auto y) { return x < y ? x : y; });
+                q.mx = wave_reduce(q.mx, [](auto x, auto y) { return x > y ? x : y; });
+                if (wl == 0) finish_row(lj, ls, le, q);
+            }
+            __syncthreads();
+            if (threadIdx.x == 0) nlong[pass & 1] = 0;
+            __syncthreads();
         }
     }
-    __syncthreads();
-    if (threadIdx.x == 0 && runs_sum) atomicAdd((unsigned long long*)&ctl->bc_total, runs_sum);
 }
 
 inline unsigned grid_for(int64_t threads, int per_block) {
@@ -766,7 +1091,13 @@ inline unsigned grid_for(int64_t threads, int per_block) {
 
 }  // namespace
 
-int64_t scan_tiles(int32_t m) { return ((int64_t)m + SCAN_TILE - 1) / SCAN_TILE; }
+// Rows per thread of the scan: one for small m, where a thread's eight rows
+// one after another (two class choices each) are most of the kernel's time.
+constexpr int32_t SCAN_SMALL = 1 << 17;
+int64_t scan_tiles(int32_t m) {
+    const int64_t tile = SCAN_THREADS * (m <= SCAN_SMALL ? 1 : SCAN_ITEMS);
+    return ((int64_t)m + tile - 1) / tile;
+}
 
 void launch_pack(hipStream_t s, int32_t count, const int64_t* desc, const int32_t* rp_pool, const int32_t* col_pool,
                  int32_t* rp_out, int32_t* col_out, int32_t* err) {
@@ -789,19 +1120,36 @@ void launch_fill_u8(hipStream_t s, void* p, uint8_t v, int64_t bytes) {
     hipLaunchKernelGGL(k_fill_u8, dim3((unsigned)g), dim3(256), 0, s, (uint8_t*)p, v, bytes);
 }
 
+void launch_zero(hipStream_t s, void* p, int64_t bytes) {
+    if (bytes <= 0) return;
+    const int64_t n16 = bytes / 16;
+    hipLaunchKernelGGL(k_zero, dim3((unsigned)std::min<int64_t>((n16 + 255) / 256, 1024)), dim3(256), 0, s,
+                       (uint4*)p, n16);
+}
+
 void launch_b_rows(hipStream_t s, int32_t n, int32_t k, const int32_t* brp, const int32_t* bci, int64_t bnnz,
                    int4* binfo, int2* bc, int4* bhdr, Control* ctl) {
     if (n <= 0) return;
-    hipLaunchKernelGGL(k_b_rows, dim3(std::min(grid_for((int64_t)n * ROW_LANES, 256), 4096u)), dim3(256), 0, s, n, k,
-                       brp, bci, bnnz, binfo, bc, bhdr, ctl);
+    if (n >= SHORT_MIN_ROWS && bnnz <= (int64_t)SHORT_ROWS * n)
+        hipLaunchKernelGGL(k_b_rows<1>, dim3(std::min(grid_for(n, 256), 2048u)), dim3(256), 0, s, n, k, brp, bci, bnnz,
+                           binfo, bc, bhdr, ctl);
+    else
+        hipLaunchKernelGGL(k_b_rows<ROW_LANES>, dim3(std::min(grid_for((int64_t)n * ROW_LANES, 256), 4096u)),
+                           dim3(256), 0, s, n, k, brp, bci, bnnz, binfo, bc, bhdr, ctl);
 }
 
 void launch_a_rowinfo(hipStream_t s, int32_t m, int32_t n, const int32_t* arp, const int32_t* aci, int64_t annz,
                       const int4* binfo, RowInfo* rinfo, float* feats, ClassCfg cfg, int binning,
-                      uint8_t* sym_cls, int32_t* row_nnz, int32_t* row_blocks, int32_t* lofs, Control* ctl) {
+                      uint8_t* sym_cls, int32_t* row_nnz, int32_t* row_blocks, int32_t* lofs, Shard* shards,
+                      Control* ctl) {
     if (m <= 0) return;
-    hipLaunchKernelGGL(k_a_rowinfo, dim3(std::min(grid_for((int64_t)m * AN_LANES, 256), 4096u)), dim3(256), 0, s, m, n,
-                       arp, aci, annz, binfo, rinfo, feats, cfg, binning, sym_cls, row_nnz, row_blocks, lofs, ctl);
+    if (m >= SHORT_MIN_ROWS && annz <= (int64_t)SHORT_ROWS * m)
+        hipLaunchKernelGGL(k_a_rowinfo<1>, dim3(std::min(grid_for(m, 256), 2048u)), dim3(256), 0, s, m, n, arp, aci,
+                           annz, binfo, rinfo, feats, cfg, binning, sym_cls, row_nnz, row_blocks, lofs, shards, ctl);
+    else
+        hipLaunchKernelGGL(k_a_rowinfo<AN_LANES>, dim3(std::min(grid_for((int64_t)m * AN_LANES, 256), 2048u)),
+                           dim3(256), 0, s, m, n, arp, aci, annz, binfo, rinfo, feats, cfg, binning, sym_cls, row_nnz,
+                           row_blocks, lofs, shards, ctl);
 }
 
 void launch_mlp_classify(hipStream_t s, int32_t m, const float* feats, const float* w, const RowInfo* rinfo,
@@ -820,17 +1168,21 @@ void launch_scatter(hipStream_t s, int32_t m, const uint8_t* cls, int merge, con
                     int32_t* perm, const int32_t* arp, const int32_t* crp, int4* desc, int32_t* lofs, Control* ctl,
                     int64_t list_limit) {
     if (m <= 0) return;
-    launch_fill_u8(s, state, 0, (int64_t)scatter_state_bytes(m));
     hipLaunchKernelGGL(k_scatter, dim3(std::min(grid_for(m, SCATTER_CHUNK), 1024u)), dim3(256), 0, s, m, cls, merge,
                        hist, state, perm, arp, crp, desc, lofs, ctl, list_limit);
 }
 
 void launch_scan(hipStream_t s, int32_t m, const int32_t* row_nnz, const int32_t* row_blocks, const RowInfo* rinfo,
                  const int32_t* arp, const uint8_t* sym_cls, const int32_t* lofs, int32_t* c_row_ptr,
-                 uint64_t* tile_status, ClassCfg cfg, uint8_t* num_cls, Control* ctl) {
+                 uint64_t* tile_status, ClassCfg cfg, uint8_t* num_cls, Shard* shards, Control* ctl) {
     if (m <= 0) return;
-    hipLaunchKernelGGL(k_scan, dim3((unsigned)scan_tiles(m)), dim3(SCAN_THREADS), 0, s, m, row_nnz, row_blocks,
-                       rinfo, arp, sym_cls, lofs, c_row_ptr, tile_status, cfg, num_cls, ctl);
+    const dim3 grid((unsigned)scan_tiles(m));
+    if (m <= SCAN_SMALL)
+        hipLaunchKernelGGL(k_scan<1>, grid, dim3(SCAN_THREADS), 0, s, m, row_nnz, row_blocks, rinfo, arp, sym_cls, lofs,
+                           c_row_ptr, tile_status, cfg, num_cls, shards, ctl);
+    else
+        hipLaunchKernelGGL(k_scan<SCAN_ITEMS>, grid, dim3(SCAN_THREADS), 0, s, m, row_nnz, row_blocks, rinfo, arp,
+                           sym_cls, lofs, c_row_ptr, tile_status, cfg, num_cls, shards, ctl);
 }
 
 void launch_export_rows(hipStream_t s, int32_t m, const float* feats, const int32_t* row_blocks,
