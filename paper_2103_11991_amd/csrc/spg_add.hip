@@ -7,16 +7,20 @@
 // alpha*A(i,j) and beta*B(i,j) to those positions and writes the columns, so
 // a numeric call with new values needs no search at all.
 //
-// Per row, the entries' keys (column, then the entry's index inside the row:
-// A's entries first) are ordered, and a key whose column differs from its
-// predecessor's starts a new column of C.  When both rows are stored in
-// ascending column order, A's keys followed by B's in reverse form a bitonic
-// sequence, so the merge network of a bitonic sort alone orders them (log2 of
-// the row's length steps, section 2.3); otherwise the full bitonic sort runs
-// (section 5's team-level sort).  Rows of up to 64 entries sort in registers
-// with cross-lane swaps (one wavefront per row), rows of up to 1024 in the
+// A row whose entries are strictly ascending in both matrices (at most 64 in
+// all) needs no sort: an entry's position is its own index plus the entries
+// of the other matrix before its column (a binary search among the columns
+// in LDS) less the columns before it that both hold (a popcount of the
+// matches).  G lanes hold one row, 64 / G rows per wavefront (section 2.3's
+// sorted merge).  Other rows order their keys (column, then the entry's index
+// inside the row: A's entries first), and a key whose column differs from its
+// predecessor's starts a new column of C: rows of up to 256 entries with a
+// bitonic network over 32-bit keys in registers (one to four per lane, when
+// column and index fit 32 bits), rows of up to 1024 with 64-bit keys in the
 // wavefront's LDS, rows of up to 16384 on a 1024-lane workgroup with 128 KB
-// of LDS; longer rows are refused (SPG_ERR_UNSUPPORTED).
+// of LDS (section 5's team-level sort); longer rows are refused
+// (SPG_ERR_UNSUPPORTED).  In LDS, two sorted rows take the merge network
+// alone.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -29,6 +33,8 @@ namespace {
 
 constexpr int WAVE = 64;
 constexpr int MID_CAP = 1024;      // keys per wavefront in LDS
+constexpr int NUM_CAP = 512;       // columns per wavefront in LDS, numeric (16 KB per workgroup: full occupancy)
+constexpr int NUM_SEGMENTS = 8;    // numeric rows of more than this many times NUM_CAP columns sum in C's storage
 constexpr int LONG_CAP = 16384;    // keys per row on the long-row path
 constexpr int LONG_THREADS = 1024;
 constexpr int ROWS_PER_WG = 4;     // wavefronts (rows) per workgroup of the short/medium kernels
@@ -58,12 +64,6 @@ __device__ inline void wave_sync() {
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
 }
 
-__device__ inline uint64_t shfl_xor64(uint64_t v, int m) {
-    const uint32_t lo = (uint32_t)__shfl_xor((int)(uint32_t)v, m, WAVE);
-    const uint32_t hi = (uint32_t)__shfl_xor((int)(uint32_t)(v >> 32), m, WAVE);
-    return ((uint64_t)hi << 32) | lo;
-}
-
 // Inclusive sum over the wavefront.
 __device__ inline int wave_scan(int x) {
     const int lane = threadIdx.x & 63;
@@ -74,13 +74,20 @@ __device__ inline int wave_scan(int x) {
     return x;
 }
 
-// Key of entry t of the row (A's la entries, then B's): column, then t.
-__device__ inline uint64_t make_key(int32_t col, int t) { return ((uint64_t)(uint32_t)col << 32) | (uint32_t)t; }
-
-// Validity of the row's pointers and columns; the row's lengths.
-__device__ inline bool row_range(const int32_t* rp, int64_t nnz, int32_t m, int64_t i, int& s, int& e) {
-    s = rp[i], e = rp[i + 1];
-    return !(s < 0 || e < s || (int64_t)e > nnz || (i == 0 && s != 0) || (i == m - 1 && (int64_t)e != nnz));
+// Key of entry t of the row (A's la entries, then B's): column, then t, in
+// 64 bits, or in 32 where columns fit the 22 bits that MID_CAP's index leaves.
+constexpr int32_t KEY32_COLS = 1 << 22;
+template <typename K>
+constexpr int key_bits() {
+    return sizeof(K) == 8 ? 32 : 10;
+}
+template <typename K>
+__device__ inline K make_key(int32_t col, int t) {
+    return ((K)(uint32_t)col << key_bits<K>()) | (K)t;
+}
+template <typename K>
+__device__ inline int key_entry(K k) {
+    return (int)(k & (((K)1 << key_bits<K>()) - 1));
 }
 
 // The row's entries: t < la are A's, the others B's.
@@ -98,17 +105,17 @@ __device__ inline int merge_slot(int t, int la, int lb, int P) { return t < la ?
 // Writes each entry's position in C's row from the ordered keys (slot s
 // holds key[s]) and returns the row's size.  Lanes of the group own P/G
 // consecutive slots each.
-template <int G>
-__device__ inline int positions_from_sorted(const uint64_t* key, int P, int la, int32_t* apos, int32_t* bpos,
+template <int G, typename K>
+__device__ inline int positions_from_sorted(const K* key, int P, int la, int32_t* apos, int32_t* bpos,
                                             int* red) {
     const int lane = threadIdx.x % G;
     const int per = P / G > 0 ? P / G : 1;
     const int s0 = lane * per;
     int local = 0;
     for (int s = s0; s < s0 + per && s < P; ++s) {
-        const uint64_t k = key[s];
-        if (k == ~0ull) break;
-        local += s == 0 || (key[s - 1] >> 32) != (k >> 32);
+        const K k = key[s];
+        if (k == (K)~(K)0) break;
+        local += s == 0 || (key[s - 1] >> key_bits<K>()) != (k >> key_bits<K>());
     }
     int total, ex;
     if constexpr (G == WAVE) {
@@ -131,10 +138,10 @@ __device__ inline int positions_from_sorted(const uint64_t* key, int P, int la, 
     }
     int pos = ex - 1;
     for (int s = s0; s < s0 + per && s < P; ++s) {
-        const uint64_t k = key[s];
-        if (k == ~0ull) break;
-        pos += s == 0 || (key[s - 1] >> 32) != (k >> 32);
-        const int t = (int)(uint32_t)k;
+        const K k = key[s];
+        if (k == (K)~(K)0) break;
+        pos += s == 0 || (key[s - 1] >> key_bits<K>()) != (k >> key_bits<K>());
+        const int t = key_entry(k);
         if (t < la) apos[t] = pos;
         else bpos[t - la] = pos;
     }
@@ -144,8 +151,8 @@ __device__ inline int positions_from_sorted(const uint64_t* key, int P, int la, 
 // Bitonic ordering of P (a power of two) keys in LDS by a group of G lanes:
 // the merge network alone when the keys form a bitonic sequence, else the
 // whole sort.  sync() orders the group's LDS accesses.
-template <int G, typename Sync>
-__device__ inline void lds_bitonic(uint64_t* key, int P, bool merge_only, Sync sync) {
+template <int G, typename K, typename Sync>
+__device__ inline void lds_bitonic(K* key, int P, bool merge_only, Sync sync) {
     const int lane = threadIdx.x % G;
     for (int k = merge_only ? P : 2; k <= P; k <<= 1) {
         for (int j = k >> 1; j > 0; j >>= 1) {
@@ -154,7 +161,7 @@ __device__ inline void lds_bitonic(uint64_t* key, int P, bool merge_only, Sync s
                 const int lo = ((x & ~(j - 1)) << 1) | (x & (j - 1));
                 const int hi = lo | j;
                 const bool up = (lo & k) == 0;
-                const uint64_t a = key[lo], b = key[hi];
+                const K a = key[lo], b = key[hi];
                 if ((a > b) == up) key[lo] = b, key[hi] = a;
             }
             sync();
@@ -162,8 +169,140 @@ __device__ inline void lds_bitonic(uint64_t* key, int P, bool merge_only, Sync s
     }
 }
 
-// Symbolic phase for rows of at most MID_CAP entries (longer rows are queued
-// for k_add_sym_long).  One wavefront per row.
+// Lane ^ J of the wavefront (J a power of two below 64): quad permutes for 1
+// and 2, a swizzle inside 32 lanes up to 16, a permute across for 32.
+template <int J>
+__device__ inline uint32_t lane_xor(uint32_t v) {
+    if constexpr (J == 1) return (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0xb1, 0xf, 0xf, false);
+    else if constexpr (J == 2) return (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0x4e, 0xf, 0xf, false);
+    else if constexpr (J < 32) return (uint32_t)__builtin_amdgcn_ds_swizzle((int)v, (J << 10) | 0x1f);
+    else return (uint32_t)__shfl_xor((int)v, 32, WAVE);
+}
+
+// Bitonic sort of 64 R keys in registers, slot r * 64 + lane in v[r]; strides
+// of 64 and more stay inside a lane.
+template <int R, int K, int J>
+__device__ inline void sort_step(uint32_t* v) {
+    const int lane = threadIdx.x & 63;
+    if constexpr (J >= WAVE) {
+        constexpr int jr = J / WAVE;
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            if (r & jr) continue;
+            const bool up = ((r * WAVE) & K) == 0;  // K > J >= 64: the same for all lanes
+            const uint32_t lo = min(v[r], v[r | jr]), hi = max(v[r], v[r | jr]);
+            v[r] = up ? lo : hi, v[r | jr] = up ? hi : lo;
+        }
+    } else {
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            const uint32_t o = lane_xor<J>(v[r]);
+            const bool up = ((r * WAVE + lane) & K) == 0, low = (lane & J) == 0;
+            // the lower slot of a pair keeps the smaller key when ascending
+            v[r] = low == up ? min(v[r], o) : max(v[r], o);
+        }
+    }
+    if constexpr (J > 1) sort_step<R, K, J / 2>(v);
+    else if constexpr (K < WAVE * R) sort_step<R, 2 * K, K>(v);
+}
+
+// Positions of a row of la + lb <= 64 R entries by sorting; returns its size.
+template <int R>
+__device__ inline int sort_positions(const RowPair& rw, int32_t* ap, int32_t* bp) {
+    constexpr int TB = R == 1 ? 6 : R == 2 ? 7 : 8;  // bits of an entry's index
+    const int lane = threadIdx.x & 63, L = rw.la + rw.lb;
+    uint32_t v[R];
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        const int t = r * WAVE + lane;
+        v[r] = ~0u;
+        if (t < L) v[r] = ((uint32_t)rw.col(t) << TB) | (uint32_t)t;
+    }
+    sort_step<R, 2, 1>(v);
+    int before = 0;
+    uint32_t last = 0;  // key of the previous register's lane 63
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        uint32_t pv = (uint32_t)__shfl_up((int)v[r], 1, WAVE);
+        if (lane == 0) pv = last;
+        // valid keys come first: their count is L
+        const bool valid = r * WAVE + lane < L;
+        const bool start = valid && ((r == 0 && lane == 0) || (pv >> TB) != (v[r] >> TB));
+        const uint64_t starts = __ballot(start);
+        if (valid) {
+            const int t = (int)(v[r] & ((1u << TB) - 1u));
+            const int pos = before + __popcll(starts & ((2ull << lane) - 1)) - 1;
+            if (t < rw.la) ap[t] = pos;
+            else bp[t - rw.la] = pos;
+        }
+        before += __popcll(starts);
+        last = (uint32_t)__builtin_amdgcn_readlane((int)v[r], 63);
+    }
+    return before;
+}
+
+// One row by a whole wavefront, of at most MID_CAP entries (longer rows are
+// queued for k_add_sym_long).  Its pointers are valid.
+template <typename K>
+__device__ inline void wave_row(int64_t i, int32_t n, const RowPair& rw, int32_t* ap, int32_t* bp, K* key,
+                                int32_t* row_nnz, int32_t* long_list, AddCtl* ctl) {
+    const int lane = threadIdx.x % WAVE;
+    const int L = rw.la + rw.lb;
+    if (L > MID_CAP) {
+        if (lane == 0) {
+            long_list[atomicAdd(&ctl->long_rows, 1)] = (int32_t)i;
+            row_nnz[i] = 0;
+        }
+        return;
+    }
+    // columns in range, and whether each matrix row is ascending
+    int bad = 0, unsorted = 0;
+    for (int t = lane; t < L; t += WAVE) {
+        const int32_t c = rw.col(t);
+        bad |= c < 0 || c >= n;
+        if (t != 0 && t != rw.la && rw.col(t - 1) > c) unsorted = 1;
+    }
+    if (__any(bad)) {
+        if (lane == 0) atomicOr(&ctl->err, AE_COL), row_nnz[i] = 0;
+        return;
+    }
+    int total;
+    if (L <= WAVE && n <= 1 << 26) {
+        total = sort_positions<1>(rw, ap, bp);
+    } else if (L <= 2 * WAVE && n <= 1 << 25) {
+        total = sort_positions<2>(rw, ap, bp);
+    } else if (L <= 4 * WAVE && n <= 1 << 24) {
+        total = sort_positions<4>(rw, ap, bp);
+    } else {
+        // keys in the wavefront's LDS
+        const bool merge_only = !__any(unsorted);
+        int P = WAVE;
+        while (P < L) P <<= 1;
+        for (int s = lane; s < P; s += WAVE) key[s] = (K)~(K)0;
+        wave_sync();
+        for (int t = lane; t < L; t += WAVE) {
+            const int s = merge_only ? merge_slot(t, rw.la, rw.lb, P) : t;
+            key[s] = make_key<K>(rw.col(t), t);
+        }
+        wave_sync();
+        lds_bitonic<WAVE, K>(key, P, merge_only, wave_sync);
+        total = positions_from_sorted<WAVE, K>(key, P, rw.la, ap, bp, nullptr);
+        wave_sync();
+    }
+    if (lane == 0) row_nnz[i] = total;
+}
+
+// Symbolic phase.  G lanes per row: rows of at most G entries, strictly
+// ascending in A and in B, are merged in place, two of them per lane group
+// and step; every other row of the wavefront is then taken by the whole
+// wavefront, one after another.  Bound by its instructions per row and the
+// latency of a row's dependent accesses (pointers, columns, the search), hence
+// the two rows together, the next ones' pointers a step ahead, and 32-bit
+// keys (4 KB of LDS per wavefront, full occupancy) where columns allow (1M
+// rows of 30 + 30 entries, G = 64: 0.86 ms as a bitonic merge of 64-bit keys,
+// 0.48 as this search one row at a time, 0.32 now; 250k unsorted rows of 0 to
+// 96 entries: 0.39 ms with 64-bit keys through LDS permutes, 0.15 now).
+template <int G, typename K>
 __global__ __launch_bounds__(WAVE * ROWS_PER_WG) void k_add_sym(int32_t m, int32_t n, const int32_t* __restrict__ arp,
                                                                 const int32_t* __restrict__ aci, int64_t annz,
                                                                 const int32_t* __restrict__ brp,
@@ -171,91 +310,112 @@ __global__ __launch_bounds__(WAVE * ROWS_PER_WG) void k_add_sym(int32_t m, int32
                                                                 int32_t* __restrict__ apos, int32_t* __restrict__ bpos,
                                                                 int32_t* __restrict__ row_nnz,
                                                                 int32_t* __restrict__ long_list, AddCtl* ctl) {
-    __shared__ uint64_t keys[ROWS_PER_WG][MID_CAP];
-    const int wv = threadIdx.x / WAVE, lane = threadIdx.x % WAVE;
-    uint64_t* key = keys[wv];
-    for (int64_t i = (int64_t)blockIdx.x * ROWS_PER_WG + wv; i < m; i += (int64_t)gridDim.x * ROWS_PER_WG) {
+    constexpr int RPW = WAVE / G;  // lane groups per wavefront
+    constexpr int R = 2;           // rows per lane group and step
+    constexpr uint64_t ONES = G == WAVE ? ~0ull : (1ull << (G & 63)) - 1;
+    __shared__ K keys[ROWS_PER_WG][MID_CAP];
+    static_assert(sizeof(keys[0]) >= (size_t)R * 2 * WAVE * 4, "two lists of G columns per row");
+    const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x / WAVE);
+    const int wl = threadIdx.x % WAVE, lane = wl % G, sub = wl / G;
+    K* key = keys[wv];
+    const int64_t step = (int64_t)gridDim.x * ROWS_PER_WG * RPW * R;
+    // rows i0 + r * RPW + sub (a row past the end: the last, unused)
+    struct Ptr {
         int as, ae, bs, be;
-        const bool ok = row_range(arp, annz, m, i, as, ae) & row_range(brp, bnnz, m, i, bs, be);
-        if (!ok) {
-            if (lane == 0) atomicOr(&ctl->err, AE_ROWPTR), row_nnz[i] = 0;
-            continue;
+    };
+    auto ptrs = [&](int64_t i) {
+        i = i < m ? i : m - 1;
+        return Ptr{arp[i], arp[i + 1], brp[i], brp[i + 1]};
+    };
+    int64_t i0 = ((int64_t)blockIdx.x * ROWS_PER_WG + wv) * RPW * R;
+    Ptr nxt[R];
+#pragma unroll
+    for (int r = 0; r < R; ++r) nxt[r] = ptrs(i0 + r * RPW + sub);
+    for (; i0 < m; i0 += step) {
+        Ptr p[R];
+        int la[R], lb[R], c[R];
+        bool ok[R], has[R], strict[R];
+#pragma unroll
+        for (int r = 0; r < R; ++r) p[r] = nxt[r], nxt[r] = ptrs(i0 + step + r * RPW + sub);
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            const int64_t i = i0 + r * RPW + sub;
+            const bool valid = p[r].as >= 0 && p[r].ae >= p[r].as && (int64_t)p[r].ae <= annz && p[r].bs >= 0 &&
+                               p[r].be >= p[r].bs && (int64_t)p[r].be <= bnnz &&
+                               (i != 0 || (p[r].as == 0 && p[r].bs == 0)) &&
+                               (i != m - 1 || ((int64_t)p[r].ae == annz && (int64_t)p[r].be == bnnz));
+            ok[r] = i < m && valid;
+            if (i < m && !valid && lane == 0) atomicOr(&ctl->err, AE_ROWPTR), row_nnz[i] = 0;
+            la[r] = ok[r] ? p[r].ae - p[r].as : 0, lb[r] = ok[r] ? p[r].be - p[r].bs : 0;
+            if (la[r] > G || lb[r] > G - la[r]) la[r] = lb[r] = 0, strict[r] = false;  // not in place
+            else strict[r] = ok[r];
+            has[r] = lane < la[r] + lb[r];
+            c[r] = 0;
+            if (has[r]) c[r] = lane < la[r] ? aci[p[r].as + lane] : bci[p[r].bs + lane - la[r]];
         }
-        const RowPair rw{aci + as, bci + bs, ae - as, be - bs};
-        const int L = rw.la + rw.lb;
-        if (L > MID_CAP) {
-            if (lane == 0) {
-                long_list[atomicAdd(&ctl->long_rows, 1)] = (int32_t)i;
-                row_nnz[i] = 0;
-            }
-            continue;
-        }
-        // columns in range, and whether each matrix row is ascending
-        int bad = 0, unsorted = 0;
-        for (int t = lane; t < L; t += WAVE) {
-            const int32_t c = rw.col(t);
-            bad |= c < 0 || c >= n;
-            if (t != 0 && t != rw.la && rw.col(t - 1) > c) unsorted = 1;
-        }
-        if (__any(bad)) {
-            if (lane == 0) atomicOr(&ctl->err, AE_COL), row_nnz[i] = 0;
-            continue;
-        }
-        const bool merge_only = !__any(unsorted);
-        int32_t* ap = apos + as;
-        int32_t* bp = bpos + bs;
-        if (L <= WAVE) {
-            // one key per lane, the network in registers
-            const int slot = lane;
-            int P = 1;
-            while (P < L) P <<= 1;
-            // lane s holds slot s of the bitonic arrangement (or the whole input for a full sort)
-            uint64_t v = ~0ull;
-            if (merge_only) {
-                const int t = slot < rw.la ? slot : (P - 1 - slot) < rw.lb ? rw.la + (P - 1 - slot) : -1;
-                if (slot < P && t >= 0) v = make_key(rw.col(t), t);
-            } else if (slot < L) {
-                v = make_key(rw.col(slot), slot);
-            }
-            for (int k = merge_only ? P : 2; k <= P; k <<= 1)
-                for (int j = k >> 1; j > 0; j >>= 1) {
-                    const uint64_t o = shfl_xor64(v, j);
-                    const bool up = (slot & k) == 0;
-                    const bool low = (slot & j) == 0;
-                    // the lower slot of the pair keeps the smaller key when ascending
-                    const bool take = low == up ? o < v : o > v;
-                    if (slot < P && take) v = o;
-                }
-            // the previous slot's key (its column decides whether this one starts a column of C)
-            const uint32_t plo = (uint32_t)__shfl_up((int)(uint32_t)v, 1, WAVE);
-            const uint32_t phi = (uint32_t)__shfl_up((int)(uint32_t)(v >> 32), 1, WAVE);
-            const uint64_t pv = ((uint64_t)phi << 32) | plo;
-            const bool valid = v != ~0ull;
-            const int start = valid && (slot == 0 || (pv >> 32) != (v >> 32));
-            const int incl = wave_scan(start);
-            if (valid) {
-                const int t = (int)(uint32_t)v;
-                if (t < rw.la) ap[t] = incl - 1;
-                else bp[t - rw.la] = incl - 1;
-            }
-            const int total = __shfl(incl, WAVE - 1, WAVE);
-            if (lane == 0) row_nnz[i] = total;
-            continue;
-        }
-        // keys in the wavefront's LDS
-        int P = WAVE;
-        while (P < L) P <<= 1;
-        for (int s = lane; s < P; s += WAVE) key[s] = ~0ull;
-        wave_sync();
-        for (int t = lane; t < L; t += WAVE) {
-            const int s = merge_only ? merge_slot(t, rw.la, rw.lb, P) : t;
-            key[s] = make_key(rw.col(t), t);
+        // the row's two lists of columns, each padded to G with a column past all
+        wave_sync();  // the previous step's readers are done
+        int32_t* list[R];
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            list[r] = reinterpret_cast<int32_t*>(key) + r * 2 * WAVE + sub * 2 * G;
+            list[r][lane] = INT_MAX, list[r][G + lane] = INT_MAX;
         }
         wave_sync();
-        lds_bitonic<WAVE>(key, P, merge_only, wave_sync);
-        const int total = positions_from_sorted<WAVE>(key, P, rw.la, ap, bp, nullptr);
-        if (lane == 0) row_nnz[i] = total;
+        int longest = 0;
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            if (has[r]) list[r][lane < la[r] ? lane : G + lane - la[r]] = c[r];
+            // strictly ascending, except from A's last entry to B's first
+            const int prev = __shfl_up(c[r], 1, WAVE);
+            const bool wrong =
+                has[r] && (c[r] < 0 || c[r] >= n || (lane != 0 && lane != la[r] && prev >= c[r]));
+            if (__ballot(wrong) >> (sub * G) & ONES) strict[r] = false;
+            longest = max(longest, max(la[r], lb[r]));
+        }
         wave_sync();
+        // entries of the other list below this column: a count built bit by
+        // bit (an entry's own list is not empty, so the other has less than G)
+        int lo[R] = {};
+        const int32_t* other[R];
+#pragma unroll
+        for (int r = 0; r < R; ++r) other[r] = list[r] + (lane < la[r] ? G : 0);
+#pragma unroll
+        for (int h = G / 2; h >= 1; h >>= 1) {
+            if (!__any(longest >= h)) continue;
+#pragma unroll
+            for (int r = 0; r < R; ++r)
+                if (other[r][lo[r] + h - 1] < c[r]) lo[r] += h;
+        }
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            const int64_t i = i0 + r * RPW + sub;
+            const bool mine = has[r] && strict[r];
+            const bool match = mine && other[r][lo[r]] == c[r];
+            const uint64_t mt = __ballot(match) >> (sub * G) & ONES;
+            const uint64_t a_lanes = la[r] >= 64 ? ~0ull : (1ull << la[r]) - 1;
+            const uint64_t below = (1ull << lane) - 1;
+            if (mine) {
+                if (lane < la[r]) apos[p[r].as + lane] = lane + lo[r] - __popcll(mt & below);
+                else bpos[p[r].bs + lane - la[r]] = lane - la[r] + lo[r] - __popcll(mt & below & ~a_lanes);
+            }
+            if (strict[r] && lane == 0) row_nnz[i] = la[r] + lb[r] - __popcll(mt & a_lanes);
+        }
+        // the wavefront's other rows
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            uint64_t rest = __ballot(ok[r] && !strict[r] && lane == 0);
+            while (rest) {
+                const int src = __builtin_ctzll(rest);
+                rest &= rest - 1;
+                const int64_t ri = i0 + r * RPW + src / G;
+                const int ras = __builtin_amdgcn_readlane(p[r].as, src), rae = __builtin_amdgcn_readlane(p[r].ae, src);
+                const int rbs = __builtin_amdgcn_readlane(p[r].bs, src), rbe = __builtin_amdgcn_readlane(p[r].be, src);
+                const RowPair rw{aci + ras, bci + rbs, rae - ras, rbe - rbs};
+                wave_sync();
+                wave_row<K>(ri, n, rw, apos + ras, bpos + rbs, key, row_nnz, long_list, ctl);
+            }
+        }
     }
 }
 
@@ -305,11 +465,11 @@ __global__ __launch_bounds__(LONG_THREADS) void k_add_sym_long(int32_t n, const 
         __syncthreads();
         for (int t = tid; t < L; t += LONG_THREADS) {
             const int s = merge_only ? merge_slot(t, rw.la, rw.lb, P) : t;
-            key[s] = make_key(rw.col(t), t);
+            key[s] = make_key<uint64_t>(rw.col(t), t);
         }
         __syncthreads();
-        lds_bitonic<LONG_THREADS>(key, P, merge_only, [] { __syncthreads(); });
-        const int total = positions_from_sorted<LONG_THREADS>(key, P, rw.la, apos + as, bpos + bs, red);
+        lds_bitonic<LONG_THREADS, uint64_t>(key, P, merge_only, [] { __syncthreads(); });
+        const int total = positions_from_sorted<LONG_THREADS, uint64_t>(key, P, rw.la, apos + as, bpos + bs, red);
         if (tid == 0) row_nnz[i] = total;
         __syncthreads();
     }
@@ -348,28 +508,38 @@ __global__ __launch_bounds__(SCAN_THREADS) void k_add_scan(int32_t m, const int3
         if (u < wv) wpre += wsum[u];
         agg += wsum[u];
     }
-    if (threadIdx.x == 0) {
+    if (threadIdx.x < 64) {
+        // look-back over 64 tiles at a time (tiles are numbered in the order
+        // they started, so every wait ends)
+        if (threadIdx.x == 0)
+            __hip_atomic_store(&tile_status[tile], (tile == 0 ? ST_PRE : ST_AGG) | (uint64_t)agg, __ATOMIC_RELAXED,
+                               __HIP_MEMORY_SCOPE_AGENT);
         int64_t prefix = 0;
-        if (tile == 0) {
-            __hip_atomic_store(&tile_status[0], ST_PRE | (uint64_t)agg, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        } else {
-            __hip_atomic_store(&tile_status[tile], ST_AGG | (uint64_t)agg, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            for (int t = tile - 1; t >= 0; --t) {
-                uint64_t st;
+        for (int t0 = tile - 1; t0 >= 0; t0 -= 64) {
+            const int t = t0 - lane;
+            uint64_t st = ST_PRE;  // past the first tile: nothing before
+            if (t >= 0) {
                 do {
                     st = __hip_atomic_load(&tile_status[t], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                 } while ((st >> 62) == 0);
-                prefix += (int64_t)(st & ST_VAL);
-                if ((st >> 62) == 2) break;
             }
-            __hip_atomic_store(&tile_status[tile], ST_PRE | (uint64_t)(prefix + agg), __ATOMIC_RELAXED,
-                               __HIP_MEMORY_SCOPE_AGENT);
+            const uint64_t pre = __ballot((st >> 62) == 2);
+            const int last = pre ? __builtin_ctzll(pre) : 63;  // the nearest tile whose prefix is known
+            int64_t w = lane <= last ? (int64_t)(st & ST_VAL) : 0;
+            for (int d = 32; d > 0; d >>= 1) w += __shfl_xor(w, d, 64);
+            prefix += w;
+            if (pre) break;
         }
-        tile_prefix = prefix;
-        const int64_t last_tile = ((int64_t)m + SCAN_TILE - 1) / SCAN_TILE - 1;
-        if (tile == last_tile) {
-            ctl->nnz_c = prefix + agg;
-            if (prefix + agg > INT_MAX) atomicOr(&ctl->err, AE_OVERFLOW);
+        if (threadIdx.x == 0) {
+            if (tile > 0)
+                __hip_atomic_store(&tile_status[tile], ST_PRE | (uint64_t)(prefix + agg), __ATOMIC_RELAXED,
+                                   __HIP_MEMORY_SCOPE_AGENT);
+            tile_prefix = prefix;
+            const int64_t last_tile = ((int64_t)m + SCAN_TILE - 1) / SCAN_TILE - 1;
+            if (tile == last_tile) {
+                ctl->nnz_c = prefix + agg;
+                if (prefix + agg > INT_MAX) atomicOr(&ctl->err, AE_OVERFLOW);
+            }
         }
     }
     __syncthreads();
@@ -383,11 +553,64 @@ __global__ __launch_bounds__(SCAN_THREADS) void k_add_scan(int32_t m, const int3
 }
 
 // Numeric phase: per row, every entry adds alpha*a (A's first) or beta*b at
-// its position; columns written by every contributor (the same value).  Rows
-// of at most MID_CAP columns sum in the wavefront's LDS and copy out
-// coalesced; longer rows sum in C's own storage.  Entries of A are added
-// before those of B, so a column with one entry of each gets alpha*a + beta*b
-// exactly as written.
+// its position; columns written by every contributor (the same value).  The
+// values of NUM_CAP columns at a time are summed in the wavefront's LDS, in
+// FP64 (an LDS add of FP32 values serialises its lanes, see acc_bytes), and
+// copied out coalesced; rows of more than NUM_SEGMENTS times that sum in C's
+// own storage.  Entries of A are added before those of B, so a column with
+// one entry of each gets alpha*a + beta*b, each rounded once.  Two rows per
+// wavefront and step, their loads issued together and the next two rows'
+// pointers a step ahead: the kernel is bound by the latency of its two
+// dependent loads (1M rows of 30 + 30 entries, FP64: 0.62 ms with one row at
+// a time, 0.375 now, 4.7 TB/s, about what a copy of that size reaches).
+template <typename T>
+__device__ inline void add_long_row(const int32_t* __restrict__ aci, const T* __restrict__ av,
+                                    const int32_t* __restrict__ bci, const T* __restrict__ bv,
+                                    const int32_t* __restrict__ apos, const int32_t* __restrict__ bpos, T alpha,
+                                    T beta, int as, int ae, int bs, int be, int nc, int32_t* cc, T* cv, double* s) {
+    const int lane = threadIdx.x % WAVE;
+    if (nc > NUM_SEGMENTS * NUM_CAP) {
+        for (int r = lane; r < nc; r += WAVE) cv[r] = T(0);
+        wg_fence();
+        wave_sync();
+        for (int t = as + lane; t < ae; t += WAVE) {
+            const int p = apos[t];
+            cc[p] = aci[t];
+            atomicAdd(&cv[p], alpha * av[t]);
+        }
+        wg_fence();
+        wave_sync();
+        for (int t = bs + lane; t < be; t += WAVE) {
+            const int p = bpos[t];
+            cc[p] = bci[t];
+            atomicAdd(&cv[p], beta * bv[t]);
+        }
+        wave_sync();
+        return;
+    }
+    for (int s0 = 0; s0 < nc; s0 += NUM_CAP) {
+        const int len = min(NUM_CAP, nc - s0);
+        for (int r = lane; r < len; r += WAVE) s[r] = 0.0;
+        wave_sync();
+        for (int t = as + lane; t < ae; t += WAVE) {
+            const int p = apos[t] - s0;
+            if ((unsigned)p >= (unsigned)len) continue;
+            cc[s0 + p] = aci[t];
+            atomicAdd(&s[p], (double)(alpha * av[t]));
+        }
+        wave_sync();
+        for (int t = bs + lane; t < be; t += WAVE) {
+            const int p = bpos[t] - s0;
+            if ((unsigned)p >= (unsigned)len) continue;
+            cc[s0 + p] = bci[t];
+            atomicAdd(&s[p], (double)(beta * bv[t]));
+        }
+        wave_sync();
+        for (int r = lane; r < len; r += WAVE) cv[s0 + r] = (T)s[r];
+        wave_sync();
+    }
+}
+
 template <typename T>
 __global__ __launch_bounds__(WAVE * ROWS_PER_WG) void k_add_num(int32_t m, const int32_t* __restrict__ arp,
                                                                 const int32_t* __restrict__ aci,
@@ -398,34 +621,70 @@ __global__ __launch_bounds__(WAVE * ROWS_PER_WG) void k_add_num(int32_t m, const
                                                                 const int32_t* __restrict__ bpos,
                                                                 const int32_t* __restrict__ crp, T alpha, T beta,
                                                                 int32_t* __restrict__ ccol, T* __restrict__ cval) {
-    __shared__ T acc[ROWS_PER_WG][MID_CAP];
-    const int wv = threadIdx.x / WAVE, lane = threadIdx.x % WAVE;
-    T* s = acc[wv];
-    for (int64_t i = (int64_t)blockIdx.x * ROWS_PER_WG + wv; i < m; i += (int64_t)gridDim.x * ROWS_PER_WG) {
-        const int as = arp[i], ae = arp[i + 1], bs = brp[i], be = brp[i + 1];
-        const int c0 = crp[i], nc = crp[i + 1] - c0;
-        int32_t* cc = ccol + c0;
-        T* cv = cval + c0;
-        const bool in_lds = nc <= MID_CAP;
-        T* dst = in_lds ? s : cv;
-        for (int r = lane; r < nc; r += WAVE) dst[r] = T(0);
-        if (!in_lds) wg_fence();
-        wave_sync();
-        for (int t = as + lane; t < ae; t += WAVE) {
-            const int p = apos[t];
-            cc[p] = aci[t];
-            atomicAdd(&dst[p], alpha * av[t]);
+    __shared__ double acc[ROWS_PER_WG][NUM_CAP];
+    const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x / WAVE), lane = threadIdx.x % WAVE;
+    double* s = acc[wv];
+    constexpr int R = 2;
+    const int64_t step = (int64_t)gridDim.x * ROWS_PER_WG * R;
+    // pointers of rows i0 and i0 + 1 (a row past the end: the last, unused)
+    struct Ptr {
+        int as, ae, bs, be, c0, nc;
+    };
+    auto ptrs = [&](int64_t i) {
+        i = i < m ? i : m - 1;
+        Ptr p;
+        p.as = arp[i], p.ae = arp[i + 1], p.bs = brp[i], p.be = brp[i + 1], p.c0 = crp[i], p.nc = crp[i + 1] - p.c0;
+        return p;
+    };
+    int64_t i0 = ((int64_t)blockIdx.x * ROWS_PER_WG + wv) * R;
+    Ptr nxt[R];
+    for (int r = 0; r < R; ++r) nxt[r] = ptrs(i0 + r);
+    for (; i0 < m; i0 += step) {
+        Ptr p[R];
+#pragma unroll
+        for (int r = 0; r < R; ++r) p[r] = nxt[r], nxt[r] = ptrs(i0 + step + r);
+        bool small = true;
+#pragma unroll
+        for (int r = 0; r < R; ++r) small &= p[r].ae - p[r].as + p[r].be - p[r].bs <= WAVE;
+        if (!small) {
+            for (int r = 0; r < R; ++r)
+                if (i0 + r < m)
+                    add_long_row<T>(aci, av, bci, bv, apos, bpos, alpha, beta, p[r].as, p[r].ae, p[r].bs, p[r].be,
+                                    p[r].nc, ccol + p[r].c0, cval + p[r].c0, s);
+            continue;
         }
-        if (!in_lds) wg_fence();
-        wave_sync();
-        for (int t = bs + lane; t < be; t += WAVE) {
-            const int p = bpos[t];
-            cc[p] = bci[t];
-            atomicAdd(&dst[p], beta * bv[t]);
+        // one entry per lane and row: A's, then B's
+        int pos[R], col[R];
+        double v[R];
+        bool in_a[R], has[R];
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            const int la = p[r].ae - p[r].as, L = la + p[r].be - p[r].bs;
+            in_a[r] = lane < la;
+            has[r] = lane < L && i0 + r < m;
+            pos[r] = 0, col[r] = 0, v[r] = 0.0;
+            if (has[r]) {
+                const int q = in_a[r] ? p[r].as + lane : p[r].bs + lane - la;
+                pos[r] = (in_a[r] ? apos : bpos)[q];
+                col[r] = (in_a[r] ? aci : bci)[q];
+                v[r] = (double)((in_a[r] ? alpha : beta) * (in_a[r] ? av : bv)[q]);
+            }
+            s[r * WAVE + lane] = 0.0;
         }
         wave_sync();
-        if (in_lds)
-            for (int r = lane; r < nc; r += WAVE) cv[r] = s[r];
+#pragma unroll
+        for (int r = 0; r < R; ++r)
+            if (has[r] && in_a[r]) atomicAdd(&s[r * WAVE + pos[r]], v[r]);
+        wave_sync();
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            if (has[r] && !in_a[r]) atomicAdd(&s[r * WAVE + pos[r]], v[r]);
+            if (has[r]) ccol[p[r].c0 + pos[r]] = col[r];
+        }
+        wave_sync();
+#pragma unroll
+        for (int r = 0; r < R; ++r)
+            if (lane < p[r].nc && i0 + r < m) cval[p[r].c0 + lane] = (T)s[r * WAVE + lane];
         wave_sync();
     }
 }
@@ -537,16 +796,27 @@ spg_status spg_add_symbolic(spg_add h, int32_t m, int32_t n, const int32_t* a_ro
         h->tiles = reinterpret_cast<uint64_t*>(p), p += align256((size_t)(add_scan_tiles(m) + 1) * 8);
         h->ctl = reinterpret_cast<AddCtl*>(p);
         hipStream_t s = h->stream;
-        spg::launch_fill_u8(s, h->ctl, 0, sizeof(AddCtl));
+        // the scan's tile states and the control block after them start from zero
+        spg::launch_zero(s, h->tiles, (int64_t)(align256((size_t)(add_scan_tiles(m) + 1) * 8) + align256(sizeof(AddCtl))));
         if (m > 0) {
-            const int grid_rows = (int)std::min<int64_t>(((int64_t)m + ROWS_PER_WG - 1) / ROWS_PER_WG,
-                                                         (int64_t)h->n_cu * 32);
-            hipLaunchKernelGGL(k_add_sym, dim3(grid_rows), dim3(WAVE * ROWS_PER_WG), 0, s, m, n, a_row_ptr, a_col_idx,
+            // lanes per row: the fewest that hold most rows (up to a third
+            // more entries than the average row; the others take a whole
+            // wavefront each, which costs more than idle lanes)
+            const int64_t total = (a_nnz + b_nnz) * 4 / 3;
+            const int G = total <= (int64_t)16 * m ? 16 : total <= (int64_t)32 * m ? 32 : 64;
+            const int64_t per_wg = (int64_t)ROWS_PER_WG * (WAVE / G) * 2;
+            const int grid_rows = (int)std::min<int64_t>((m + per_wg - 1) / per_wg, (int64_t)h->n_cu * 32);
+            const auto kernel = n <= KEY32_COLS ? (G == 16   ? k_add_sym<16, uint32_t>
+                                                   : G == 32 ? k_add_sym<32, uint32_t>
+                                                             : k_add_sym<64, uint32_t>)
+                                                : (G == 16   ? k_add_sym<16, uint64_t>
+                                                   : G == 32 ? k_add_sym<32, uint64_t>
+                                                             : k_add_sym<64, uint64_t>);
+            hipLaunchKernelGGL(kernel, dim3(grid_rows), dim3(WAVE * ROWS_PER_WG), 0, s, m, n, a_row_ptr, a_col_idx,
                                a_nnz, b_row_ptr, b_col_idx, b_nnz, h->apos, h->bpos, h->row_nnz, h->long_list, h->ctl);
             hipLaunchKernelGGL(k_add_sym_long, dim3((unsigned)std::min(h->n_cu, m)), dim3(LONG_THREADS),
                                (size_t)LONG_CAP * 8, s, n, a_row_ptr, a_col_idx, b_row_ptr, b_col_idx, h->apos,
                                h->bpos, h->row_nnz, h->long_list, h->ctl);
-            spg::launch_fill_u8(s, h->tiles, 0, (size_t)(add_scan_tiles(m) + 1) * 8);
             hipLaunchKernelGGL(k_add_scan, dim3((unsigned)add_scan_tiles(m)), dim3(SCAN_THREADS), 0, s, m, h->row_nnz,
                                c_row_ptr, h->tiles, h->ctl);
         } else {
