@@ -620,6 +620,30 @@ __device__ void flat_walk(const int32_t* __restrict__ aci, const int4* __restric
     flat_walk_hdr<G, K, V, RUNS, T>(aci, hdr, av, a0, a1, off, ava, win, red, load, static_cast<Apply&&>(apply));
 }
 
+// LDS by byte address: tables that hold addresses need no base added to them.
+template <typename T>
+using lds_ptr = __attribute__((address_space(3))) T*;
+template <typename T>
+__device__ inline uint32_t lds_addr(T* p) {
+    return (uint32_t)(uintptr_t)(lds_ptr<T>)p;
+}
+template <typename T>
+__device__ inline lds_ptr<T> at_lds(uint32_t a) {
+    return (lds_ptr<T>)(uintptr_t)a;
+}
+
+// Slot tables, for rows of one batch in groups of up to 64 lanes: instead of
+// the window table every lane with an entry writes its entry's slots (at most
+// SLOT_MAX) to LDS, and the lanes of the batch read theirs with one access
+// each.  A row's stencil-sized batch costs about a third of the window
+// table's instructions that way (its masks, popcounts and broadcasts are paid
+// per slot, twice): 252 vector instructions per symbolic row of the 27-point
+// 100^3 stencil against 468, 0.63 ms against 0.71 (with the sparse direct
+// table below).  Longer pieces of B would make the writing lanes walk: they
+// keep the window table.  (The numeric kernel gains nothing from it: its rows
+// wait for memory, see its columns.)
+constexpr int SLOT_MAX = 16;
+
 // ------------------------------------------------------------------ symbolic
 // Every entry of compressed B is a {block, mask} run: the row's table gets
 // the mask OR-ed in, and the bits that were not yet set (and blocks that were
@@ -632,7 +656,7 @@ __device__ __forceinline__ void sym_row(const SymArgs& a, const int4 d, const in
                                         int* occ, int* ovf) {
     constexpr int KC = FLAT_KC;
     constexpr int VC = FLAT_VC_SYM;
-    const int bytes = tier_bytes(a.tier);
+    const int bytes = a.table_bytes;
     const int per_row = bytes + sym_stage_bytes(G);
     const int lane = threadIdx.x % G, wv = lane >> 6;
     const unsigned long long le = (2ull << (lane & 63)) - 1;
@@ -674,20 +698,42 @@ __device__ __forceinline__ void sym_row(const SymArgs& a, const int4 d, const in
         cb = reinterpret_cast<int32_t*>(cm + cap);
         cb16 = reinterpret_cast<uint16_t*>(cm + cap);
     }
-    // 16-byte clears (tables start 256-byte aligned and tiers are multiples of 16 bytes)
-    if constexpr (MODE == MODE_DIRECT) {
-        for (int c = 4 * lane; c < ncell; c += 4 * G) *reinterpret_cast<uint4*>(&masks[c]) = make_uint4(0, 0, 0, 0);
-    } else if constexpr (MODE == MODE_HASHED) {
-        for (int c = 4 * lane; c < ncell; c += 4 * G) {
-            *reinterpret_cast<int4*>(&keys[c]) = make_int4(-1, -1, -1, -1);
-            *reinterpret_cast<uint4*>(&masks[c]) = make_uint4(0, 0, 0, 0);
+    // Sparse direct table: a row whose range is wide for its few blocks, on a
+    // wavefront, keeps a mask per word of the range where the launch's LDS
+    // holds it (two-level rows sized from a guaranteed bound), or has one
+    // anyway (direct rows); the words it touches are listed as an OR finds
+    // them empty, so that nothing walks the range.
+    bool sparse = false;
+    if constexpr (G == 64 && MODE != MODE_HASHED)
+        sparse = ncell > 3 * G && ncell <= SPARSE_WORDS && (MODE == MODE_DIRECT || (ncell * 4 <= bytes && !a.ovf_list));
+    // 16-byte clears (tables start 16-byte aligned and their bytes are multiples of 16)
+    auto clear_table = [&]() {
+        if (MODE == MODE_DIRECT || sparse) {
+            for (int c = 4 * lane; c < ncell; c += 4 * G) *reinterpret_cast<uint4*>(&tab[c]) = make_uint4(0, 0, 0, 0);
+        } else if constexpr (MODE == MODE_HASHED) {
+            for (int c = 4 * lane; c < ncell; c += 4 * G) {
+                *reinterpret_cast<int4*>(&keys[c]) = make_int4(-1, -1, -1, -1);
+                *reinterpret_cast<uint4*>(&masks[c]) = make_uint4(0, 0, 0, 0);
+            }
+        } else {
+            for (int c = lane; c < w1; c += G) l1[c] = make_uint2(0u, 0u);
         }
-    } else {
-        for (int c = lane; c < w1; c += G) l1[c] = make_uint2(0u, 0u);
-    }
-    win_clear<G, KC>(win, lane);
+    };
     if (lane == 0) occ[sub] = 0, ovf[sub] = 0;
-    group_sync<G>();
+    // rows of one batch with short pieces of compressed B: slot table
+    bool slots = false;
+    int s_ex = 0, s_tot = 0;
+    if constexpr (G <= 64 && MODE != MODE_HASHED) {  // (hashed rows are scattered: seldom of one batch)
+        const int x = wave_incl_scan<G>(h0.w);
+        s_ex = x - h0.w, s_tot = group_last<G>(x);
+        slots = __all(a1 - a0 <= G && s_tot <= KC * G && h0.w <= SLOT_MAX);
+    }
+    sparse = sparse && slots;  // (the touched words share the staging area)
+    if (!slots) {
+        clear_table();
+        win_clear<G, KC>(win, lane);
+        group_sync<G>();
+    }
 
     // ---- staging: chunks of G entries of A's row, one window table of run groups
     int pc = 0, PC = 0;
@@ -753,9 +799,26 @@ __device__ __forceinline__ void sym_row(const SymArgs& a, const int4 d, const in
     };
 
     int cnt = 0, nb = 0;
+    uint16_t* touched = reinterpret_cast<uint16_t*>(cq);            // sparse: the first 128 touched words
+    uint32_t* tbits = reinterpret_cast<uint32_t*>(cq + G / 2);      // ... and a bitmap of the touched words
     // runs(apply): apply(run, entry) on every run; runs_all(f): f(group,
     // valid) on every lane of every batch
     auto finish = [&](auto&& runs, auto&& runs_all) {
+        if (sparse) {
+            auto orw = [&](const auto& g, bool valid) {
+                const int w = g.r[0].x - base;
+                uint32_t old = 1;
+                if (valid) old = atomicOr(&tab[w], (uint32_t)g.r[0].y);
+                const unsigned long long fresh = __ballot(old == 0);
+                if (old == 0) {
+                    const int at = nb + __popcll(fresh & (le >> 1));
+                    if (at < 128) touched[at] = (uint16_t)w;
+                }
+                nb += __popcll(fresh);
+            };
+            runs_all(orw);
+            return;
+        }
         if constexpr (MODE == MODE_TWOLEVEL) {
             // pass A: occupied blocks; their count and compact indices from a
             // prefix of popcounts; pass B: masks OR-ed in at the compact index.
@@ -823,8 +886,38 @@ __device__ __forceinline__ void sym_row(const SymArgs& a, const int4 d, const in
         }
     };
 
-    stage(a0, h0);
-    if (a1 - a0 <= G && PC <= KC * G) {
+    if (slots) {
+        // every lane writes its entry's runs, every lane of the batch reads
+        // its own; the table area holds the slots until the loads are issued
+        if constexpr (G <= 64) {
+            int32_t* slot = reinterpret_cast<int32_t*>(tab);
+            {
+                lds_ptr<int32_t> out = at_lds<int32_t>(lds_addr(slot + s_ex));
+                for (int t = 0; __any(t < h0.w); ++t)
+                    if (t < h0.w) out[t] = h0.z + t;
+            }
+            group_sync<G>();
+            Batch<G, KC, VC, decltype(load_run)> br;
+            static_assert(VC == 1, "a slot is one run");
+            int q[KC];
+#pragma unroll
+            for (int k = 0; k < KC; ++k) q[k] = slot[k * G + lane];
+#pragma unroll
+            for (int k = 0; k < KC; ++k)
+                if (k * G + lane < s_tot) br.v[k].r[0] = a.bc[q[k]], br.v[k].n = 1;
+            group_sync<G>();
+            clear_table();
+            if (sparse) tbits[lane] = 0;
+            group_sync<G>();
+            finish(
+                [&](auto&& apply) {
+#pragma unroll
+                    for (int k = 0; k < KC; ++k)
+                        if (k * G + lane < s_tot) apply(br.v[k], 0);
+                },
+                [&](auto&& f) { br.consume_all(0, s_tot, lane, f); });
+        }
+    } else if (stage(a0, h0), a1 - a0 <= G && PC <= KC * G) {
         // the whole row in one batch: its runs stay in registers for every pass
         Batch<G, KC, VC, decltype(load_run)> br;
         br.issue(cq, win, 0, PC, lane, wv, le, load_run);
@@ -833,7 +926,7 @@ __device__ __forceinline__ void sym_row(const SymArgs& a, const int4 d, const in
     } else {
         finish(walk_runs, walk_runs_all);
     }
-    if constexpr (MODE != MODE_TWOLEVEL) {
+    if (MODE != MODE_TWOLEVEL && !sparse) {
         cnt = group_sum<G>(cnt, red);
         nb = group_sum<G>(nb, red);
     }
@@ -841,7 +934,44 @@ __device__ __forceinline__ void sym_row(const SymArgs& a, const int4 d, const in
     // the row's list: its occupied blocks in ascending order with their masks
     const int lo = d.w;
     const bool overflowed = MODE != MODE_DIRECT && ovf[sub];
-    if constexpr (MODE == MODE_TWOLEVEL) {
+    bool listed = false;
+    if constexpr (G == 64 && MODE != MODE_HASHED) {
+        if (sparse) {
+            listed = true;
+            if (nb <= 64) {
+                // one touched word per lane; its place is the touched words
+                // before it, from a bitmap of them and its prefix
+                const bool has = lane < nb;
+                const int w = has ? touched[lane] : 0;
+                if (has) atomicOr(&tbits[w >> 5], 1u << (w & 31));
+                group_sync<G>();
+                const uint32_t wb = tbits[lane];
+                const int pc1 = __popc(wb);
+                const int px = wave_incl_scan<64>(pc1) - pc1;
+                const uint32_t bits = (uint32_t)__shfl((int)wb, w >> 5, 64);
+                const int pos = __shfl(px, w >> 5, 64) + __popc(bits & below(w & 31));
+                if (has) {
+                    const uint32_t mk = tab[w];
+                    cnt = __popc(mk);
+                    if (lo >= 0) a.lists[lo + pos] = make_int2(base + w, (int)mk);
+                }
+                cnt = group_sum<G>(cnt, red);
+            } else {
+                // many blocks: over the range, a word per lane and step
+                int at = lo;
+                for (int c0 = 0; c0 < ncell; c0 += G) {
+                    const uint32_t mk = c0 + lane < ncell ? tab[c0 + lane] : 0u;
+                    const unsigned long long on = __ballot(mk != 0);
+                    cnt += __popc(mk);
+                    if (mk && lo >= 0) a.lists[at + __popcll(on & (le >> 1))] = make_int2(base + c0 + lane, (int)mk);
+                    at += __popcll(on);
+                }
+                cnt = group_sum<G>(cnt, red);
+            }
+        }
+    }
+    if (listed) {
+    } else if constexpr (MODE == MODE_TWOLEVEL) {
         // the row size from the final masks; compact indices are in block
         // order, so the list is one coalesced store per block
         if (!overflowed) {
@@ -853,7 +983,7 @@ __device__ __forceinline__ void sym_row(const SymArgs& a, const int4 d, const in
         }
         cnt = group_sum<G>(cnt, red);
     }
-    if (MODE != MODE_TWOLEVEL && lo >= 0 && !overflowed) {
+    if (MODE != MODE_TWOLEVEL && !listed && lo >= 0 && !overflowed) {
         int2* out = a.lists + lo;
         if constexpr (MODE == MODE_DIRECT) {
             const int chunk = (ncell + G - 1) / G;
@@ -1752,7 +1882,7 @@ template <int G, int MODE>
 void sym_launch(hipStream_t s, const SymArgs& a) {
     constexpr int RPW = rows_per_wg<G>();
     const unsigned grid = (unsigned)((a.count + RPW - 1) / RPW);
-    const size_t smem = (size_t)RPW * (tier_bytes(a.tier) + sym_stage_bytes(G));
+    const size_t smem = (size_t)RPW * (a.table_bytes + sym_stage_bytes(G));
     hipLaunchKernelGGL((k_sym<G, MODE>), dim3(grid), dim3(G * RPW), smem, s, a);
 }
 
@@ -1773,15 +1903,9 @@ void sym_dispatch(hipStream_t s, const SymArgs& a) {
 template <int G>
 int sym_tier_launch(hipStream_t s, const SymArgs& a, int64_t max_rows, int n_cu) {
     constexpr int RPW = rows_per_wg<G>();
-    const size_t smem = (size_t)RPW * (tier_bytes(a.tier) + sym_stage_bytes(G));
-    // workgroups per compute unit at this LDS size, looked up once per tier
-    static int occupancy[NTIER] = {};
-    int occ = occupancy[a.tier];
-    if (occ <= 0) {
-        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, k_sym_tier<G>, G * RPW, smem) != hipSuccess || occ < 1)
-            occ = 1;
-        occupancy[a.tier] = occ;
-    }
+    const size_t smem = (size_t)RPW * (a.table_bytes + sym_stage_bytes(G));
+    // workgroups that a compute unit holds at once (2048 lanes, 160 KB of LDS)
+    const int occ = std::max(1, std::min(2048 / (G * RPW), (int)(163840 / (smem + 1024))));
     const int64_t groups = (max_rows + RPW - 1) / RPW;
     int64_t grid = std::min<int64_t>((int64_t)occ * n_cu, std::max<int64_t>(groups, 1));
     grid = (grid + 7) / 8 * 8;

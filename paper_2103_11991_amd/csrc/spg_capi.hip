@@ -531,6 +531,16 @@ void sym_stage_analysis(spg_handle h) {
     rec(h, EV_ANA1);
 }
 
+// LDS table bytes per row of a symbolic launch: its tier's; two-level rows of
+// one wavefront get what the direct table of the widest row takes, where that
+// is within SPARSE_WORDS (see sparse rows in sym_row).
+int32_t sym_table_bytes(int tier, bool twolevel, int64_t max_words) {
+    if (tier >= TIER_GLOBAL) return 0;
+    const int32_t b = tier_bytes(tier);
+    if (!twolevel || tier_threads(tier) != 64 || max_words > SPARSE_WORDS) return b;
+    return std::max(b, ((int32_t)max_words * 4 + 15) & ~15);
+}
+
 // (with read_back, the control block is copied to the host right after the
 // row-pointer scan and an event marks the copy: the host needs nothing the
 // numeric grouping after it changes, and need not wait for it)
@@ -543,6 +553,7 @@ spg_status sym_stage_rows(spg_handle h, int32_t* c_row_ptr, bool read_back = fal
     const bool learned = h->binning == 1;
     Control* ctl = h->ctl.as<Control>();
     const int wl = wide_lds(h);
+    const int64_t words_k = ((int64_t)h->k + 31) / 32 + 1;
     SymArgs base{};
     base.arp = h->arp, base.aci = h->aci, base.brp = h->brp, base.bci = h->bci;
     base.bc = h->bc.as<int2>(), base.bhdr = h->bhdr.as<int4>();
@@ -600,6 +611,7 @@ spg_status sym_stage_rows(spg_handle h, int32_t* c_row_ptr, bool read_back = fal
             a.perm = h->perm_sym.as<int32_t>();
             a.desc = h->desc_sym.as<int4>();
             a.tier = t;
+            a.table_bytes = sym_table_bytes(t, true, words_k);
             rec(h, EV_SYMCLS + 2 * t);
             launch_sym_tier(s, a, m, h->n_cu);
             rec(h, EV_SYMCLS + 2 * t + 1);
@@ -634,6 +646,7 @@ spg_status sym_stage_rows(spg_handle h, int32_t* c_row_ptr, bool read_back = fal
             a.count = hist[c];
             a.tier = c % NTIER;
             a.mode = c / NTIER;
+            a.table_bytes = sym_table_bytes(a.tier, a.mode == MODE_TWOLEVEL, h->geom.max_words_all);
             if (a.tier == TIER_GLOBAL) {
                 a.slab = h->slab_sym_words ? h->slab_sym.as<uint32_t>() : nullptr;
                 a.slab_words = h->slab_sym_words;

@@ -139,6 +139,10 @@ __host__ __device__ inline int32_t twolevel_words(int32_t words) { return (words
 __host__ __device__ inline int32_t num_twolevel_bytes(int32_t words, int32_t blocks, int32_t n, int eb) {
     return align8(twolevel_words(words) * 8 + blocks * 8) + n * eb;
 }
+// Symbolic rows of one wavefront: widest range whose direct table a launch
+// makes room for, in words (with the staging, seven workgroups of four rows
+// fit a compute unit).
+constexpr int SPARSE_WORDS = 1280;
 // A row's list capacity: its compressed-B run count bounds its occupied
 // blocks, and so does the width of its column range in words.
 __host__ __device__ inline int32_t list_capacity(int64_t runs, int32_t words) {
@@ -361,6 +365,7 @@ void launch_pack(hipStream_t s, int32_t count, const int64_t* desc, const int32_
 
 // ---- accumulator kernels (spg_accum.hip) ----
 struct SymArgs {
+    int32_t table_bytes;          // LDS bytes of one row's table (row kernels)
     const int32_t* perm;
     const int4* desc;             // per slot {row, A start, A end, list offset} (row kernels)
     int32_t count;
