@@ -650,13 +650,12 @@ constexpr int SLOT_MAX = 16;
 // empty) are counted from the value the atomic OR returns.
 
 // One row of the symbolic phase in a table of MODE in the row's LDS share
-// (d = the slot's descriptor {row, A start, A end, list offset}).
+// (`bytes` of table, then the staging; d = the slot's descriptor {row, A start, A end, list offset}).
 template <int G, int MODE>
-__device__ __forceinline__ void sym_row(const SymArgs& a, const int4 d, const int sub, uint32_t* smem, int* red,
-                                        int* occ, int* ovf) {
+__device__ __forceinline__ void sym_row(const SymArgs& a, const int bytes, const int4 d, const int sub, uint32_t* smem,
+                                        int* red, int* occ, int* ovf) {
     constexpr int KC = FLAT_KC;
     constexpr int VC = FLAT_VC_SYM;
-    const int bytes = a.table_bytes;
     const int per_row = bytes + sym_stage_bytes(G);
     const int lane = threadIdx.x % G, wv = lane >> 6;
     const unsigned long long le = (2ull << (lane & 63)) - 1;
@@ -1033,16 +1032,16 @@ __device__ __forceinline__ void sym_row(const SymArgs& a, const int4 d, const in
 
 // The symbolic rows of one LDS tier, all three table modes (the grouping
 // kernel placed them tier-major, one range of slots per mode; its control
-// block gives the ranges).  Persistent: each mode's row groups of RPW slots
-// are cut into 8 contiguous shares, one per XCD (workgroups are dispatched
-// round-robin over the XCDs, so workgroup b runs on XCD b % 8), and the
-// workgroups of an XCD take its share's groups in turn; neighbouring rows
-// share most of their B rows, which then stay in that XCD's L2.  The modes
-// run one after another, each in a loop of its own, so that each keeps the
-// register budget of its own table code.
+// block gives the ranges), G lanes per row.  Persistent: each mode's row
+// groups of RPW slots are cut into 8 contiguous shares, one per XCD
+// (workgroups are dispatched round-robin over the XCDs, so workgroup b runs
+// on XCD b % 8), and the workgroups of an XCD take its share's groups in
+// turn; neighbouring rows share most of their B rows, which then stay in that
+// XCD's L2.  The modes run one after another, each in a loop of its own, so
+// that each keeps the register budget of its own table code.
 template <int G, int MODE>
-__device__ __forceinline__ void sym_tier_mode(const SymArgs& a, const int first, const int total, const int sub,
-                                              uint32_t* smem, int* red, int* occ, int* ovf) {
+__device__ __forceinline__ void sym_tier_mode(const SymArgs& a, const int bytes, const int first, const int total,
+                                              const int sub, uint32_t* smem, int* red, int* occ, int* ovf) {
     constexpr int RPW = rows_per_wg<G>();
     constexpr int NXCD = 8;
     const int groups = (total + RPW - 1) / RPW;
@@ -1053,33 +1052,52 @@ __device__ __forceinline__ void sym_tier_mode(const SymArgs& a, const int first,
         const int k = g * RPW + sub;
         if (k >= total) break;  // uniform in the group (in the workgroup when G >= 128)
         group_sync<G>();        // the previous row's readers are done with the table
-        sym_row<G, MODE>(a, a.desc[first + k], sub, smem, red, occ, ovf);
+        sym_row<G, MODE>(a, bytes, a.desc[first + k], sub, smem, red, occ, ovf);
     }
 }
 
 template <int G>
-// (up to 128 lanes per row the symbolic kernel fits 64 VGPRs: full occupancy)
-__global__ __launch_bounds__(G * rows_per_wg<G>()) __attribute__((amdgpu_waves_per_eu(G <= 128 ? 8 : 4)))
-void k_sym_tier(SymArgs a) {
-    constexpr int RPW = rows_per_wg<G>();
-    extern __shared__ __align__(16) uint32_t smem[];
-    __shared__ int red[48];
-    __shared__ int occ[RPW];
-    __shared__ int ovf[RPW];
-    if (a.ctl->err & ERR_INPUT) return;
-    const int t = a.tier;
+__device__ __forceinline__ void sym_tier(const SymArgs& a, const int t, uint32_t* smem, int* red, int* occ, int* ovf) {
     // a group of 64 or more lanes owns whole wavefronts: its row is wave-uniform
     const int sub = G >= 64 ? __builtin_amdgcn_readfirstlane(threadIdx.x / G) : threadIdx.x / G;
+    const int bytes = sym_table_bytes(t, true, a.max_words);
     const int c0 = MODE_DIRECT * NTIER + t, c1 = MODE_HASHED * NTIER + t, c2 = MODE_TWOLEVEL * NTIER + t;
-    if (a.ctl->sym_cnt[c0]) sym_tier_mode<G, MODE_DIRECT>(a, a.ctl->sym_off[c0], a.ctl->sym_cnt[c0], sub, smem, red, occ, ovf);
-    if (a.ctl->sym_cnt[c1]) {
-        group_sync<G>();
-        sym_tier_mode<G, MODE_HASHED>(a, a.ctl->sym_off[c1], a.ctl->sym_cnt[c1], sub, smem, red, occ, ovf);
-    }
-    if (a.ctl->sym_cnt[c2]) {
-        group_sync<G>();
-        sym_tier_mode<G, MODE_TWOLEVEL>(a, a.ctl->sym_off[c2], a.ctl->sym_cnt[c2], sub, smem, red, occ, ovf);
-    }
+    const int n0 = a.ctl->sym_cnt[c0], n1 = a.ctl->sym_cnt[c1], n2 = a.ctl->sym_cnt[c2];
+    if (n0 + n1 + n2 == 0) return;
+    __syncthreads();  // the previous tier's rows, in windows of another size, are done
+    if (n0) sym_tier_mode<G, MODE_DIRECT>(a, bytes, a.ctl->sym_off[c0], n0, sub, smem, red, occ, ovf);
+    __syncthreads();
+    if (n1) sym_tier_mode<G, MODE_HASHED>(a, bytes, a.ctl->sym_off[c1], n1, sub, smem, red, occ, ovf);
+    __syncthreads();
+    if (n2) sym_tier_mode<G, MODE_TWOLEVEL>(a, bytes, a.ctl->sym_off[c2], n2, sub, smem, red, occ, ovf);
+}
+
+// All LDS tiers in three launches (an empty launch costs 2.5 to 3 us, and
+// most of nine were empty: 30 of a 2D 64^2 product's 94 us): tiers up to 4 in
+// one of 256-lane workgroups, the heaviest first; 5 and 6 with 256 lanes per
+// row; 7 and 8 with 1024.  (up to 256 lanes per row the symbolic kernel fits
+// 64 VGPRs: full occupancy)
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(8))) void k_sym_tiers0(SymArgs a) {
+    extern __shared__ __align__(16) uint32_t smem[];
+    __shared__ int red[48];
+    __shared__ int occ[rows_per_wg<8>()];
+    __shared__ int ovf[rows_per_wg<8>()];
+    if (a.ctl->err & ERR_INPUT) return;
+    sym_tier<64>(a, 4, smem, red, occ, ovf);
+    sym_tier<64>(a, 3, smem, red, occ, ovf);
+    sym_tier<32>(a, 2, smem, red, occ, ovf);
+    sym_tier<16>(a, 1, smem, red, occ, ovf);
+    sym_tier<8>(a, 0, smem, red, occ, ovf);
+}
+
+template <int G>
+__global__ __launch_bounds__(G) __attribute__((amdgpu_waves_per_eu(4))) void k_sym_tiers(SymArgs a, int t0, int t1) {
+    extern __shared__ __align__(16) uint32_t smem[];
+    __shared__ int red[48];
+    __shared__ int occ[1];
+    __shared__ int ovf[1];
+    if (a.ctl->err & ERR_INPUT) return;
+    for (int t = t1; t >= t0; --t) sym_tier<G>(a, t, smem, red, occ, ovf);
 }
 
 // One launch per symbolic class, sized on the host from the class histogram
@@ -1097,7 +1115,7 @@ void k_sym(SymArgs a) {
     const int sub = G >= 64 ? __builtin_amdgcn_readfirstlane(threadIdx.x / G) : threadIdx.x / G;
     const int slot = xcd_block<G>(blockIdx.x, gridDim.x) * RPW + sub;
     if (slot >= a.count) return;  // uniform in the group (in the workgroup when G >= 128)
-    sym_row<G, MODE>(a, a.desc[slot], sub, smem, red, occ, ovf);
+    sym_row<G, MODE>(a, a.table_bytes, a.desc[slot], sub, smem, red, occ, ovf);
 }
 
 template <bool IN_LDS>
@@ -1925,19 +1943,6 @@ void sym_dispatch(hipStream_t s, const SymArgs& a) {
     }
 }
 
-template <int G>
-int sym_tier_launch(hipStream_t s, const SymArgs& a, int64_t max_rows, int n_cu) {
-    constexpr int RPW = rows_per_wg<G>();
-    const size_t smem = (size_t)RPW * (a.table_bytes + sym_stage_bytes(G));
-    // workgroups that a compute unit holds at once (2048 lanes, 160 KB of LDS)
-    const int occ = std::max(1, std::min(2048 / (G * RPW), (int)(163840 / (smem + 1024))));
-    const int64_t groups = (max_rows + RPW - 1) / RPW;
-    int64_t grid = std::min<int64_t>((int64_t)occ * n_cu, std::max<int64_t>(groups, 1));
-    grid = (grid + 7) / 8 * 8;
-    hipLaunchKernelGGL(k_sym_tier<G>, dim3((unsigned)grid), dim3(G * RPW), smem, s, a);
-    return (int)grid;
-}
-
 template <int G, int MODE, typename T>
 void num_launch(hipStream_t s, const NumArgs& a) {
     constexpr int RPW = rows_per_wg<G>();
@@ -1981,18 +1986,25 @@ int launch_sym_class(hipStream_t s, const SymArgs& a, int grid_cap) {
     return 1;
 }
 
-int launch_sym_tier(hipStream_t s, const SymArgs& a, int64_t max_rows, int n_cu) {
-    if (max_rows <= 0 || a.tier < 0 || a.tier >= TIER_GLOBAL) return 0;
-    switch (tier_threads(a.tier)) {
-        case 8: return sym_tier_launch<8>(s, a, max_rows, n_cu);
-        case 16: return sym_tier_launch<16>(s, a, max_rows, n_cu);
-        case 32: return sym_tier_launch<32>(s, a, max_rows, n_cu);
-        case 64: return sym_tier_launch<64>(s, a, max_rows, n_cu);
-        case 128: return sym_tier_launch<128>(s, a, max_rows, n_cu);
-        case 256: return sym_tier_launch<256>(s, a, max_rows, n_cu);
-        case 512: return sym_tier_launch<512>(s, a, max_rows, n_cu);
-        default: return sym_tier_launch<1024>(s, a, max_rows, n_cu);
+void launch_sym_tiers(hipStream_t s, const SymArgs& a, int part, int t_last, int64_t max_rows, int n_cu) {
+    if (max_rows <= 0) return;
+    const int t0 = part == 0 ? 0 : part == 1 ? 5 : 7;
+    const int t1 = std::min(part == 0 ? 4 : part == 1 ? 6 : 8, t_last);
+    if (t1 < t0) return;
+    const int threads = part == 2 ? 1024 : 256;
+    size_t smem = 0;
+    for (int t = t0; t <= t1; ++t) {
+        const int g = part == 0 ? tier_threads(t) : threads;
+        smem = std::max(smem, (size_t)(threads / g) * (sym_table_bytes(t, true, a.max_words) + sym_stage_bytes(g)));
     }
+    // at most what the compute units hold at once (2048 lanes, 160 KB of
+    // LDS), and a workgroup per row group of the widest mapping
+    const int occ = std::max(1, std::min(2048 / threads, (int)(163840 / (smem + 1024))));
+    const int64_t groups = part == 0 ? (max_rows + 3) / 4 : max_rows;
+    const unsigned grid = (unsigned)((std::min<int64_t>((int64_t)occ * n_cu, groups) + 7) / 8 * 8);
+    if (part == 0) hipLaunchKernelGGL(k_sym_tiers0, dim3(grid), dim3(256), smem, s, a);
+    else if (part == 1) hipLaunchKernelGGL(k_sym_tiers<256>, dim3(grid), dim3(256), smem, s, a, t0, t1);
+    else hipLaunchKernelGGL(k_sym_tiers<1024>, dim3(grid), dim3(1024), smem, s, a, t0, t1);
 }
 
 int launch_num_class(hipStream_t s, const NumArgs& a, int elem_bytes, int grid_cap) {

@@ -531,16 +531,6 @@ void sym_stage_analysis(spg_handle h) {
     rec(h, EV_ANA1);
 }
 
-// LDS table bytes per row of a symbolic launch: its tier's; two-level rows of
-// one wavefront get what the direct table of the widest row takes, where that
-// is within SPARSE_WORDS (see sparse rows in sym_row).
-int32_t sym_table_bytes(int tier, bool twolevel, int64_t max_words) {
-    if (tier >= TIER_GLOBAL) return 0;
-    const int32_t b = tier_bytes(tier);
-    if (!twolevel || tier_threads(tier) != 64 || max_words > SPARSE_WORDS) return b;
-    return std::max(b, ((int32_t)max_words * 4 + 15) & ~15);
-}
-
 // (with read_back, the control block is copied to the host right after the
 // row-pointer scan and an event marks the copy: the host needs nothing the
 // numeric grouping after it changes, and need not wait for it)
@@ -601,19 +591,20 @@ spg_status sym_stage_rows(spg_handle h, int32_t* c_row_ptr, bool read_back = fal
         rec(h, EV_SYMCLS + 1);
         h->sym_cls_timed[0] = h->timing == 1;
     } else if (h->single_wait && !host_sized) {
-        // one persistent launch per LDS tier (its three table modes); each
-        // reads its rows from the control block the grouping kernel wrote,
-        // so no launch waits for the host.  Tiers above the LDS limit never
-        // get rows.  Times are kept per tier (in the tier's direct class).
-        for (int t = 0; t < TIER_GLOBAL; ++t) {
-            if (tier_bytes(t) > h->cfg.lds_limit) continue;
+        // three persistent launches for the LDS tiers; each reads its rows
+        // from the control block the grouping kernel wrote, so none waits for
+        // the host.  Tiers above the LDS limit never get rows.  A launch's
+        // time is kept in its first tier's direct class.
+        int t_last = -1;
+        while (t_last + 1 < TIER_GLOBAL && tier_bytes(t_last + 1) <= h->cfg.lds_limit) ++t_last;
+        for (int part = 0; part < 3; ++part) {
+            const int t = part == 0 ? 0 : part == 1 ? 5 : 7;
             SymArgs a = base;
             a.perm = h->perm_sym.as<int32_t>();
             a.desc = h->desc_sym.as<int4>();
-            a.tier = t;
-            a.table_bytes = sym_table_bytes(t, true, words_k);
+            a.max_words = words_k;
             rec(h, EV_SYMCLS + 2 * t);
-            launch_sym_tier(s, a, m, h->n_cu);
+            launch_sym_tiers(s, a, part, t_last, m, h->n_cu);
             rec(h, EV_SYMCLS + 2 * t + 1);
             h->sym_cls_timed[t] = h->timing == 1;
         }
@@ -646,7 +637,8 @@ spg_status sym_stage_rows(spg_handle h, int32_t* c_row_ptr, bool read_back = fal
             a.count = hist[c];
             a.tier = c % NTIER;
             a.mode = c / NTIER;
-            a.table_bytes = sym_table_bytes(a.tier, a.mode == MODE_TWOLEVEL, h->geom.max_words_all);
+            if (a.tier < TIER_GLOBAL)
+                a.table_bytes = sym_table_bytes(a.tier, a.mode == MODE_TWOLEVEL, h->geom.max_words_all);
             if (a.tier == TIER_GLOBAL) {
                 a.slab = h->slab_sym_words ? h->slab_sym.as<uint32_t>() : nullptr;
                 a.slab_words = h->slab_sym_words;

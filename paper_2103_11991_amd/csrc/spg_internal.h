@@ -143,6 +143,15 @@ __host__ __device__ inline int32_t num_twolevel_bytes(int32_t words, int32_t blo
 // makes room for, in words (with the staging, seven workgroups of four rows
 // fit a compute unit).
 constexpr int SPARSE_WORDS = 1280;
+// LDS table bytes per row of a symbolic launch: its tier's; two-level rows of
+// one wavefront get what the direct table of the widest row takes, where that
+// is within SPARSE_WORDS (see sparse rows in sym_row).
+__host__ __device__ inline int32_t sym_table_bytes(int tier, bool twolevel, int64_t max_words) {
+    const int32_t b = tier_bytes(tier);
+    if (!twolevel || tier_threads(tier) != 64 || max_words > SPARSE_WORDS) return b;
+    const int32_t w = ((int32_t)max_words * 4 + 15) & ~15;
+    return w > b ? w : b;
+}
 // A row's list capacity: its compressed-B run count bounds its occupied
 // blocks, and so does the width of its column range in words.
 __host__ __device__ inline int32_t list_capacity(int64_t runs, int32_t words) {
@@ -248,22 +257,35 @@ __host__ __device__ inline int num_class(int64_t ub, int32_t cmin, int32_t cmax,
 // with its tail is saved.  Merges chain upwards.  remap gets the launch class
 // of every class and merged the row counts per launch class.  The host and
 // the grouping kernel both evaluate it on the same histogram.
+// One mode's tiers; the loops unroll, so that the arrays are registers.
 __host__ __device__ inline void merge_classes_mode(const int32_t* hist, uint8_t* remap, int32_t* merged, int mode,
                                                    bool enable) {
     const int c0 = mode * NTIER;
-    for (int t = 0; t < NTIER; ++t) remap[c0 + t] = (uint8_t)(c0 + t), merged[c0 + t] = hist[c0 + t];
-    if (!enable) return;
+    int32_t rows[NTIER];
+    int to[NTIER];
+#pragma unroll
+    for (int t = 0; t < NTIER; ++t) rows[t] = hist[c0 + t], to[t] = t;
+#pragma unroll
     for (int t = 0; t < TIER_GLOBAL; ++t) {
-        if (merged[c0 + t] == 0) continue;
-        int u = t + 1;
-        while (u < TIER_GLOBAL && merged[c0 + u] == 0) ++u;
-        if (u >= TIER_GLOBAL || tier_threads(u) > 4 * tier_threads(t)) continue;
-        if ((int64_t)merged[c0 + t] * 8 > merged[c0 + u]) continue;
-        merged[c0 + u] += merged[c0 + t];
-        merged[c0 + t] = 0;
+        int u = TIER_GLOBAL;      // the next populated tier and its rows
+        int32_t next = 0;
+#pragma unroll
+        for (int v = TIER_GLOBAL - 1; v > t; --v)
+            if (rows[v] != 0) u = v, next = rows[v];
+        const int32_t mine = rows[t];
+        if (!enable || mine == 0 || u == TIER_GLOBAL || tier_threads(u) > 4 * tier_threads(t) ||
+            (int64_t)mine * 8 > next)
+            continue;
+#pragma unroll
+        for (int v = 0; v < TIER_GLOBAL; ++v)
+            if (v == u) rows[v] += mine;
+        rows[t] = 0;
+#pragma unroll
         for (int e = 0; e < NTIER; ++e)
-            if (remap[c0 + e] == c0 + t) remap[c0 + e] = (uint8_t)(c0 + u);
+            if (to[e] == t) to[e] = u;
     }
+#pragma unroll
+    for (int t = 0; t < NTIER; ++t) remap[c0 + t] = (uint8_t)(c0 + to[t]), merged[c0 + t] = rows[t];
 }
 inline void merge_classes(const int32_t* hist, uint8_t* remap, int32_t* merged, bool enable) {
     for (int mode = 0; mode < 3; ++mode) merge_classes_mode(hist, remap, merged, mode, enable);
@@ -365,7 +387,8 @@ void launch_pack(hipStream_t s, int32_t count, const int64_t* desc, const int32_
 
 // ---- accumulator kernels (spg_accum.hip) ----
 struct SymArgs {
-    int32_t table_bytes;          // LDS bytes of one row's table (row kernels)
+    int32_t table_bytes;          // LDS bytes of one row's table (class launches)
+    int64_t max_words;            // bound on a row's words (tier launches)
     const int32_t* perm;
     const int4* desc;             // per slot {row, A start, A end, list offset} (row kernels)
     int32_t count;
@@ -550,13 +573,12 @@ inline void sym_class_offsets(const int32_t* rows, int32_t* off) {
             off[c] = run, run += rows[c];
         }
 }
-// Symbolic rows of LDS tier a.tier (all three table modes), sized on the
-// device: the kernel reads the tier's rows and first slot from the control
-// block the grouping kernel wrote.  Persistent: the grid (a multiple of 8,
-// at most what the device holds at once, at most one workgroup per row
-// group of max_rows) walks the tier's row groups, each XCD a contiguous
-// share of them.  Returns the grid.
-int launch_sym_tier(hipStream_t s, const SymArgs& a, int64_t max_rows, int n_cu);
+// Symbolic rows of the LDS tiers (all three table modes) up to t_last, sized
+// on the device: the kernels read each tier's rows and first slots from the
+// control block the grouping kernel wrote.  part 0: tiers 0 to 4, 1: 5 and 6,
+// 2: 7 and 8.  Persistent: a grid of what the device holds at once, at most
+// one workgroup per row group of max_rows, each XCD a contiguous share.
+void launch_sym_tiers(hipStream_t s, const SymArgs& a, int part, int t_last, int64_t max_rows, int n_cu);
 int launch_num_class(hipStream_t s, const NumArgs& a, int elem_bytes, int grid_cap);
 
 }  // namespace spg
