@@ -76,7 +76,7 @@ struct spg_handle_s {
     Shard *shards_ana = nullptr, *shards_scan = nullptr;   // counters of the analysis and of the scan
     size_t zero_bytes = 0;
     Control* hctl = nullptr;  // pinned host copy
-    hipEvent_t ev_ctl = nullptr;  // marks the copy of the control block after the row-pointer scan
+    uint32_t seq = 0;         // publications of the control block asked for
 
     // symbolic result
     bool have_sym = false;
@@ -363,10 +363,34 @@ int clamp_lds_limit(spg_handle h, int v) {
     return v;
 }
 
+// The control block to the host: a kernel writes it into the pinned copy (see
+// k_publish) in the order of the stream, and the host polls for it.  A copy
+// with an event after it cost 10 to 15 us of a small product's time on top of
+// its kernels, this launch and the poll about 5.
+void publish_ctl(spg_handle h) { launch_publish(h->stream, h->ctl.as<Control>(), h->hctl, ++h->seq); }
+
+spg_status wait_ctl(spg_handle h) {
+    for (uint32_t spin = 1;; ++spin) {
+        if (__atomic_load_n(&h->hctl->seq, __ATOMIC_ACQUIRE) == h->seq) return SPG_OK;
+        if (spin % 256 == 0) {
+            // a stream that failed, or that is done without having published, ends the wait
+            const hipError_t e = hipStreamQuery(h->stream);
+            if (e == hipSuccess) {
+                if (__atomic_load_n(&h->hctl->seq, __ATOMIC_ACQUIRE) == h->seq) return SPG_OK;
+                return fail(h, SPG_ERR_HIP, "the control block did not arrive");
+            }
+            (void)hipGetLastError();
+            if (e != hipErrorNotReady) return hip_fail(h, e, "hipStreamQuery");
+        }
+        __builtin_ia32_pause();
+    }
+}
+
 spg_status sync_ctl(spg_handle h) {
-    HIP_TRY(h, hipMemcpyAsync(h->hctl, h->ctl.p, sizeof(Control), hipMemcpyDeviceToHost, h->stream));
-    HIP_TRY(h, hipStreamSynchronize(h->stream));
-    return SPG_OK;
+    publish_ctl(h);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return hip_fail(h, e, "control block launch");
+    return wait_ctl(h);
 }
 
 spg_status check_input_errors(spg_handle h) {
@@ -531,9 +555,9 @@ void sym_stage_analysis(spg_handle h) {
     rec(h, EV_ANA1);
 }
 
-// (with read_back, the control block is copied to the host right after the
-// row-pointer scan and an event marks the copy: the host needs nothing the
-// numeric grouping after it changes, and need not wait for it)
+// (with read_back, the control block is published to the host right after the
+// row-pointer scan: the host needs nothing the numeric grouping after it
+// changes, and need not wait for it)
 // (host_sized: launch per class from the histogram in h->geom even when the
 // handle could size its launches on the device; a captured batch graph
 // replays launches sized once by its planning run)
@@ -667,11 +691,7 @@ spg_status sym_stage_rows(spg_handle h, int32_t* c_row_ptr, bool read_back = fal
                 h->sym_cls.as<uint8_t>(), h->lofs.as<int32_t>(), c_row_ptr, h->tile_status, h->cfg,
                 h->num_cls.as<uint8_t>(), h->shards_scan, ctl);
     rec(h, EV_SCAN1);
-    if (read_back) {
-        if (!h->ev_ctl) HIP_TRY(h, hipEventCreateWithFlags(&h->ev_ctl, hipEventDisableTiming));
-        HIP_TRY(h, hipMemcpyAsync(h->hctl, h->ctl.p, sizeof(Control), hipMemcpyDeviceToHost, s));
-        HIP_TRY(h, hipEventRecord(h->ev_ctl, s));
-    }
+    if (read_back) publish_ctl(h);
     launch_scatter(s, m, h->num_cls.as<uint8_t>(), merging(h), ctl->num_hist, h->cursor_num,
                    h->perm_num.as<int32_t>(), h->arp, c_row_ptr, h->desc_num.as<int4>());
     hipError_t e = hipGetLastError();
@@ -903,6 +923,7 @@ spg_status spg_create(spg_handle* out, void* stream) {
         if (e == hipSuccess) {
             h->hctl = pinned_take();
             if (!h->hctl) e = hipErrorOutOfMemory;
+            else h->hctl->seq = 0;
         }
         if (e != hipSuccess) {
             (void)hipGetLastError();
@@ -929,7 +950,6 @@ spg_status spg_destroy(spg_handle h) {
     pinned_put(h->hctl);
     if (h->ev_made)
         for (auto& e : h->ev) (void)hipEventDestroy(e);
-    if (h->ev_ctl) (void)hipEventDestroy(h->ev_ctl);
     delete h;
     return SPG_OK;
 }
@@ -1013,7 +1033,7 @@ spg_status spg_symbolic(spg_handle h, int32_t* c_row_ptr, int64_t* nnz_c) {
         // the one wait: the control block copied right after the row-pointer
         // scan gives nnz(C), input errors and the numeric launch geometry
         // (the numeric grouping may still run; numeric is ordered after it)
-        HIP_TRY(h, hipEventSynchronize(h->ev_ctl));
+        SPG_TRY(wait_ctl(h));
         h->geom = *h->hctl;
         SPG_TRY(check_input_errors(h));
         SPG_TRY(sym_finish(h, c_row_ptr));

@@ -321,6 +321,8 @@ struct Control {
     // rows and first slot of every launch class after the class merge
     int32_t sym_cnt[NCLS];
     int32_t sym_off[NCLS];
+    uint32_t seq;                 // host copy: number of the publication it holds (last field)
+    uint32_t pad;
 };
 
 // Counters of the analysis and the scan kernels: thousands of workgroups that
@@ -346,6 +348,9 @@ static_assert(NCLS == 30, "the counter layout above");
 // ---- launch wrappers (spg_rows.hip) ----
 void launch_fill_i32(hipStream_t s, int32_t* p, int32_t v, int64_t n);
 void launch_fill_u8(hipStream_t s, void* p, uint8_t v, int64_t bytes);
+// Copies the control block into pinned host memory and then sets its seq: the
+// host polls that word instead of waiting for a copy and an event.
+void launch_publish(hipStream_t s, const Control* ctl, Control* host, uint32_t seq);
 // p 16-byte aligned, bytes a multiple of 16
 void launch_zero(hipStream_t s, void* p, int64_t bytes);
 // B rows in one pass: validation, binfo {length, smallest column, largest

@@ -14,6 +14,7 @@
 #include <hip/hip_runtime.h>
 #include <algorithm>
 #include <climits>
+#include <cstddef>
 
 #include "spg_internal.h"
 
@@ -40,6 +41,15 @@ __global__ void k_fill_u8(uint8_t* p, uint8_t v, int64_t n) {
 __global__ void k_zero(uint4* p, int64_t n16) {
     for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n16; i += (int64_t)gridDim.x * blockDim.x)
         p[i] = make_uint4(0, 0, 0, 0);
+}
+
+__global__ __launch_bounds__(256) void k_publish(const uint32_t* __restrict__ ctl, uint32_t* host, uint32_t seq) {
+    constexpr int WORDS = offsetof(Control, seq) / 4;
+    for (int i = threadIdx.x; i < WORDS; i += 256)
+        __hip_atomic_store(&host[i], ctl[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    __threadfence_system();
+    __syncthreads();
+    if (threadIdx.x == 0) __hip_atomic_store(&host[WORDS], seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
 // Every vector memory access of this thread has completed.
@@ -128,7 +138,10 @@ constexpr int long_row() {
 template <int L>
 __device__ inline int64_t dealt_row(int64_t pass, int64_t passes, int g) {
     const int C = passes == 1 ? 1 : 64 / L, per = 256 / L / C;
-    const int64_t chunk = (pass * per + g / C) * gridDim.x + blockIdx.x;
+    // (rotated from one round to the next: hub rows have few index bits set,
+    // and a power-of-two stride would deal them all to the same workgroups)
+    const int64_t round = pass * per + g / C;
+    const int64_t chunk = round * gridDim.x + (uint32_t)(blockIdx.x + round * 61) % gridDim.x;
     return chunk * C + g % C;
 }
 
@@ -1134,6 +1147,10 @@ void launch_fill_u8(hipStream_t s, void* p, uint8_t v, int64_t bytes) {
     int64_t g = (bytes + 255) / 256;
     if (g > 4096) g = 4096;
     hipLaunchKernelGGL(k_fill_u8, dim3((unsigned)g), dim3(256), 0, s, (uint8_t*)p, v, bytes);
+}
+
+void launch_publish(hipStream_t s, const Control* ctl, Control* host, uint32_t seq) {
+    hipLaunchKernelGGL(k_publish, dim3(1), dim3(256), 0, s, (const uint32_t*)ctl, (uint32_t*)host, seq);
 }
 
 void launch_zero(hipStream_t s, void* p, int64_t bytes) {
