@@ -10,6 +10,7 @@ output tensors with torch and passes pointers and the current stream.
 """
 from __future__ import annotations
 
+from contextlib import nullcontext
 from dataclasses import dataclass
 
 import numpy as np
@@ -47,6 +48,30 @@ def _dtype_code(t: torch.dtype) -> int:
     raise TypeError(f"values must be float32 or float64, got {t}")
 
 
+_NOW = nullcontext()
+_current_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
+def _on(stream: torch.cuda.Stream, device: torch.device):
+    """Context in which torch allocates in ``stream``'s order: none where it is
+    the current stream already (entering torch's own costs 6 us, half of a
+    small numeric call)."""
+    if _current_raw_stream is not None and _current_raw_stream(device.index) == stream.cuda_stream:
+        return _NOW
+    return torch.cuda.stream(stream)
+
+
+def _check_pair(A: DeviceCsr, B: DeviceCsr):
+    if A.n != B.m:
+        raise ValueError(f"inner dimensions differ: A is {A.m}x{A.n}, B is {B.m}x{B.n}")
+    if B.values.dtype != A.values.dtype:
+        raise TypeError("A and B values must have the same dtype")
+    for t, n, nm in ((A.row_ptr, A.m + 1, "A.row_ptr"), (B.row_ptr, B.m + 1, "B.row_ptr")):
+        _check_tensor(t, torch.int32, n, nm)
+    _check_tensor(A.col_idx, torch.int32, A.nnz, "A.col_idx")
+    _check_tensor(B.col_idx, torch.int32, B.nnz, "B.col_idx")
+
+
 def _check_tensor(t: torch.Tensor, dtype, n: int, what: str):
     if not t.is_cuda:
         raise ValueError(f"{what} must be on the GPU")
@@ -62,33 +87,20 @@ class SpGEMM:
     """Two-phase C = A*B bound to one handle and one stream."""
 
     def __init__(self, A: DeviceCsr, B: DeviceCsr, stream: torch.cuda.Stream | None = None, **options):
-        if A.n != B.m:
-            raise ValueError(f"inner dimensions differ: A is {A.m}x{A.n}, B is {B.m}x{B.n}")
-        self.A, self.B = A, B
-        self.dtype = A.values.dtype
-        if B.values.dtype != self.dtype:
-            raise TypeError("A and B values must have the same dtype")
-        for t, n, nm in ((A.row_ptr, A.m + 1, "A.row_ptr"), (B.row_ptr, B.m + 1, "B.row_ptr")):
-            _check_tensor(t, torch.int32, n, nm)
-        _check_tensor(A.col_idx, torch.int32, A.nnz, "A.col_idx")
-        _check_tensor(B.col_idx, torch.int32, B.nnz, "B.col_idx")
+        _check_pair(A, B)
         self.stream = stream or torch.cuda.current_stream()
         self.h = _lib.spg_create(self.stream.cuda_stream)
         for k, v in options.items():
             _lib.spg_set_option(self.h, k, int(v))
-        self.set_matrices(A, B)
+        self._bind(A, B)
 
     def set_matrices(self, A: DeviceCsr, B: DeviceCsr):
         """New matrices on the same handle (its buffers are kept and grown as
         needed); the symbolic result of the old ones is dropped."""
-        if A.n != B.m:
-            raise ValueError(f"inner dimensions differ: A is {A.m}x{A.n}, B is {B.m}x{B.n}")
-        if B.values.dtype != A.values.dtype:
-            raise TypeError("A and B values must have the same dtype")
-        for t, n, nm in ((A.row_ptr, A.m + 1, "A.row_ptr"), (B.row_ptr, B.m + 1, "B.row_ptr")):
-            _check_tensor(t, torch.int32, n, nm)
-        _check_tensor(A.col_idx, torch.int32, A.nnz, "A.col_idx")
-        _check_tensor(B.col_idx, torch.int32, B.nnz, "B.col_idx")
+        _check_pair(A, B)
+        self._bind(A, B)
+
+    def _bind(self, A: DeviceCsr, B: DeviceCsr):
         self.A, self.B = A, B
         self.dtype = A.values.dtype
         _lib.spg_set_matrices(self.h, _dtype_code(self.dtype), A.m, A.n, B.n,
@@ -114,10 +126,25 @@ class SpGEMM:
         _lib.spg_set_mlp(self.h, w.ctypes.data, int(w.size))
 
     def symbolic(self):
-        with torch.cuda.stream(self.stream):
-            self.row_ptr = torch.empty(self.A.m + 1, dtype=torch.int32, device=self.A.row_ptr.device)
+        dev = self.A.row_ptr.device
+        with _on(self.stream, dev):
+            self.row_ptr = torch.empty(self.A.m + 1, dtype=torch.int32, device=dev)
         self.nnz = _lib.spg_symbolic(self.h, self.row_ptr.data_ptr())
         return self.row_ptr, self.nnz
+
+    def _outputs(self, dev, out_col, out_val):
+        """C's arrays: the caller's, checked, or new ones in the handle's stream."""
+        if out_col is not None:
+            _check_tensor(out_col, torch.int32, self.nnz, "out_col")
+        if out_val is not None:
+            _check_tensor(out_val, self.dtype, self.nnz, "out_val")
+        if out_col is None or out_val is None:
+            with _on(self.stream, dev):
+                if out_col is None:
+                    out_col = torch.empty(self.nnz, dtype=torch.int32, device=dev)
+                if out_val is None:
+                    out_val = torch.empty(self.nnz, dtype=self.dtype, device=dev)
+        return out_col, out_val
 
     def numeric(self, a_vals: torch.Tensor | None = None, b_vals: torch.Tensor | None = None,
                 out_col: torch.Tensor | None = None, out_val: torch.Tensor | None = None):
@@ -128,13 +155,7 @@ class SpGEMM:
         _check_tensor(a_vals, self.dtype, self.A.nnz, "a_vals")
         _check_tensor(b_vals, self.dtype, self.B.nnz, "b_vals")
         dev = self.A.row_ptr.device
-        with torch.cuda.stream(self.stream):
-            if out_col is None:
-                out_col = torch.empty(self.nnz, dtype=torch.int32, device=dev)
-            if out_val is None:
-                out_val = torch.empty(self.nnz, dtype=self.dtype, device=dev)
-        _check_tensor(out_col, torch.int32, self.nnz, "out_col")
-        _check_tensor(out_val, self.dtype, self.nnz, "out_val")
+        out_col, out_val = self._outputs(dev, out_col, out_val)
         _lib.spg_numeric(self.h, a_vals.data_ptr(), b_vals.data_ptr(), out_col.data_ptr(), out_val.data_ptr())
         return out_col, out_val
 
@@ -151,13 +172,7 @@ class SpGEMM:
         _check_tensor(b_vals, self.dtype, self.B.nnz, "b_vals")
         _check_tensor(dinv, self.dtype, self.A.m, "dinv")
         dev = self.A.row_ptr.device
-        with torch.cuda.stream(self.stream):
-            if out_col is None:
-                out_col = torch.empty(self.nnz, dtype=torch.int32, device=dev)
-            if out_val is None:
-                out_val = torch.empty(self.nnz, dtype=self.dtype, device=dev)
-        _check_tensor(out_col, torch.int32, self.nnz, "out_col")
-        _check_tensor(out_val, self.dtype, self.nnz, "out_val")
+        out_col, out_val = self._outputs(dev, out_col, out_val)
         _lib.spg_numeric_jacobi(self.h, omega, dinv.data_ptr(), a_vals.data_ptr(), b_vals.data_ptr(),
                                 out_col.data_ptr(), out_val.data_ptr())
         return out_col, out_val
@@ -216,11 +231,26 @@ class SpAdd:
 
     def symbolic(self):
         A, B = self.A, self.B
-        with torch.cuda.stream(self.stream):
-            self.row_ptr = torch.empty(A.m + 1, dtype=torch.int32, device=A.row_ptr.device)
+        dev = A.row_ptr.device
+        with _on(self.stream, dev):
+            self.row_ptr = torch.empty(A.m + 1, dtype=torch.int32, device=dev)
         self.nnz = _lib.spg_add_symbolic(self.h, A.m, A.n, A.row_ptr.data_ptr(), A.col_idx.data_ptr(), A.nnz,
                                          B.row_ptr.data_ptr(), B.col_idx.data_ptr(), B.nnz, self.row_ptr.data_ptr())
         return self.row_ptr, self.nnz
+
+    def _outputs(self, dev, out_col, out_val):
+        """C's arrays: the caller's, checked, or new ones in the handle's stream."""
+        if out_col is not None:
+            _check_tensor(out_col, torch.int32, self.nnz, "out_col")
+        if out_val is not None:
+            _check_tensor(out_val, self.dtype, self.nnz, "out_val")
+        if out_col is None or out_val is None:
+            with _on(self.stream, dev):
+                if out_col is None:
+                    out_col = torch.empty(self.nnz, dtype=torch.int32, device=dev)
+                if out_val is None:
+                    out_val = torch.empty(self.nnz, dtype=self.dtype, device=dev)
+        return out_col, out_val
 
     def numeric(self, alpha: float = 1.0, beta: float = 1.0, a_vals: torch.Tensor | None = None,
                 b_vals: torch.Tensor | None = None, out_col: torch.Tensor | None = None,
@@ -232,13 +262,7 @@ class SpAdd:
         _check_tensor(a_vals, self.dtype, self.A.nnz, "a_vals")
         _check_tensor(b_vals, self.dtype, self.B.nnz, "b_vals")
         dev = self.A.row_ptr.device
-        with torch.cuda.stream(self.stream):
-            if out_col is None:
-                out_col = torch.empty(self.nnz, dtype=torch.int32, device=dev)
-            if out_val is None:
-                out_val = torch.empty(self.nnz, dtype=self.dtype, device=dev)
-        _check_tensor(out_col, torch.int32, self.nnz, "out_col")
-        _check_tensor(out_val, self.dtype, self.nnz, "out_val")
+        out_col, out_val = self._outputs(dev, out_col, out_val)
         _lib.spg_add_numeric(self.h, _dtype_code(self.dtype), alpha, a_vals.data_ptr(), beta, b_vals.data_ptr(),
                              out_col.data_ptr(), out_val.data_ptr())
         return out_col, out_val
