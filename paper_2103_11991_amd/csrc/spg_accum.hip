@@ -504,6 +504,76 @@ struct Batch {
     }
 };
 
+// Groups of several wavefronts: the P groups of a staged chunk (entry e's
+// begin at pbs[e]; off as above; all of it synchronised) are cut into one
+// contiguous range per wavefront, and every wavefront walks its own range
+// with a window table of its own, so that nothing but the staging of a chunk
+// takes workgroup barriers.  Windows over the whole group take six per batch:
+// R-MAT scale 18, 1024-lane symbolic rows 4.44 ms with them, 2.82 so; scale 13
+// FP64, 1024-lane numeric rows 46 us and 42, groups of 128 to 512 lanes within
+// 7% either way.  The global path's walks keep the windows: their chunks are
+// one batch each (the tiled kernel 14.1 ms with windows, 15.0 with ranges).
+// body(group, entry, valid) is called by all lanes.
+template <int G, int K, int V, typename Load, typename Body>
+__device__ inline void wave_ranges(const int* pbs, int n_entries, int P, const int2* off, Win* win, Load& load,
+                                   Body&& body) {
+    constexpr int W = G / 64;
+    const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), wl = threadIdx.x & 63;
+    const unsigned long long le = (2ull << wl) - 1;
+    const int per = (P + W * 64 - 1) / (W * 64) * 64;
+    const int r0 = wv * per, r1 = min(P, r0 + per);
+    if (r0 >= r1) return;
+    // the entry that owns group r0
+    int cur = 0;
+    for (int hi = n_entries - 1; cur < hi;) {
+        const int mid = (cur + hi + 1) >> 1;
+        if (__builtin_amdgcn_readfirstlane(pbs[mid]) <= r0) cur = mid;
+        else hi = mid - 1;
+    }
+    unsigned long long* masks = &win[wv * K].mask;  // one per Win, 16 bytes apart
+    for (int P0 = r0; P0 < r1; P0 += K * 64) {
+        // masks of the positions where later entries' groups begin
+        if (wl < K) masks[2 * wl] = 0ull;
+        group_sync<64>();
+        int next = cur + 1;
+        for (;;) {
+            const int e = next + wl;
+            const int d = e < n_entries ? pbs[e] - P0 : K * 64;
+            if (d < K * 64) atomicOr(&masks[2 * (d >> 6)], 1ull << (d & 63));
+            const int begun = __popcll(__ballot(d < K * 64));
+            next += begun;
+            if (begun < 64) break;
+        }
+        group_sync<64>();
+        unsigned long long m = 0;
+        if (wl < K) m = masks[2 * wl];
+        int entry[K], before = cur;
+#pragma unroll
+        for (int k = 0; k < K; ++k) {
+            const unsigned long long mk =
+                (unsigned long long)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(m >> 32), k) << 32 |
+                (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)m, k);
+            entry[k] = before + __popcll(mk & le);
+            before += __popcll(mk);
+        }
+        int2 o[K];
+#pragma unroll
+        for (int k = 0; k < K; ++k) {
+            o[k] = make_int2(0, 0);
+            if (P0 + k * 64 + wl < r1) o[k] = off[entry[k]];
+        }
+        decltype(load(0, 0)) v[K];
+#pragma unroll
+        for (int k = 0; k < K; ++k) {
+            const int g = P0 + k * 64 + wl;
+            if (g < r1) v[k] = load(o[k].x + V * g, o[k].y);
+        }
+#pragma unroll
+        for (int k = 0; k < K; ++k) body(v[k], entry[k], P0 + k * 64 + wl < r1);
+        cur = next - 1;
+    }
+}
+
 // ORs `bits` into l1[key].x; lanes next to each other in one group that hold
 // the same key are OR-ed together first (a segmented OR over each aligned
 // run of 16 lanes with DPP row shifts; segments also start at every group's
@@ -666,7 +736,8 @@ __device__ __forceinline__ void sym_row(const SymArgs& a, const int bytes, const
     uint8_t* row_lds = reinterpret_cast<uint8_t*>(smem) + (size_t)sub * per_row;
     uint32_t* tab = reinterpret_cast<uint32_t*>(row_lds);
     int2* cq = reinterpret_cast<int2*>(row_lds + bytes);   // staged run {offset, end}
-    Win* win = reinterpret_cast<Win*>(row_lds + bytes + 8 * G);
+    int* pbs = reinterpret_cast<int*>(row_lds + bytes + 8 * G);   // G > 64: their first runs' numbers
+    Win* win = reinterpret_cast<Win*>(row_lds + bytes + (G > 64 ? 12 : 8) * G);
     // direct: a mask per word of the row's range.  hashed: keys, then masks.
     // two-level: {bits, prefix} per 32 words, then per occupied block a mask,
     // then per occupied block its id (for the row's list; 16-bit offsets from
@@ -730,7 +801,7 @@ __device__ __forceinline__ void sym_row(const SymArgs& a, const int bytes, const
     sparse = sparse && slots;  // (the touched words share the staging area)
     if (!slots) {
         clear_table();
-        win_clear<G, KC>(win, lane);
+        if constexpr (G <= 64) win_clear<G, KC>(win, lane);
         group_sync<G>();
     }
 
@@ -740,12 +811,19 @@ __device__ __forceinline__ void sym_row(const SymArgs& a, const int bytes, const
     int staged = -1, wc0 = 0;
     // h: the lane's B header in chunk e0 (window table cleared and
     // synchronised by the caller)
+    int n_entries = 0;
     auto stage = [&](int e0, int4 h) {
         ne = h.w > 0;
-        int3 tot;
-        const int3 ex = group_excl_scan3<G>(make_int3(ne, (h.w + VC - 1) / VC, 0), tot, red);
-        pc = ex.y, PC = tot.y;
+        int2 tot;
+        const int2 ex = group_excl_scan2<G>(make_int2(ne, (h.w + VC - 1) / VC), tot, red);
+        pc = ex.y, PC = tot.y, n_entries = tot.x;
         if (ne) cq[ex.x] = make_int2(h.z - VC * ex.y, h.z + h.w);
+        if constexpr (G > 64) {
+            if (ne) pbs[ex.x] = ex.y;
+            group_sync<G>();
+            staged = e0;
+            return;
+        }
         win_mark<G, KC>(win, ne, pc, 0);
         group_sync<G>();
         win_scan<G, KC, 0>(win, nullptr, 0, 0, lane, red);
@@ -757,8 +835,10 @@ __device__ __forceinline__ void sym_row(const SymArgs& a, const int bytes, const
         int4 h = make_int4(0, 0, 0, 0);
         if (lane < a1 - e0) h = a.bhdr[a.aci[e0 + lane]];
         group_sync<G>();
-        win_clear<G, KC>(win, lane);
-        group_sync<G>();
+        if constexpr (G <= 64) {
+            win_clear<G, KC>(win, lane);
+            group_sync<G>();
+        }
         stage(e0, h);
     };
     auto rewin = [&](int P0) {
@@ -777,6 +857,12 @@ __device__ __forceinline__ void sym_row(const SymArgs& a, const int bytes, const
     auto walk_runs = [&](auto&& apply) {
         for (int e0 = a0; e0 < a1; e0 += G) {
             restage(e0);
+            if constexpr (G > 64) {
+                wave_ranges<G, KC, VC>(pbs, n_entries, PC, cq, win, load_run, [&](const auto& g, int e, bool valid) {
+                    if (valid) apply(g, e);
+                });
+                continue;
+            }
             for (int P0 = 0; P0 < PC; P0 += KC * G) {
                 rewin(P0);
                 Batch<G, KC, VC, decltype(load_run)> bt;
@@ -788,6 +874,11 @@ __device__ __forceinline__ void sym_row(const SymArgs& a, const int bytes, const
     auto walk_runs_all = [&](auto&& f) {
         for (int e0 = a0; e0 < a1; e0 += G) {
             restage(e0);
+            if constexpr (G > 64) {
+                wave_ranges<G, KC, VC>(pbs, n_entries, PC, cq, win, load_run,
+                                       [&](const auto& g, int, bool valid) { f(g, valid); });
+                continue;
+            }
             for (int P0 = 0; P0 < PC; P0 += KC * G) {
                 rewin(P0);
                 Batch<G, KC, VC, decltype(load_run)> bt;
@@ -916,7 +1007,7 @@ __device__ __forceinline__ void sym_row(const SymArgs& a, const int bytes, const
                 },
                 [&](auto&& f) { br.consume_all(0, s_tot, lane, f); });
         }
-    } else if (stage(a0, h0), a1 - a0 <= G && PC <= KC * G) {
+    } else if (stage(a0, h0), G <= 64 && a1 - a0 <= G && PC <= KC * G) {
         // the whole row in one batch: its runs stay in registers for every pass
         Batch<G, KC, VC, decltype(load_run)> br;
         br.issue(cq, win, 0, PC, lane, wv, le, load_run);
@@ -1266,7 +1357,8 @@ void k_num(NumArgs a) {
     uint8_t* tab = row_lds;
     int2* bq = reinterpret_cast<int2*>(row_lds + bytes);              // staged B {offset, end}
     T* ava = reinterpret_cast<T*>(row_lds + bytes + G * 8);           // their A values
-    Win* winb = reinterpret_cast<Win*>(row_lds + bytes + G * 16);     // B group windows
+    int* pbs = reinterpret_cast<int*>(row_lds + bytes + G * 16);      // G > 64: their first groups
+    Win* winb = reinterpret_cast<Win*>(row_lds + bytes + G * (G > 64 ? 20 : 16));  // B group windows
     // direct: {mask, prefix} per word.  two-level: l1 {bits, first list index}
     // per 32 blocks, then {mask, prefix} per occupied block.  hashed: slots.
     // Indices and prefixes are kept as LDS byte offsets from the start of the
@@ -1300,12 +1392,12 @@ void k_num(NumArgs a) {
         for (int c = lane; c < TT; c += G) slots[c] = make_int4(-1, 0, 0, 0);
     }
     for (int r = lane; r < n; r += G) vals[r] = V(0);
-    win_clear<G, KB>(winb, lane);
+    if constexpr (G <= 64) win_clear<G, KB>(winb, lane);
     group_sync<G>();
 
     // ---- staging (chunks of G entries of A's row; a window table of one batch)
     bool ne = false;
-    int pb = 0, P = 0;
+    int pb = 0, P = 0, n_entries = 0;
     int staged = -1, wb0 = 0;
     // h, v: the lane's B header and A value in chunk e0 (window table
     // cleared and synchronised by the caller)
@@ -1313,10 +1405,16 @@ void k_num(NumArgs a) {
         ne = h.y > 0;
         int2 tot;
         const int2 ex = group_excl_scan2<G>(make_int2(ne, (h.y + FLAT_VB - 1) / FLAT_VB), tot, red);
-        pb = ex.y, P = tot.y;
+        pb = ex.y, P = tot.y, n_entries = tot.x;
         if (ne) {
             bq[ex.x] = make_int2(h.x - FLAT_VB * ex.y, h.x + h.y);
             ava[ex.x] = v;
+        }
+        if constexpr (G > 64) {
+            if (ne) pbs[ex.x] = ex.y;
+            group_sync<G>();
+            staged = e0;
+            return;
         }
         win_mark<G, KB>(winb, ne, pb, 0);
         group_sync<G>();
@@ -1333,8 +1431,10 @@ void k_num(NumArgs a) {
             v = av[e0 + lane];
         }
         group_sync<G>();
-        win_clear<G, KB>(winb, lane);
-        group_sync<G>();
+        if constexpr (G <= 64) {
+            win_clear<G, KB>(winb, lane);
+            group_sync<G>();
+        }
         stage(e0, h, v);
     };
     // window table rebuilt for the batch starting at P0
@@ -1454,7 +1554,16 @@ void k_num(NumArgs a) {
     };
 
     stage(a0, h0, v0);
-    if (a1 - a0 <= G && P <= KB * G) {
+    if constexpr (G > 64) {
+        build();
+        for (int e0 = a0; e0 < a1; e0 += G) {
+            restage(e0);
+            wave_ranges<G, KB, FLAT_VB>(pbs, n_entries, P, bq, winb, load_cv,
+                                        [&](const BGroup<T>& g, int e, bool valid) {
+                                            if (valid) add(g, e);
+                                        });
+        }
+    } else if (a1 - a0 <= G && P <= KB * G) {
         // the whole row in one batch: its B loads are in flight while the table is built
         Batch<G, KB, FLAT_VB, decltype(load_cv)> bb;
         bb.issue(bq, winb, 0, P, lane, wv, le, load_cv);

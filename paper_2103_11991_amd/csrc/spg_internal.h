@@ -81,9 +81,14 @@ __host__ __device__ inline int group_waves(int g) { return g > 64 ? g / 64 : 1; 
 // numeric staging of one row: per staged A entry its B {offset, end} pair
 // and A's value (8 bytes each), then the window table (16 bytes per window
 // and wavefront) of the batch in flight
-__host__ __device__ inline int stage_bytes(int g) { return g * 16 + FLAT_KB_F32 * group_waves(g) * 16; }
+// (groups of several wavefronts also keep every entry's first group)
+__host__ __device__ inline int stage_bytes(int g) {
+    return g * (g > 64 ? 20 : 16) + FLAT_KB_F32 * group_waves(g) * 16;
+}
 // the symbolic phase stages no values and walks compressed B only
-__host__ __device__ inline int sym_stage_bytes(int g) { return g * 8 + FLAT_KC * group_waves(g) * 16; }
+__host__ __device__ inline int sym_stage_bytes(int g) {
+    return g * (g > 64 ? 12 : 8) + FLAT_KC * group_waves(g) * 16;
+}
 // dynamic LDS of one workgroup of tier t: the rows' tables plus staging
 __host__ __device__ inline int64_t tier_smem_bytes(int t) {
     return (int64_t)tier_rows(t) * (tier_bytes(t) + stage_bytes(tier_threads(t)));
