@@ -1315,12 +1315,10 @@ __global__ __launch_bounds__(G * rows_per_wg<G>()) __attribute__((amdgpu_waves_p
 void k_num(NumArgs a) {
     constexpr int RPW = rows_per_wg<G>();
     constexpr int KB = sizeof(T) == 8 ? FLAT_KB_F64 : FLAT_KB_F32;
-    // sums in FP64 up to the tier that acc_bytes names (its lanes per row)
-    using V = std::conditional_t<(G <= 256), double, T>;
-    static_assert(ACC64_TIER == 6, "tiers up to 6 have groups of at most 256 lanes");
+    using V = double;  // of the sums, whatever T is (see num_table_bytes)
     extern __shared__ __align__(16) uint32_t smem[];
     __shared__ int red[48];
-    const int bytes = tier_bytes(a.tier);
+    const int bytes = num_table_bytes(a.tier, sizeof(T));
     const int per_row = bytes + stage_bytes(G);
     // a group of 64 or more lanes owns whole wavefronts: its row is wave-uniform
     const int sub = G >= 64 ? __builtin_amdgcn_readfirstlane(threadIdx.x / G) : threadIdx.x / G;
@@ -2056,7 +2054,7 @@ template <int G, int MODE, typename T>
 void num_launch(hipStream_t s, const NumArgs& a) {
     constexpr int RPW = rows_per_wg<G>();
     const unsigned grid = (unsigned)((a.count + RPW - 1) / RPW);
-    const size_t smem = (size_t)RPW * (tier_bytes(a.tier) + stage_bytes(G));
+    const size_t smem = (size_t)RPW * (num_table_bytes(a.tier, sizeof(T)) + stage_bytes(G));
     hipLaunchKernelGGL((k_num<G, MODE, T>), dim3(grid), dim3(G * RPW), smem, s, a);
 }
 

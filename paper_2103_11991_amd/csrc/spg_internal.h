@@ -89,9 +89,26 @@ __host__ __device__ inline int stage_bytes(int g) {
 __host__ __device__ inline int sym_stage_bytes(int g) {
     return g * (g > 64 ? 12 : 8) + FLAT_KC * group_waves(g) * 16;
 }
-// dynamic LDS of one workgroup of tier t: the rows' tables plus staging
+// Bytes that the class choice counts per summed value of a numeric row of tier
+// t.  All rows sum in FP64: an LDS atomic add of FP32 values takes 192 cycles
+// of a compute unit per wavefront whatever the addresses (the lanes go one
+// after another), one of FP64 values 9 to 29 (FP32 numeric of the 27-point
+// 61^3 stencil: 0.85 ms with FP32 sums, 0.22 with FP64 ones).  Up to tier
+// ACC64_TIER the FP64 values count in full; FP32 rows that need more LDS than
+// that are classed by 4 bytes per value (else most would take the global
+// path) and run with twice their tier's LDS (num_table_bytes): half as many
+// wavefronts fit a compute unit, and still the 512-lane rows of R-MAT scale
+// 18 took 0.64 ms against 0.82 with FP32 sums, the 1024-lane ones 1.36
+// against 2.26.
+constexpr int ACC64_TIER = 6;
+__host__ __device__ inline int acc_bytes(int t, int elem_bytes) { return t <= ACC64_TIER ? 8 : elem_bytes; }
+// LDS table bytes per row of a numeric launch
+__host__ __device__ inline int num_table_bytes(int t, int elem_bytes) {
+    return acc_bytes(t, elem_bytes) < 8 ? 2 * tier_bytes(t) : tier_bytes(t);
+}
+// most dynamic LDS of one workgroup of tier t: the rows' tables plus staging
 __host__ __device__ inline int64_t tier_smem_bytes(int t) {
-    return (int64_t)tier_rows(t) * (tier_bytes(t) + stage_bytes(tier_threads(t)));
+    return (int64_t)tier_rows(t) * (num_table_bytes(t, 4) + stage_bytes(tier_threads(t)));
 }
 
 // Runtime knobs of the class choice (copied into kernels by value).
@@ -206,16 +223,6 @@ __host__ __device__ inline int sym_class(int64_t ub, int32_t cmin, int32_t cmax,
     if (t == TIER_GLOBAL || bd <= tier_bytes(t)) mode = MODE_DIRECT;
     return mode * NTIER + t;
 }
-
-// Bytes of one summed value in the numeric tables of tier t.  FP32 rows sum
-// in FP64 up to tier ACC64_TIER: an LDS atomic add of FP32 values takes 192
-// cycles of a compute unit per wavefront whatever the addresses (the lanes
-// go one after another), one of FP64 values 9 to 29 (27-point 61^3, FP32
-// numeric: 0.85 ms with FP32 sums).  Rows whose values need more LDS than
-// that tier has keep FP32 sums, which halve their tables: the alternative
-// for most of them is the global path.
-constexpr int ACC64_TIER = 6;
-__host__ __device__ inline int acc_bytes(int t, int elem_bytes) { return t <= ACC64_TIER ? 8 : elem_bytes; }
 
 // Numeric class of a row from its exact size n and occupied blocks, with eb
 // bytes per value: the direct table when the row's block range is about as
