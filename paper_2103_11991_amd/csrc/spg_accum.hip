@@ -624,18 +624,19 @@ __device__ inline auto each(F& f) {
 // One staged chunk of the walk: the lane's entry (if `has`) covers the piece
 // {first, length} = h of a B row with A value v.  The caller has cleared the
 // window table and synchronised the group.
-// extra: a value of the caller's scanned in the same pass, its exclusive
-// prefix and total returned in *extra_scan.
-template <int G, int K, int V, bool RUNS, typename T, typename Load, typename Apply>
+// extra: a value of the caller's scanned in the same pass; scanned(its
+// exclusive prefix, its total) is called before the walk, and what it writes to
+// LDS is there for apply.
+template <int G, int K, int V, bool RUNS, typename T, typename Load, typename Apply, typename Scanned>
 __device__ inline void walk_chunk(int2 h, T v, int2* off, T* ava, Win* win, int* red, Load& load, Apply&& apply,
-                                  int extra = 0, int2* extra_scan = nullptr) {
+                                  int extra, Scanned&& scanned) {
     const int lane = threadIdx.x % G, wv = lane >> 6;
     const unsigned long long le = (2ull << (lane & 63)) - 1;
     const int start = h.x, len = h.y;
     const bool ne = len > 0;
     int3 tot;
     const int3 ex = group_excl_scan3<G>(make_int3(ne, (len + V - 1) / V, extra), tot, red);
-    if (extra_scan) *extra_scan = make_int2(ex.z, tot.z);
+    scanned(ex.z, tot.z);
     const int P = tot.y;
     if (ne) {
         off[ex.x] = make_int2(start - V * ex.y, start + len);
@@ -674,7 +675,7 @@ __device__ void flat_walk_hdr(const int32_t* __restrict__ aci, Hdr&& hdr, const 
             h = hdr(aci[e0 + lane]);
             if constexpr (!RUNS) v = av[e0 + lane];
         }
-        walk_chunk<G, K, V, RUNS, T>(h, v, off, ava, win, red, load, apply);
+        walk_chunk<G, K, V, RUNS, T>(h, v, off, ava, win, red, load, apply, 0, [](int, int) {});
     }
     group_sync<G>();
 }
@@ -1766,93 +1767,201 @@ __global__ __launch_bounds__(WIDE_THREADS) void k_num_wide(NumArgs a) {
 // on the same tile of B and share it in L2.
 
 // Tile offsets: per B row, toff[t] = first entry whose column lies in tile t
-// or later (t = 0..T-1), toff[T] = the row's end.  Sixteen lanes per row; a
-// row whose tiles go down somewhere raises b_tile_unordered (the items then
-// all take the segment path).
+// or later (t = 0..T-1), toff[T] = the row's end.  One wavefront per row notes
+// the first entry of every tile that the row has and fills the tiles between
+// by a minimum from the back, so that the offsets are stored coalesced; a hub
+// row is read by the whole workgroup, four loads in flight per lane (R-MAT
+// scale 18, 64 tiles: 0.63 ms with 16 lanes per row that stored each gap one
+// lane after another, 0.49 with hub rows by one wavefront, 0.19 so).  A row whose tiles go down somewhere raises b_tile_unordered (the items
+// then all take the segment path).
 __global__ __launch_bounds__(256) void k_b_tiles(TileArgs a) {
+    __shared__ int first[4][TILE_MAX + 64];
+    constexpr int U = 4;
+    constexpr int HUB = 1024;  // longer rows are read by the whole workgroup
+    const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
     const int T = a.ntiles;
-    const int64_t total = (int64_t)a.n * 16;
-    for (int64_t g = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; g < total; g += (int64_t)gridDim.x * blockDim.x) {
-        const int j = (int)(g >> 4), l = (int)(g & 15);
-        const int s0 = a.brp[j], e0 = a.brp[j + 1];
-        int32_t* to = a.toff + (int64_t)j * (T + 1);
-        if (s0 == e0) {
-            for (int t = l; t <= T; t += 16) to[t] = s0;
-            continue;
-        }
-        for (int q = s0 + l; q < e0; q += 16) {
-            const int tq = a.bci[q] >> a.log_cols;
-            const int tp = q > s0 ? a.bci[q - 1] >> a.log_cols : -1;
-            if (tq < tp) {
-                a.ctl->b_tile_unordered = 1;
-                continue;
+    bool down = false;
+    // the first entries of the tiles that begin in [q0, q1) of the row from s0 on
+    auto heads = [&](int* f, int s0, int q0, int q1) {
+        int before = q0 > s0 ? a.bci[q0 - 1] >> a.log_cols : -1;
+        for (; q0 < q1; q0 += 64 * U) {
+            int tq[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) tq[u] = a.bci[min(q0 + u * 64 + lane, q1 - 1)] >> a.log_cols;
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const int q = q0 + u * 64 + lane;
+                const int up = __shfl_up(tq[u], 1);
+                const int tp = lane ? up : before;
+                if (q < q1) {
+                    down |= tq[u] < tp;
+                    if (tq[u] != tp) f[tq[u]] = q;
+                }
+                before = __builtin_amdgcn_readlane(tq[u], 63);
+                if (q0 + u * 64 + 64 >= q1) break;  // uniform
             }
-            for (int t = tp + 1; t <= tq; ++t) to[t] = q;
-            if (q == e0 - 1)
-                for (int t = tq + 1; t <= T; ++t) to[t] = e0;
         }
+    };
+    auto fill = [&](const int* f, int j, int e0) {
+        int after = e0;  // first entry of the tiles behind the round's
+        int32_t* to = a.toff + (int64_t)j * (T + 1);
+        if (lane == 0) to[T] = e0;
+        for (int t0 = (T - 1) & ~63; t0 >= 0; t0 -= 64) {
+            int x = t0 + lane < T ? f[t0 + lane] : e0;
+#pragma unroll
+            for (int d = 1; d < 64; d <<= 1) {
+                const int y = __shfl_down(x, d);
+                if (lane + d < 64) x = min(x, y);
+            }
+            x = min(x, after);
+            after = __builtin_amdgcn_readlane(x, 0);
+            if (t0 + lane < T) to[t0 + lane] = x;
+        }
+    };
+    const int step = gridDim.x * 4;
+    int j0 = blockIdx.x * 4;
+    int s1 = 0, e1 = 0;
+    if (j0 + w < a.n) s1 = a.brp[j0 + w], e1 = a.brp[j0 + w + 1];
+    while (j0 < a.n) {
+        const int j = j0 + w, s0 = s1, e0 = e1;
+        const bool more = j0 < a.n - step;  // (no overflow of j0)
+        if (more && j < a.n - step) s1 = a.brp[j + step], e1 = a.brp[j + step + 1];
+        else s1 = e1 = 0;
+        for (int t = lane; t < T; t += 64) first[w][t] = e0;
+        __builtin_amdgcn_wave_barrier();
+        const bool hub = e0 - s0 > HUB;
+        if (!hub && j < a.n) {
+            heads(first[w], s0, s0, e0);
+            __builtin_amdgcn_wave_barrier();
+            fill(first[w], j, e0);
+        }
+        if (__syncthreads_or(hub)) {
+            for (int v = 0; v < 4 && j0 + v < a.n; ++v) {
+                const int s = a.brp[j0 + v], e = a.brp[j0 + v + 1];
+                if (e - s <= HUB) continue;
+                const int per = (e - s + 255) / 256 * 64;
+                heads(first[v], s, min(s + w * per, e), min(s + w * per + per, e));
+            }
+            __syncthreads();
+            if (hub) fill(first[w], j, e0);
+        }
+        __builtin_amdgcn_wave_barrier();
+        if (!more) break;
+        j0 += step;
     }
+    if (down) a.ctl->b_tile_unordered = 1;
 }
 
 // Work items: one wavefront per row of the class walks the row's list once
-// and records, per tile, the list pairs that fall in it and the rank of the
-// first.  Rows without a list (or all rows, if B's rows are not grouped by
-// tile) go to the fallback list for the segment path, with empty items.
+// (the next round's pairs in flight) and records, per tile, its columns, the
+// list pairs that fall in it and the rank of the first.  Rows without a list
+// (or all rows, if B's rows are not grouped by tile) go to the fallback list
+// for the segment path, with empty items.  The class's rows are first dealt to
+// the heavy, light and fallback lists, 256 at a time by the first workgroups:
+// one atomic per row on one counter took half of the kernel's time (R-MAT
+// scale 18, 33 thousand rows: 0.78 ms, 0.41 so, of which the lists' pairs
+// take most).
 __global__ __launch_bounds__(256) void k_tile_items(TileArgs a) {
-    __shared__ int3 tl[4][TILE_MAX];
+    __shared__ int4 tl[4][TILE_MAX];
+    __shared__ int wsum[4][3], at[3];
     const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
     const int T = a.ntiles, R = a.rows;
     const int log_blocks = a.log_cols - 5;
     const bool unordered = a.ctl->b_tile_unordered != 0;
+    for (int64_t r0 = blockIdx.x * 256ll; r0 < R; r0 += gridDim.x * 256ll) {
+        const int r = (int)r0 + threadIdx.x;
+        int kind = -1, i = 0;  // 0 fallback, 1 heavy, 2 light
+        if (r < R) {
+            i = a.perm[r];
+            kind = a.lofs[i] < 0 || unordered ? 0 : a.arp[i + 1] - a.arp[i] > TILE_G ? 1 : 2;
+        }
+        int rank = 0;
+#pragma unroll
+        for (int k = 0; k < 3; ++k) {
+            const unsigned long long m = __ballot(kind == k);
+            if (kind == k) rank = __popcll(m & ((1ull << lane) - 1));
+            if (lane == 0) wsum[w][k] = __popcll(m);
+        }
+        __syncthreads();
+        if (threadIdx.x < 3) {
+            const int k = threadIdx.x, n = wsum[0][k] + wsum[1][k] + wsum[2][k] + wsum[3][k];
+            int* c = k == 0 ? &a.ctl->tile_fallback : k == 1 ? &a.ctl->tile_heavy : &a.ctl->tile_light;
+            at[k] = n ? atomicAdd(c, n) : 0;
+        }
+        __syncthreads();
+        if (kind >= 0) {
+            for (int v = 0; v < w; ++v) rank += wsum[v][kind];
+            rank += at[kind];
+            if (kind == 0) a.fallback[rank] = i;
+            else if (kind == 1) a.heavy[rank] = r;
+            else a.light[rank] = r;
+        }
+        __syncthreads();
+    }
     for (int r = blockIdx.x * 4 + w; r < R; r += gridDim.x * 4) {
         const int i = a.perm[r];
         const int lo = a.lofs[i];
         if (lo < 0 || unordered) {
-            if (lane == 0) a.fallback[atomicAdd(&a.ctl->tile_fallback, 1)] = i;
-            for (int t = lane; t < T; t += 64) a.items[(int64_t)t * R + r] = make_int4(i, 0, 0, 0);
+            for (int t = lane; t < T; t += 64) a.items[(int64_t)t * R + r] = make_int4(0, 0, 0, 0);
             continue;
         }
-        if (lane == 0) {
-            if (a.arp[i + 1] - a.arp[i] > TILE_G) a.heavy[atomicAdd(&a.ctl->tile_heavy, 1)] = r;
-            else a.light[atomicAdd(&a.ctl->tile_light, 1)] = r;
-        }
-        for (int t = lane; t < T; t += 64) tl[w][t] = make_int3(0, 0, 0);
+        for (int t = lane; t < T; t += 64) tl[w][t] = make_int4(0, 0, 0, 0);
         __builtin_amdgcn_wave_barrier();
         const int nbk = a.row_blocks[i];
         const int2* L = a.lists + lo;
-        int run = 0;
-        for (int p0 = 0; p0 < nbk; p0 += 64) {
-            const int p = p0 + lane;
-            const bool ok = p < nbk;
-            const int2 e = ok ? L[p] : make_int2(0, 0);
-            const int tile = e.x >> log_blocks;
-            const int prev = ok && p > 0 ? L[p - 1].x >> log_blocks : -1;
-            const int next = ok && p + 1 < nbk ? L[p + 1].x >> log_blocks : -1;
-            const int pop = ok ? __popc((uint32_t)e.y) : 0;
-            const int incl = wave_incl_scan<64>(pop);
-            if (ok && tile != prev) tl[w][tile].x = p, tl[w][tile].z = run + incl - pop;
-            if (ok && tile != next) tl[w][tile].y = p + 1;
-            run += __builtin_amdgcn_readlane(incl, 63);
+        constexpr int U = 4;
+        int run = 0, before = -1;
+        for (int p0 = 0; p0 < nbk; p0 += 64 * U) {
+            int2 e[U + 1];
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const int p = p0 + u * 64 + lane;
+                e[u] = make_int2(-1, 0);
+                if (p < nbk) e[u] = L[p];
+            }
+            e[U] = make_int2(-1, 0);  // the pair behind the rounds
+            if (lane == 0 && p0 + 64 * U < nbk) e[U] = L[p0 + 64 * U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const int p = p0 + u * 64 + lane;
+                const int tile = e[u].x >> log_blocks;  // -1 past the list's end
+                const int up = __shfl_up(tile, 1), down = __shfl_down(tile, 1);
+                const int prev = lane ? up : before;
+                const int next = lane < 63 ? down : __builtin_amdgcn_readlane(e[u + 1].x, 0) >> log_blocks;
+                const int incl = wave_incl_scan<64>(__popc((uint32_t)e[u].y));
+                if (tile >= 0) {
+                    if (tile != prev) tl[w][tile].y = p, tl[w][tile].w = run + incl - __popc((uint32_t)e[u].y);
+                    if (tile != next) tl[w][tile].z = p + 1, tl[w][tile].x = run + incl;
+                }
+                run += __builtin_amdgcn_readlane(incl, 63);
+                before = __builtin_amdgcn_readlane(tile, 63);
+            }
         }
         __builtin_amdgcn_wave_barrier();
         for (int t = lane; t < T; t += 64) {
-            const int3 v = tl[w][t];
-            a.items[(int64_t)t * R + r] = make_int4(i, lo + v.x, lo + v.y, v.z);
+            const int4 v = tl[w][t];
+            a.items[(int64_t)t * R + r] = make_int4(v.x - v.w, lo + v.y, lo + v.z, v.w);
         }
         __builtin_amdgcn_wave_barrier();
     }
 }
 
-// Work units, strided over the grid: first one per (tile, row) of the rows
+// Work units, strided over the grid.  HEAVY: one per (tile, row) of the rows
 // of more than TILE_G entries of A (their chunks are restaged per tile, and
-// the units of one row run on many workgroups), then one per other row, whose
-// tiles run in order on one workgroup with the row's entries held in
-// registers.  There each lane loads its entry's offset of the tile after next
-// while the current tile is walked (consecutive tiles share a boundary) and
-// the next tile's item is fetched early, so a tile waits only for its B
-// loads; the tile's list pairs are loaded before the walk and scanned after
-// it.
-template <typename T>
+// the units of one row run on many workgroups).  Else: one per other row,
+// whose tiles run in order on one workgroup with the row's entries held in
+// registers; each lane loads its entry's offset and list pairs of the next
+// tile while the current one is walked.  A tile costs a row a chain of
+// barriers and loads whatever it holds, and with 64 tiles (R-MAT scale 18) the
+// median tile of a row holds 325 products for 250 columns of C: neighbouring
+// sparse tiles are walked as one where their columns fit half the window in
+// rank order, with a {mask, rank} pair per word of the range in the other
+// half.  One more LDS read per product, 15 groups a row instead of 64 tiles:
+// 7.6 ms against 15.9 tile by tile in this kernel, and 14.1 against 12.4 with
+// the long rows, which ran in one kernel with the others before (two: each
+// has the registers and the order of units that it needs).  Both are bound by
+// latency: 16 wavefronts fit a compute unit beside the windows.
+template <typename T, bool HEAVY>
 __global__ __launch_bounds__(TILE_G) void k_num_tiled(TileArgs a) {
     constexpr int G = TILE_G;
     // The window sums in FP64 whatever T is: LDS atomic adds of FP32 values
@@ -1869,10 +1978,15 @@ __global__ __launch_bounds__(TILE_G) void k_num_tiled(TileArgs a) {
     __shared__ T ava[G];
     __shared__ Win win[K * (G / 64)];
     __shared__ int red[48];
+    __shared__ int2 cum[TILE_MAX + 1];  // light row: list pairs and columns before each tile
+    static_assert(TILE_MAX <= G, "a light row's items must fit one per lane");
+    constexpr int VM = W / 2;         // merged tiles: most columns of C, half the window
+    constexpr int MERGE = VM / NB;    // and most tiles (a {mask, rank} pair per word in the other half)
+    constexpr int PL = 4;             // and list pairs per lane
     const int tid = threadIdx.x;
     const int T_ = a.ntiles, R = a.rows;
-    const int nh = a.ctl->tile_heavy, nl = a.ctl->tile_light;
-    const int64_t units = (int64_t)nh * T_ + nl;
+    const int rows = HEAVY ? a.ctl->tile_heavy : a.ctl->tile_light;
+    const int64_t units = HEAVY ? (int64_t)rows * T_ : rows;
     const T* av = reinterpret_cast<const T*>(a.av);
     const T* bv = reinterpret_cast<const T*>(a.bv);
     T* cvals = reinterpret_cast<T*>(a.cval);
@@ -1907,12 +2021,11 @@ __global__ __launch_bounds__(TILE_G) void k_num_tiled(TileArgs a) {
     // the walk no longer needs, and each chunk is then written out.
     // pos: the lane's pair's first rank (the exclusive prefix of the pairs'
     // popcounts), n_t: the tile's columns
-    auto place_tile = [&](int i, int col0, int4 d, int np, int2 pr, int pos, int n_t) {
+    auto place_tile = [&](int64_t coff, int col0, int np, int2 pr, int pos, int n_t) {
         constexpr int CH = 2 * G;
         int* cbuf = reinterpret_cast<int*>(off);
         uint32_t rest = tid < np ? (uint32_t)pr.y : 0u;  // the pair's columns not yet placed
         const int first = tid < np ? (pr.x << 5) - col0 : 0;
-        const int64_t coff = (int64_t)a.crp[i] + d.w;
         for (int q0 = 0; q0 < n_t; q0 += CH) {
             while (rest && pos < q0 + CH) {
                 cbuf[pos - q0] = first + __builtin_ctz(rest);
@@ -1933,16 +2046,16 @@ __global__ __launch_bounds__(TILE_G) void k_num_tiled(TileArgs a) {
     auto end_tile = [&](int i, int col0, int4 d, int np, int2 pr) {
         int n_t;
         const int pos = group_excl_scan<G>(tid < np ? __popc((uint32_t)pr.y) : 0, n_t, red);
-        place_tile(i, col0, d, np, pr, pos, n_t);
+        place_tile((int64_t)a.crp[i] + d.w, col0, np, pr, pos, n_t);
     };
     for (int64_t u = blockIdx.x; u < units; u += gridDim.x) {
-        if (u < (int64_t)nh * T_) {
+        if constexpr (HEAVY) {
             // one tile of a long row; units are numbered tile-major, so the
             // workgroups in flight share a tile of B
-            const int r = a.heavy[u % nh];
-            const int t = (int)(u / nh);
+            const int r = a.heavy[u % rows];
+            const int t = (int)(u / rows);
             const int4 d = a.items[(int64_t)t * R + r];
-            const int i = __builtin_amdgcn_readfirstlane(d.x);
+            const int i = a.perm[r];
             const int p0 = __builtin_amdgcn_readfirstlane(d.y);
             const int np = __builtin_amdgcn_readfirstlane(d.z) - p0;
             if (np <= 0) continue;
@@ -1965,65 +2078,154 @@ __global__ __launch_bounds__(TILE_G) void k_num_tiled(TileArgs a) {
                                                    add);
             jacobi_tile(i, t, col0);
             end_tile(i, col0, d, np, pr);
-            continue;
-        }
-        // a row of at most G entries, all its tiles
-        const int r = a.light[u - (int64_t)nh * T_];
-        int4 d = a.items[r];
-        const int i = __builtin_amdgcn_readfirstlane(d.x);
-        const int a0 = a.arp[i], a1 = a.arp[i + 1];
-        const int* tj = nullptr;
-        T v = T(0);
-        int s_cur = 0, s_nxt = 0, s_nn = 0;
-        if (tid < a1 - a0) {
-            const int j = a.aci[a0 + tid];
-            v = av[a0 + tid];
-            tj = a.toff + (int64_t)j * (T_ + 1);
-            s_cur = tj[0];
-            s_nxt = tj[1];
-            if (T_ > 1) s_nn = tj[2];
-        }
-        // items are fetched two tiles ahead and list pairs one tile ahead
-        // (every lane loads: a lane past the tile's pairs reloads its last);
-        // the pairs' rank prefix is scanned with the walk's staging
-        auto pairs_of = [&](int4 it) {
-            const int q0 = __builtin_amdgcn_readfirstlane(it.y);
-            const int nq = __builtin_amdgcn_readfirstlane(it.z) - q0;
-            return nq > 0 ? a.lists[q0 + min(tid, nq - 1)] : make_int2(0, 0);
-        };
-        int4 dn = T_ > 1 ? a.items[(int64_t)R + r] : make_int4(0, 0, 0, 0);
-        int2 pr = pairs_of(d);
-        for (int t = 0; t < T_; ++t) {
-            const int4 dnn = t + 2 < T_ ? a.items[(int64_t)(t + 2) * R + r] : make_int4(0, 0, 0, 0);
-            const int2 pr_next = t + 1 < T_ ? pairs_of(dn) : make_int2(0, 0);
-            const int p0 = __builtin_amdgcn_readfirstlane(d.y);
-            const int np = __builtin_amdgcn_readfirstlane(d.z) - p0;
-            const int2 h = make_int2(s_cur, s_nxt - s_cur);
-            if (tj) {  // shift the offsets one tile on, fetching the next one early
-                s_cur = s_nxt;
-                s_nxt = s_nn;
-                if (t + 3 <= T_) s_nn = tj[t + 3];
+        } else {
+            // a row of at most G entries, all its tiles
+            const int r = a.light[u];
+            const int i = a.perm[r];
+            const int a0 = a.arp[i], a1 = a.arp[i + 1], lo = a.lofs[i];
+            const int64_t c0 = a.crp[i];
+            int2 item = make_int2(0, 0);
+            if (tid < T_) {
+                const int4 d = a.items[(int64_t)tid * R + r];
+                item = make_int2(d.z - d.y, d.x);
             }
-            if (np > 0) {
-                const int col0 = t * W;
-                win_clear<G, K>(win, tid);
-                auto add = [&](const BGroup<T>& g, int e) {
-                    const T x = ava[e];
+            // (the loads below run in every lane: one under a condition would be
+            // waited for before the next goes out)
+            const bool has = tid < a1 - a0;
+            const int q = a0 + min(tid, a1 - a0 - 1);
+            const T v = av[q];
+            const int* tj = a.toff + (int64_t)a.aci[q] * (T_ + 1);
+            int2 all;
+            const int2 before = group_excl_scan2<G>(item, all, red);
+            if (tid < T_) cum[tid] = before;
+            if (tid == 0) cum[T_] = all;
+            group_sync<G>();
+            // one past the last tile of the group that begins with tile t (the
+            // same in every wavefront; the conditions hold up to some lane)
+            auto group_end = [&](int t) {
+                const int l = tid & 63;
+                bool in = l < MERGE && t + l < T_;
+                if (in && l > 0) {
+                    const int2 b = cum[t], e = cum[t + l + 1];
+                    in = e.x - b.x <= PL * G && e.y - b.y <= VM;
+                }
+                return t + __popcll(__ballot(in));
+            };
+            // the list pairs of a group of tiles: one per lane of a tile by
+            // itself, PL in a row of merged ones
+            auto pairs_of = [&](int t, int te, int2* p) {
+                const int p0 = cum[t].x, n = cum[te].x - p0;
+                const int q = te - t == 1 ? tid : PL * tid;
 #pragma unroll
-                    for (int j = 0; j < 4; ++j)
-                        if (j < g.n) atomicAdd(&dense[g.c[j] - col0], (D)x * (D)g.y[j]);
-                };
-                group_sync<G>();
-                int2 sc;
-                walk_chunk<G, K, FLAT_VB, false, T>(h, v, off, ava, win, red, load_cv, add,
-                                                    tid < np ? __popc((uint32_t)pr.y) : 0, &sc);
-                group_sync<G>();
-                jacobi_tile(i, t, col0);
-                place_tile(i, col0, d, np, pr, sc.x, sc.y);
+                for (int k = 0; k < PL; ++k) {
+                    const int x = min(p0 + min(q + k, max(n - 1, 0)), max(all.x - 1, 0));
+                    p[k] = a.lists[lo + x];
+                }
+            };
+            // the columns of the lane's pair k, 0 past the group's end
+            auto bits = [&](int t, int te, const int2* p, int k) {
+                const int n = cum[te].x - cum[t].x;
+                return (te - t == 1 ? k == 0 && tid < n : PL * tid + k < n) ? (uint32_t)p[k].y : 0u;
+            };
+            int t = 0, te = group_end(0);
+            int s_cur = tj[0], s_nxt = tj[te];
+            int2 pr[PL];
+            pairs_of(0, te, pr);
+            while (t < T_) {
+                // the next group's offsets and list pairs are fetched early
+                const int tn = te < T_ ? group_end(te) : te;
+                const int s_nn = tj[tn];
+                int2 pn[PL];
+                pairs_of(te, tn, pn);
+#pragma unroll
+                for (int k = 0; k < PL; ++k) pr[k].y = bits(t, te, pr, k);
+                const int np = cum[te].x - cum[t].x;
+                if (np > 0) {
+                    const int2 h = make_int2(s_cur, has ? s_nxt - s_cur : 0);
+                    const int64_t coff = c0 + cum[t].y;
+                    const int n_t = cum[te].y - cum[t].y;
+                    win_clear<G, K>(win, tid);
+                    group_sync<G>();
+                    if (te - t == 1) {
+                        const int col0 = t * W;
+                        auto add = [&](const BGroup<T>& g, int e) {
+                            const T x = ava[e];
+#pragma unroll
+                            for (int j = 0; j < 4; ++j)
+                                if (j < g.n) atomicAdd(&dense[g.c[j] - col0], (D)x * (D)g.y[j]);
+                        };
+                        int pos = 0;
+                        walk_chunk<G, K, FLAT_VB, false, T>(h, v, off, ava, win, red, load_cv, add,
+                                                            __popc((uint32_t)pr[0].y),
+                                                            [&](int x, int) { pos = x; });
+                        group_sync<G>();
+                        jacobi_tile(i, t, col0);
+                        place_tile(coff, col0, np, pr[0], pos, n_t);
+                    } else {
+                        // merged tiles: the lower half of the window holds the
+                        // group's values in rank order, the upper half {mask,
+                        // rank} of each of its words (zero between groups)
+                        const int w0 = t * NB;
+                        uint2* tab = reinterpret_cast<uint2*>(dense + VM);
+                        auto slot_of = [&](int c) {
+                            const uint2 m = tab[(c >> 5) - w0];
+                            return &dense[m.y + __popc(m.x & below(c & 31))];
+                        };
+                        auto add = [&](const BGroup<T>& g, int e) {
+                            const T x = ava[e];
+                            D* pv[4];
+#pragma unroll
+                            for (int j = 0; j < 4; ++j) pv[j] = slot_of(j < g.n ? g.c[j] : g.c[0]);
+#pragma unroll
+                            for (int j = 0; j < 4; ++j)
+                                if (j < g.n) atomicAdd(pv[j], (D)x * (D)g.y[j]);
+                        };
+                        int cols = 0, pos = 0;
+#pragma unroll
+                        for (int k = 0; k < PL; ++k) cols += __popc((uint32_t)pr[k].y);
+                        walk_chunk<G, K, FLAT_VB, false, T>(h, v, off, ava, win, red, load_cv, add, cols,
+                                                            [&](int x, int) {
+                                                                pos = x;
+#pragma unroll
+                                                                for (int k = 0; k < PL; ++k) {
+                                                                    if (pr[k].y)
+                                                                        tab[pr[k].x - w0] = make_uint2(pr[k].y, x);
+                                                                    x += __popc((uint32_t)pr[k].y);
+                                                                }
+                                                            });
+                        group_sync<G>();
+                        if (a.dinv) {
+                            const T sc = -(T)a.omega * reinterpret_cast<const T*>(a.dinv)[i];
+                            for (int q = tid; q < n_t; q += G) dense[q] *= (D)sc;
+                            group_sync<G>();
+                            const int* ti = a.toff + (int64_t)i * (T_ + 1);
+                            for (int q = ti[t] + tid; q < ti[te]; q += G) atomicAdd(slot_of(a.bci[q]), (D)bv[q]);
+                            group_sync<G>();
+                        }
+                        // the columns in rank order, in the words' place
+                        int* cbuf = reinterpret_cast<int*>(tab);
+#pragma unroll
+                        for (int k = 0; k < PL; ++k)
+                            if (pr[k].y) tab[pr[k].x - w0] = make_uint2(0u, 0u);
+                        group_sync<G>();
+#pragma unroll
+                        for (int k = 0; k < PL; ++k)
+                            for (uint32_t m = pr[k].y; m; m &= m - 1u)
+                                cbuf[pos++] = (pr[k].x << 5) + __builtin_ctz(m);
+                        group_sync<G>();
+                        for (int q = tid; q < n_t; q += G) {
+                            a.ccol[coff + q] = cbuf[q];
+                            cvals[coff + q] = (T)dense[q];
+                            cbuf[q] = 0;
+                            dense[q] = D(0);
+                        }
+                    }
+                }
+                t = te, te = tn;
+                s_cur = s_nxt, s_nxt = s_nn;
+#pragma unroll
+                for (int k = 0; k < PL; ++k) pr[k] = pn[k];
             }
-            d = dn;
-            dn = dnn;
-            pr = pr_next;
         }
     }
 }
@@ -2138,8 +2340,7 @@ int launch_num_class(hipStream_t s, const NumArgs& a, int elem_bytes, int grid_c
 }
 
 void launch_tile_build(hipStream_t s, const TileArgs& a) {
-    const int64_t lanes = (int64_t)a.n * 16;
-    const unsigned gb = (unsigned)std::min<int64_t>((lanes + 255) / 256, 8192);
+    const unsigned gb = (unsigned)std::min<int64_t>(((int64_t)a.n + 3) / 4, 4096);
     if (gb > 0) hipLaunchKernelGGL(k_b_tiles, dim3(gb), dim3(256), 0, s, a);
     const unsigned gi = (unsigned)std::min<int64_t>(((int64_t)a.rows + 3) / 4, 4096);
     if (gi > 0) hipLaunchKernelGGL(k_tile_items, dim3(gi), dim3(256), 0, s, a);
@@ -2148,10 +2349,19 @@ void launch_tile_build(hipStream_t s, const TileArgs& a) {
 int launch_num_tiled(hipStream_t s, const TileArgs& a, int elem_bytes, int n_cu) {
     if (a.ntiles <= 0 || a.rows <= 0) return 0;
     // four 256-lane workgroups fit a compute unit's LDS (the unit counts are
-    // read on the device; workgroups beyond them exit at once)
+    // read on the device; workgroups beyond them exit at once).  Tiles of long
+    // rows are many and alike: the resident workgroups stride over them (8
+    // times as many: 5.27 ms for 4.82).  The other rows differ up to a hundred
+    // times in products: a workgroup each, placed as others end (R-MAT scale
+    // 18: 5.55 ms; dealt to the resident ones in advance 7.60).
     const int grid = (int)std::min<int64_t>((int64_t)a.rows * a.ntiles, (int64_t)n_cu * 4);
-    if (elem_bytes == 8) hipLaunchKernelGGL(k_num_tiled<double>, dim3(grid), dim3(TILE_G), 0, s, a);
-    else hipLaunchKernelGGL(k_num_tiled<float>, dim3(grid), dim3(TILE_G), 0, s, a);
+    if (elem_bytes == 8) {
+        hipLaunchKernelGGL((k_num_tiled<double, true>), dim3(grid), dim3(TILE_G), 0, s, a);
+        hipLaunchKernelGGL((k_num_tiled<double, false>), dim3(a.rows), dim3(TILE_G), 0, s, a);
+    } else {
+        hipLaunchKernelGGL((k_num_tiled<float, true>), dim3(grid), dim3(TILE_G), 0, s, a);
+        hipLaunchKernelGGL((k_num_tiled<float, false>), dim3(a.rows), dim3(TILE_G), 0, s, a);
+    }
     return grid;
 }
 

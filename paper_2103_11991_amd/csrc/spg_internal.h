@@ -490,7 +490,7 @@ struct TileArgs {
     const int32_t* row_blocks;
     const int2* lists;
     int32_t* toff;                // per B row, T + 1 tile offsets: first entry of each tile, then the row end
-    int4* items;                  // [T][R]: {row, first list pair, end pair, rank of the first pair}
+    int4* items;                  // [T][R]: {columns of C, first list pair, end pair, rank of the first pair}
     int32_t* fallback;            // rows for the segment path (no list, or B rows not grouped by tile)
     int32_t* heavy;               // class slots of rows of more than TILE_G entries of A
     int32_t* light;               // class slots of the other rows
