@@ -545,7 +545,7 @@ __global__ __launch_bounds__(64 * QWAVES) __attribute__((amdgpu_waves_per_eu(6))
 // time stamps reset; products without rows finished at once.
 __global__ void k_queue_init(QueueArgs a) {
     const int64_t g = blockIdx.x * (int64_t)blockDim.x + threadIdx.x, stride = (int64_t)gridDim.x * blockDim.x;
-    if (g == 0) a.qc->head = 0, a.qc->tail = 0, a.qc->used = 0;
+    if (g == 0) a.qc->head = 0, a.qc->tail = 0, a.qc->used = 0, a.qc->pad = 0;
     for (int64_t q = g; q < a.n_items; q += stride) a.queue[q] = 0;
     for (int64_t p = g; p < a.count; p += stride) {
         a.sym_left[p] = (int32_t)(a.item_off[p + 1] - a.item_off[p]);
