@@ -133,7 +133,7 @@ constexpr int long_row() {
 // A chunk is a wavefront's rows: neighbouring rows share what they gather and
 // the cache lines that they write.  One row where a single pass covers all
 // (m up to 131072): everything is in cache then, and the hub rows spread best
-// (R-MAT scale 13: 51 us with chunks of 16 rows).
+// (R-MAT scale 13: 51 us with chunks of 16 rows, 21 so).
 // The row of thread group `g` of the workgroup's 256 / L in pass `pass`:
 template <int L>
 __device__ inline int64_t dealt_row(int64_t pass, int64_t passes, int g) {
