@@ -1971,7 +1971,12 @@ __global__ __launch_bounds__(TILE_G) void k_num_tiled(TileArgs a) {
     using D = double;
     constexpr int W = TILE_BYTES / (int)sizeof(D);  // columns per tile
     constexpr int NB = W / 32;                       // blocks per tile
-    constexpr int K = sizeof(T) == 8 ? FLAT_KB_F64 : FLAT_KB_F32;
+    // B groups per lane and batch: two for the shorter rows in FP32, whose
+    // groups of tiles seldom fill more (R-MAT scale 18: 4.78 ms, 5.58 with
+    // four, 5.25 with one).  In FP64 three are as good (R-MAT scale 17: the
+    // numeric phase 4.81 ms, 4.90 with two), and the long rows' chunks gain
+    // nothing from fewer (4.80 ms with four, 4.94 with two).
+    constexpr int K = sizeof(T) == 8 ? FLAT_KB_F64 : HEAVY ? FLAT_KB_F32 : 2;
     static_assert(NB <= G, "a tile's list pairs must fit one per lane");
     __shared__ D dense[W];
     __shared__ int2 off[G];
