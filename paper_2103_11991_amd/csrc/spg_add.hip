@@ -104,17 +104,18 @@ __device__ inline int merge_slot(int t, int la, int lb, int P) { return t < la ?
 
 // Writes each entry's position in C's row from the ordered keys (slot s
 // holds key[s]) and returns the row's size.  Lanes of the group own P/G
-// consecutive slots each.
+// consecutive slots each.  The row's L keys come first; the slots after them
+// go by that count and not by their filling, which is a key too: column
+// 2^22 - 1 and entry 1023 are 32 set bits.
 template <int G, typename K>
-__device__ inline int positions_from_sorted(const K* key, int P, int la, int32_t* apos, int32_t* bpos,
+__device__ inline int positions_from_sorted(const K* key, int P, int L, int la, int32_t* apos, int32_t* bpos,
                                             int* red) {
     const int lane = threadIdx.x % G;
     const int per = P / G > 0 ? P / G : 1;
-    const int s0 = lane * per;
+    const int s0 = lane * per, s1 = min(s0 + per, L);
     int local = 0;
-    for (int s = s0; s < s0 + per && s < P; ++s) {
+    for (int s = s0; s < s1; ++s) {
         const K k = key[s];
-        if (k == (K)~(K)0) break;
         local += s == 0 || (key[s - 1] >> key_bits<K>()) != (k >> key_bits<K>());
     }
     int total, ex;
@@ -137,9 +138,8 @@ __device__ inline int positions_from_sorted(const K* key, int P, int la, int32_t
         ex = pre + incl - local;
     }
     int pos = ex - 1;
-    for (int s = s0; s < s0 + per && s < P; ++s) {
+    for (int s = s0; s < s1; ++s) {
         const K k = key[s];
-        if (k == (K)~(K)0) break;
         pos += s == 0 || (key[s - 1] >> key_bits<K>()) != (k >> key_bits<K>());
         const int t = key_entry(k);
         if (t < la) apos[t] = pos;
@@ -286,7 +286,7 @@ __device__ inline void wave_row(int64_t i, int32_t n, const RowPair& rw, int32_t
         }
         wave_sync();
         lds_bitonic<WAVE, K>(key, P, merge_only, wave_sync);
-        total = positions_from_sorted<WAVE, K>(key, P, rw.la, ap, bp, nullptr);
+        total = positions_from_sorted<WAVE, K>(key, P, L, rw.la, ap, bp, nullptr);
         wave_sync();
     }
     if (lane == 0) row_nnz[i] = total;
@@ -469,7 +469,7 @@ __global__ __launch_bounds__(LONG_THREADS) void k_add_sym_long(int32_t n, const 
         }
         __syncthreads();
         lds_bitonic<LONG_THREADS, uint64_t>(key, P, merge_only, [] { __syncthreads(); });
-        const int total = positions_from_sorted<LONG_THREADS, uint64_t>(key, P, rw.la, apos + as, bpos + bs, red);
+        const int total = positions_from_sorted<LONG_THREADS, uint64_t>(key, P, L, rw.la, apos + as, bpos + bs, red);
         if (tid == 0) row_nnz[i] = total;
         __syncthreads();
     }
