@@ -1278,25 +1278,31 @@ void drop_queue_graph(spg_batch b) {
 
 constexpr int QUEUE_ROWS_PER_ITEM = 128;
 
-// Once per batch: the row facts of the packed product (one synchronised
-// analysis), the widest row's range (which sizes the kernel's LDS windows, or
-// rules the queued path out), and the per-product item, row and row-pointer
-// offsets.
+// Once per batch: the row facts of the packed product, the widest row's range
+// (which sizes the kernel's LDS windows, or rules the queued path out), and
+// the per-product item, row and row-pointer offsets.  The facts are those of
+// the plan where there is one: a further analysis would place the rows' lists
+// anew (their order depends on which chunk of rows asks first), and numeric
+// runs on the plan would read the planned lists in the new places.  Without a
+// plan, one synchronised analysis (a plan made later analyses again).
 spg_status queue_prepare(spg_batch b) {
     if (b->q_ready) return SPG_OK;
     spg_handle h = b->h;
-    SPG_TRY(sym_prepare(h));
-    sym_stage_analysis(h);
-    SPG_TRY(sync_ctl(h));
-    SPG_TRY(check_input_errors(h));
-    const Control c = *h->hctl;
-    if (c.max_words_all > QUEUE_MAX_WORDS)
+    if (!b->planned) {
+        SPG_TRY(sym_prepare(h));
+        sym_stage_analysis(h);
+        SPG_TRY(sync_ctl(h));
+        SPG_TRY(check_input_errors(h));
+        h->geom = *h->hctl;
+    }
+    const int64_t max_words = h->geom.max_words_all;
+    if (max_words > QUEUE_MAX_WORDS)
         return bfail(b, SPG_ERR_UNSUPPORTED,
-                     "a row of C spans " + std::to_string(c.max_words_all * 32) +
+                     "a row of C spans " + std::to_string(max_words * 32) +
                          " columns; the queued kernel holds rows of up to " + std::to_string(QUEUE_MAX_WORDS * 32) +
                          " (use spg_batch_run)");
-    // compressed B for the symbolic items: built by the analysis above
-    b->q_wmax = (int)std::max<int64_t>(c.max_words_all, 1);
+    // compressed B for the symbolic items: built by the same analysis
+    b->q_wmax = (int)std::max<int64_t>(max_words, 1);
     b->q_vmax = 32 * b->q_wmax;
     const int32_t cnt = b->count;
     std::vector<int64_t> item_off((size_t)cnt + 1, 0), crp_off((size_t)std::max(cnt, 1), 0);
