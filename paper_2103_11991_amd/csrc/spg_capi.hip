@@ -1289,6 +1289,7 @@ spg_status queue_prepare(spg_batch b) {
     if (b->q_ready) return SPG_OK;
     spg_handle h = b->h;
     if (!b->planned) {
+        if (h->binning == 1 && !h->have_mlp) return bfail(b, SPG_ERR_STATE, "learned binning needs spg_batch_set_mlp");
         SPG_TRY(sym_prepare(h));
         sym_stage_analysis(h);
         SPG_TRY(sync_ctl(h));

@@ -42,3 +42,13 @@ def test_numeric_runs_on_the_plan_after_a_queued_run(plan_first):
         batch.run_queued(need)
         _check(batch.product_queued, prods)
 
+
+def test_learned_sizes_without_a_predictor_are_refused():
+    from paper_2103_11991_amd._lib import SpgError
+    from paper_2103_11991_amd.spgemm import DeviceCsr, SpGEMMBatch
+    A = gen.banded_random(300, 9, 1, 0)
+    batch = SpGEMMBatch([DeviceCsr.from_host(A)], [DeviceCsr.from_host(A)], binning=1)
+    for call in (batch.plan, lambda: batch.run_queued(10 ** 5)):
+        with pytest.raises(SpgError) as e:
+            call()
+        assert e.value.status_name == "SPG_ERR_STATE"
