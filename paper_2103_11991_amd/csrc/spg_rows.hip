@@ -894,7 +894,10 @@ struct BRow {
     int done = 0;          // runs begun in earlier chunks
     int mn = INT_MAX, mx = -1;
     uint32_t carry = 0;    // bits of the run still open at the end of the last chunk
-    int last_blk = -1;     // block of the last chunk's final entry
+    // block of the last chunk's final entry; before the first chunk what no
+    // column's block is, an invalid one's included: the first entry starts a
+    // run whatever it holds, so no run index is below 0
+    int last_blk = INT_MIN;
 };
 
 // U chunks of the row from entry Q0 on.  Unconditional loads, indices clamped
