@@ -378,6 +378,9 @@ struct WinView {
     }
 };
 
+// (Entries are stepped as unsigned numbers in the walks below: a row may end
+// at 2^31 - 1, and the step behind its last chunk passes the int32 range.)
+
 // Groups: V consecutive entries of one B row (or runs of one compressed-B
 // row) from index q, the first n = min(V, end - q) of them valid, read with
 // one 16-byte load per array (dword-aligned: 16-byte loads need only that on
@@ -421,7 +424,7 @@ __device__ inline RunGroup<V> load_runs(const int2* __restrict__ bc, int64_t tot
     g.n = min(V, end - q);
     if constexpr (V == 1) {
         g.r[0] = bc[q];
-    } else if (q + 2 <= total) {
+    } else if ((int64_t)q + 2 <= total) {
         const U4 v = *reinterpret_cast<const U4*>(bc + q);
         g.r[0] = make_int2(v.x, v.y);
         g.r[1] = make_int2(v.z, v.w);
@@ -437,7 +440,7 @@ __device__ inline BGroup<T> load_b(const int32_t* __restrict__ bci, const T* __r
                                    int end) {
     BGroup<T> g;
     g.n = min(4, end - q);
-    if (q + 4 <= total) {
+    if ((int64_t)q + 4 <= total) {
         const U4 c = *reinterpret_cast<const U4*>(bci + q);
         g.c[0] = c.x, g.c[1] = c.y, g.c[2] = c.z, g.c[3] = c.w;
         if constexpr (sizeof(T) == 8) {
@@ -666,7 +669,7 @@ template <int G, int K, int V, bool RUNS, typename T, typename Hdr, typename Loa
 __device__ void flat_walk_hdr(const int32_t* __restrict__ aci, Hdr&& hdr, const T* __restrict__ av, int a0, int a1,
                               int2* off, T* ava, Win* win, int* red, Load& load, Apply&& apply) {
     const int lane = threadIdx.x % G;
-    for (int e0 = a0; e0 < a1; e0 += G) {
+    for (uint32_t e0 = a0; e0 < (uint32_t)a1; e0 += G) {
         group_sync<G>();  // the previous chunk's readers are done
         win_clear<G, K>(win, lane);
         int2 h = make_int2(0, 0);
@@ -856,7 +859,7 @@ __device__ __forceinline__ void sym_row(const SymArgs& a, const int bytes, const
     };
     auto load_run = [&](int q, int end) { return load_runs<VC>(a.bc, a.bc_total, q, end); };
     auto walk_runs = [&](auto&& apply) {
-        for (int e0 = a0; e0 < a1; e0 += G) {
+        for (uint32_t e0 = a0; e0 < (uint32_t)a1; e0 += G) {
             restage(e0);
             if constexpr (G > 64) {
                 wave_ranges<G, KC, VC>(pbs, n_entries, PC, cq, win, load_run, [&](const auto& g, int e, bool valid) {
@@ -873,7 +876,7 @@ __device__ __forceinline__ void sym_row(const SymArgs& a, const int bytes, const
         }
     };
     auto walk_runs_all = [&](auto&& f) {
-        for (int e0 = a0; e0 < a1; e0 += G) {
+        for (uint32_t e0 = a0; e0 < (uint32_t)a1; e0 += G) {
             restage(e0);
             if constexpr (G > 64) {
                 wave_ranges<G, KC, VC>(pbs, n_entries, PC, cq, win, load_run,
@@ -1555,7 +1558,7 @@ void k_num(NumArgs a) {
     stage(a0, h0, v0);
     if constexpr (G > 64) {
         build();
-        for (int e0 = a0; e0 < a1; e0 += G) {
+        for (uint32_t e0 = a0; e0 < (uint32_t)a1; e0 += G) {
             restage(e0);
             wave_ranges<G, KB, FLAT_VB>(pbs, n_entries, P, bq, winb, load_cv,
                                         [&](const BGroup<T>& g, int e, bool valid) {
@@ -1570,7 +1573,7 @@ void k_num(NumArgs a) {
         bb.consume(0, P, lane, wv, le, add);
     } else {
         build();
-        for (int e0 = a0; e0 < a1; e0 += G) {
+        for (uint32_t e0 = a0; e0 < (uint32_t)a1; e0 += G) {
             restage(e0);
             for (int P0 = 0; P0 < P; P0 += KB * G) {
                 rewin(P0);
@@ -1587,7 +1590,7 @@ void k_num(NumArgs a) {
         const V sc = (V)(-(T)a.omega * reinterpret_cast<const T*>(a.dinv)[i]);
         for (int r = lane; r < n; r += G) vals[r] *= sc;
         group_sync<G>();
-        for (int q = a.brp[i] + lane; q < a.brp[i + 1]; q += G) atomicAdd(val_at(a.bci[q]), (V)bv[q]);
+        for (uint32_t q = a.brp[i] + lane; q < (uint32_t)a.brp[i + 1]; q += G) atomicAdd(val_at(a.bci[q]), (V)bv[q]);
     }
     group_sync<G>();
     T* cv = reinterpret_cast<T*>(a.cval) + off;
@@ -1617,7 +1620,7 @@ __device__ void wide_num_row(const NumArgs& a, int i, uint32_t* masks, int2* off
     int32_t* cc = a.ccol + coff;
     for (int c = tid; c < words; c += G) masks[c] = 0;
     if (!in_lds)
-        for (int r = tid; r < n; r += G) cv[r] = T(0);
+        for (uint32_t r = tid; r < (uint32_t)n; r += G) cv[r] = T(0);
     wg_fence();
     __syncthreads();
     const int a0 = a.arp[i], a1 = a.arp[i + 1];
@@ -1687,7 +1690,7 @@ __device__ void wide_num_row(const NumArgs& a, int i, uint32_t* masks, int2* off
                 const T sc = -(T)a.omega * reinterpret_cast<const T*>(a.dinv)[i];
                 for (int r = tid; r < len; r += G) lv[r] *= (double)sc;
                 __syncthreads();
-                for (int q = a.brp[i] + tid; q < a.brp[i + 1]; q += G) {
+                for (uint32_t q = a.brp[i] + tid; q < (uint32_t)a.brp[i + 1]; q += G) {
                     const int r = rank_of(a.bci[q]) - s0;
                     if ((unsigned)r < (unsigned)len) atomicAdd(&lv[r], (double)bv[q]);
                 }
@@ -1710,12 +1713,13 @@ __device__ void wide_num_row(const NumArgs& a, int i, uint32_t* masks, int2* off
             const T sc = -(T)a.omega * reinterpret_cast<const T*>(a.dinv)[i];
             wg_fence();
             __syncthreads();
-            for (int r = tid; r < n; r += G)
+            for (uint32_t r = tid; r < (uint32_t)n; r += G)
                 __hip_atomic_store(&cv[r], __hip_atomic_load(&cv[r], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) * sc,
                                    __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             wg_fence();
             __syncthreads();
-            for (int q = a.brp[i] + tid; q < a.brp[i + 1]; q += G) atomicAdd(&cv[rank_of(a.bci[q])], bv[q]);
+            for (uint32_t q = a.brp[i] + tid; q < (uint32_t)a.brp[i + 1]; q += G)
+                atomicAdd(&cv[rank_of(a.bci[q])], bv[q]);
         }
     }
     for (int t = tid; t < words; t += G) {
@@ -1782,7 +1786,7 @@ __global__ __launch_bounds__(256) void k_b_tiles(TileArgs a) {
     const int T = a.ntiles;
     bool down = false;
     // the first entries of the tiles that begin in [q0, q1) of the row from s0 on
-    auto heads = [&](int* f, int s0, int q0, int q1) {
+    auto heads = [&](int* f, uint32_t s0, uint32_t q0, uint32_t q1) {
         int before = q0 > s0 ? a.bci[q0 - 1] >> a.log_cols : -1;
         for (; q0 < q1; q0 += 64 * U) {
             int tq[U];
@@ -1790,12 +1794,12 @@ __global__ __launch_bounds__(256) void k_b_tiles(TileArgs a) {
             for (int u = 0; u < U; ++u) tq[u] = a.bci[min(q0 + u * 64 + lane, q1 - 1)] >> a.log_cols;
 #pragma unroll
             for (int u = 0; u < U; ++u) {
-                const int q = q0 + u * 64 + lane;
+                const uint32_t q = q0 + u * 64 + lane;
                 const int up = __shfl_up(tq[u], 1);
                 const int tp = lane ? up : before;
                 if (q < q1) {
                     down |= tq[u] < tp;
-                    if (tq[u] != tp) f[tq[u]] = q;
+                    if (tq[u] != tp) f[tq[u]] = (int)q;
                 }
                 before = __builtin_amdgcn_readlane(tq[u], 63);
                 if (q0 + u * 64 + 64 >= q1) break;  // uniform
@@ -1837,9 +1841,9 @@ __global__ __launch_bounds__(256) void k_b_tiles(TileArgs a) {
         }
         if (__syncthreads_or(hub)) {
             for (int v = 0; v < 4 && j0 + v < a.n; ++v) {
-                const int s = a.brp[j0 + v], e = a.brp[j0 + v + 1];
+                const uint32_t s = a.brp[j0 + v], e = a.brp[j0 + v + 1];
                 if (e - s <= HUB) continue;
-                const int per = (e - s + 255) / 256 * 64;
+                const uint32_t per = (e - s + 255) / 256 * 64;
                 heads(first[v], s, min(s + w * per, e), min(s + w * per + per, e));
             }
             __syncthreads();
@@ -2016,7 +2020,7 @@ __global__ __launch_bounds__(TILE_G) void k_num_tiled(TileArgs a) {
         for (int c = tid; c < W; c += G) dense[c] *= (D)sc;
         __syncthreads();
         const int* tr = a.toff + (int64_t)i * (T_ + 1);
-        for (int q = tr[t] + tid; q < tr[t + 1]; q += G) atomicAdd(&dense[a.bci[q] - col0], (D)bv[q]);
+        for (uint32_t q = tr[t] + tid; q < (uint32_t)tr[t + 1]; q += G) atomicAdd(&dense[a.bci[q] - col0], (D)bv[q]);
         __syncthreads();
     };
     // after the walk: the tile's columns in rank order, then columns and
@@ -2204,7 +2208,8 @@ __global__ __launch_bounds__(TILE_G) void k_num_tiled(TileArgs a) {
                             for (int q = tid; q < n_t; q += G) dense[q] *= (D)sc;
                             group_sync<G>();
                             const int* ti = a.toff + (int64_t)i * (T_ + 1);
-                            for (int q = ti[t] + tid; q < ti[te]; q += G) atomicAdd(slot_of(a.bci[q]), (D)bv[q]);
+                            for (uint32_t q = ti[t] + tid; q < (uint32_t)ti[te]; q += G)
+                                atomicAdd(slot_of(a.bci[q]), (D)bv[q]);
                             group_sync<G>();
                         }
                         // the columns in rank order, in the words' place

@@ -567,20 +567,21 @@ template <typename T>
 __device__ inline void add_long_row(const int32_t* __restrict__ aci, const T* __restrict__ av,
                                     const int32_t* __restrict__ bci, const T* __restrict__ bv,
                                     const int32_t* __restrict__ apos, const int32_t* __restrict__ bpos, T alpha,
-                                    T beta, int as, int ae, int bs, int be, int nc, int32_t* cc, T* cv, double* s) {
+                                    T beta, uint32_t as, uint32_t ae, uint32_t bs, uint32_t be, int nc, int32_t* cc,
+                                    T* cv, double* s) {  // (unsigned: the step behind a row's end may pass 2^31)
     const int lane = threadIdx.x % WAVE;
     if (nc > NUM_SEGMENTS * NUM_CAP) {
         for (int r = lane; r < nc; r += WAVE) cv[r] = T(0);
         wg_fence();
         wave_sync();
-        for (int t = as + lane; t < ae; t += WAVE) {
+        for (uint32_t t = as + lane; t < ae; t += WAVE) {
             const int p = apos[t];
             cc[p] = aci[t];
             atomicAdd(&cv[p], alpha * av[t]);
         }
         wg_fence();
         wave_sync();
-        for (int t = bs + lane; t < be; t += WAVE) {
+        for (uint32_t t = bs + lane; t < be; t += WAVE) {
             const int p = bpos[t];
             cc[p] = bci[t];
             atomicAdd(&cv[p], beta * bv[t]);
@@ -592,14 +593,14 @@ __device__ inline void add_long_row(const int32_t* __restrict__ aci, const T* __
         const int len = min(NUM_CAP, nc - s0);
         for (int r = lane; r < len; r += WAVE) s[r] = 0.0;
         wave_sync();
-        for (int t = as + lane; t < ae; t += WAVE) {
+        for (uint32_t t = as + lane; t < ae; t += WAVE) {
             const int p = apos[t] - s0;
             if ((unsigned)p >= (unsigned)len) continue;
             cc[s0 + p] = aci[t];
             atomicAdd(&s[p], (double)(alpha * av[t]));
         }
         wave_sync();
-        for (int t = bs + lane; t < be; t += WAVE) {
+        for (uint32_t t = bs + lane; t < be; t += WAVE) {
             const int p = bpos[t] - s0;
             if ((unsigned)p >= (unsigned)len) continue;
             cc[s0 + p] = bci[t];

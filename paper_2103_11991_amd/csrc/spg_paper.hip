@@ -275,8 +275,8 @@ __global__ __launch_bounds__(256) void k_paper_sym(PaperArgs a) {
             }
         } else {
             // team method: the flattened (A entry, compressed-B run) space, chunk by chunk
-            for (int e0 = a0; e0 < a1; e0 += G) {
-                const int cnt = min(G, a1 - e0);
+            for (uint32_t e0 = a0; e0 < (uint32_t)a1; e0 += G) {  // (a row may end at 2^31 - 1)
+                const int cnt = min((uint32_t)G, a1 - e0);
                 int len = 0, first = 0;
                 if (lane < cnt) {
                     const int4 h = a.bhdr[a.aci[e0 + lane]];
@@ -362,8 +362,8 @@ __global__ __launch_bounds__(256) void k_paper_num(PaperArgs a) {
                                      [&](int p) { return KV<T>{a.bci[b0 + p], x * bv[b0 + p]}; }, acc1, acc2);
             }
         } else {
-            for (int e0 = a0; e0 < a1; e0 += G) {
-                const int cnt = min(G, a1 - e0);
+            for (uint32_t e0 = a0; e0 < (uint32_t)a1; e0 += G) {  // (a row may end at 2^31 - 1)
+                const int cnt = min((uint32_t)G, a1 - e0);
                 int len = 0, first = 0;
                 T x = T(0);
                 if (lane < cnt) {

@@ -182,12 +182,16 @@ struct RowSums {
     int mx = 0, cmin = INT_MAX, cmax = -1, bad = 0, diag = 0;
 };
 
+// Indices of entries are stepped as unsigned numbers in the walks below: a
+// row may end at 2^31 - 1, and the step behind its last entries then passes
+// the int32 range.
+
 // Entries q..q+7 of an index array of `total` (those past its end: the last
 // one), with two 16-byte loads (dword-aligned) unless they reach past it.
 struct __attribute__((packed, aligned(4))) I4 {
     int x, y, z, w;
 };
-__device__ inline void load8(int* c, const int32_t* __restrict__ p, int32_t q, int64_t total) {
+__device__ inline void load8(int* c, const int32_t* __restrict__ p, uint32_t q, int64_t total) {
     if (q + (int64_t)8 <= total) {
         const I4 a = *reinterpret_cast<const I4*>(p + q), b = *reinterpret_cast<const I4*>(p + q + 4);
         c[0] = a.x, c[1] = a.y, c[2] = a.z, c[3] = a.w;
@@ -207,8 +211,8 @@ __device__ inline void load8(int* c, const int32_t* __restrict__ p, int32_t q, i
 // it before the next one is issued.
 template <int U, bool STEP1 = false>
 __device__ inline void row_entries(RowSums& r, const int32_t* __restrict__ aci, int64_t annz,
-                                   const int4* __restrict__ binfo, int32_t n, int64_t row, int32_t p0, int step,
-                                   int32_t e) {
+                                   const int4* __restrict__ binfo, int32_t n, int64_t row, uint32_t p0, int step,
+                                   uint32_t e) {
     int jj[U];
     if constexpr (STEP1) {
         static_assert(U == 8, "load8");
@@ -328,11 +332,11 @@ __global__ __launch_bounds__(256) void k_a_rowinfo(int32_t m, int32_t n, const i
         }
         // as many loads per round trip as the wavefront's longest row needs
         if constexpr (L == 1) {
-            for (int32_t p0 = s; p0 < e; p0 += 8) row_entries<8, true>(r, aci, annz, binfo, n, row, p0, 1, e);
+            for (uint32_t p0 = s; p0 < (uint32_t)e; p0 += 8) row_entries<8, true>(r, aci, annz, binfo, n, row, p0, 1, e);
         } else if (!__any(e - s > 2 * L)) {
-            if (s < e) row_entries<2>(r, aci, annz, binfo, n, row, s + lane, L, e);
+            if (s < e) row_entries<2>(r, aci, annz, binfo, n, row, (uint32_t)s + lane, L, e);
         } else {
-            for (int32_t p0 = s + lane; p0 < e; p0 += AN_LOADS * L)
+            for (uint32_t p0 = (uint32_t)s + lane; p0 < (uint32_t)e; p0 += AN_LOADS * L)
                 row_entries<AN_LOADS>(r, aci, annz, binfo, n, row, p0, L, e);
         }
         if (r.bad) atomicOr(&ctl->err, r.bad);
@@ -353,7 +357,7 @@ __global__ __launch_bounds__(256) void k_a_rowinfo(int32_t m, int32_t n, const i
                 const int64_t lrow = longs[l];
                 const int32_t ls = arp[lrow], le = arp[lrow + 1];
                 RowSums q;
-                for (int32_t p0 = ls + wl; p0 < le; p0 += AN_LOADS * 64)
+                for (uint32_t p0 = (uint32_t)ls + wl; p0 < (uint32_t)le; p0 += AN_LOADS * 64)
                     row_entries<AN_LOADS>(q, aci, annz, binfo, n, lrow, p0, 64, le);
                 auto add = [](auto x, auto y) { return x + y; };
                 auto hi = [](auto x, auto y) { return x > y ? x : y; };
@@ -904,22 +908,22 @@ struct BRow {
 // into the row (a load under a condition would be waited for before the next
 // one is issued); entries past the row's end are not used.
 template <int U>
-__device__ inline void b_chunks(BRow& r, const int32_t* __restrict__ bci, int2* __restrict__ bc, int32_t k, int32_t s,
-                                int32_t e, int32_t Q0, int sl, int shift) {
+__device__ inline void b_chunks(BRow& r, const int32_t* __restrict__ bci, int2* __restrict__ bc, int32_t k, uint32_t s,
+                                uint32_t e, uint32_t Q0, int sl, int shift) {
     constexpr int L = ROW_LANES;
     static_assert(L == 8, "the DPP shifts and swizzles below assume 8-lane groups");
     int cc[U], nx[U];
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-        const int32_t q = Q0 + u * L + sl;
+        const uint32_t q = Q0 + u * L + sl;
         cc[u] = bci[min(q, e - 1)];
         nx[u] = bci[min(q + 1, e - 1)];
     }
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-        const int32_t q0 = Q0 + u * L;
+        const uint32_t q0 = Q0 + u * L;
         if (q0 >= e) break;  // uniform in the row's lanes
-        const int32_t q = q0 + sl;
+        const uint32_t q = q0 + sl;
         const bool v = q < e;
         const int c = cc[u];
         if (v) {
@@ -965,11 +969,11 @@ __device__ inline void b_chunks(BRow& r, const int32_t* __restrict__ bci, int2* 
 
 // A row by one lane, eight entries at a time; its runs are written as they end.
 __device__ inline void b_lane(BRow& r, const int32_t* __restrict__ bci, int64_t bnnz, int2* __restrict__ bc, int32_t k,
-                              int32_t s, int32_t e) {
+                              uint32_t s, uint32_t e) {
     int blk = -1;
     uint32_t m = 0;  // the open run
     int2* out = bc + s;
-    for (int32_t q = s; q < e; q += 8) {
+    for (uint32_t q = s; q < e; q += 8) {
         int c[8];
         load8(c, bci, q, bnnz);
 #pragma unroll
@@ -991,15 +995,15 @@ __device__ inline void b_lane(BRow& r, const int32_t* __restrict__ bci, int64_t 
 
 // 64 U entries of a row from Q0 on by a whole wavefront, as b_chunks.
 template <int U>
-__device__ inline void b_wave(BRow& r, const int32_t* __restrict__ bci, int2* __restrict__ bc, int32_t k, int32_t s,
-                              int32_t e, int32_t Q0, int wl) {
+__device__ inline void b_wave(BRow& r, const int32_t* __restrict__ bci, int2* __restrict__ bc, int32_t k, uint32_t s,
+                              uint32_t e, uint32_t Q0, int wl) {
     int cc[U];
 #pragma unroll
     for (int u = 0; u < U; ++u) cc[u] = bci[min(Q0 + u * 64 + wl, e - 1)];
     const int after = bci[min(Q0 + U * 64, e - 1)];
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-        const int32_t q = Q0 + u * 64 + wl;
+        const uint32_t q = Q0 + u * 64 + wl;
         if (Q0 + u * 64 >= e) break;  // uniform
         const bool v = q < e;
         const int c = cc[u];
@@ -1088,7 +1092,8 @@ __global__ __launch_bounds__(256) void k_b_rows(int32_t n, int32_t k, const int3
             if (!__any(len > L)) {
                 if (len > 0) b_chunks<1>(r, bci, bc, k, s, e, s, sl, shift);
             } else {
-                for (int32_t Q0 = s; Q0 < s + len; Q0 += 4 * L) b_chunks<4>(r, bci, bc, k, s, e, Q0, sl, shift);
+                for (uint32_t Q0 = s; Q0 < (uint32_t)(s + len); Q0 += 4 * L)
+                    b_chunks<4>(r, bci, bc, k, s, e, Q0, sl, shift);
             }
             r.bad = row8_reduce(r.bad, [](int x, int y) { return x | y; });
             r.mn = row8_reduce(r.mn, [](int x, int y) { return min(x, y); });
@@ -1103,7 +1108,7 @@ __global__ __launch_bounds__(256) void k_b_rows(int32_t n, int32_t k, const int3
                 const int64_t lj = longs[l];
                 const int32_t ls = brp[lj], le = brp[lj + 1];
                 BRow q;
-                for (int32_t Q0 = ls; Q0 < le; Q0 += 8 * 64) b_wave<8>(q, bci, bc, k, ls, le, Q0, wl);
+                for (uint32_t Q0 = ls; Q0 < (uint32_t)le; Q0 += 8 * 64) b_wave<8>(q, bci, bc, k, ls, le, Q0, wl);
                 q.bad = __any(q.bad) ? ERR_B_COL : 0;
                 q.mn = wave_reduce(q.mn, [](auto x, auto y) { return x < y ? x : y; });
                 q.mx = wave_reduce(q.mx, [](auto x, auto y) { return x > y ? x : y; });
