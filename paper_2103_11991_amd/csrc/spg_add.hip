@@ -248,7 +248,7 @@ __device__ inline void wave_row(int64_t i, int32_t n, const RowPair& rw, int32_t
                                 int32_t* row_nnz, int32_t* long_list, AddCtl* ctl) {
     const int lane = threadIdx.x % WAVE;
     const int L = rw.la + rw.lb;
-    if (L > MID_CAP) {
+    if (rw.la > MID_CAP - rw.lb) {  // (their sum may pass 2^31)
         if (lane == 0) {
             long_list[atomicAdd(&ctl->long_rows, 1)] = (int32_t)i;
             row_nnz[i] = 0;
@@ -440,7 +440,7 @@ __global__ __launch_bounds__(LONG_THREADS) void k_add_sym_long(int32_t n, const 
         const int L = rw.la + rw.lb;
         if (tid == 0) flags[0] = flags[1] = 0;
         __syncthreads();
-        if (L > LONG_CAP) {
+        if (rw.la > LONG_CAP - rw.lb) {
             if (tid == 0) atomicOr(&ctl->err, AE_LONG);
             continue;
         }

@@ -99,3 +99,16 @@ def test_last_rows_of_an_addition(length):
         col, val = add.numeric(3.0, 3.0)
         _same(col, val, A, lambda c: torch.full(c.shape, 3.0, device="cuda"))
         del add, rp, col, val
+
+
+@pytest.mark.parametrize("la,lb", [(2 ** 30, 2 ** 30 + 5), (NNZ, 2), (2 ** 30, 16)])
+def test_row_pair_of_more_than_int32_entries_is_refused(la, lb):
+    import torch
+    from paper_2103_11991_amd._lib import SpgError
+    from paper_2103_11991_amd.spgemm import DeviceCsr, SpAdd
+    def row(count):
+        return DeviceCsr(1, 8, torch.tensor([0, count], dtype=torch.int32, device="cuda"),
+                         torch.zeros(count, dtype=torch.int32, device="cuda"), torch.ones(count, device="cuda"))
+    with pytest.raises(SpgError) as e:
+        SpAdd(row(la), row(lb)).symbolic()
+    assert e.value.status_name == "SPG_ERR_UNSUPPORTED"
