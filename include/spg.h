@@ -88,7 +88,10 @@ typedef enum {
        hashed block table (default 64) */
     SPG_OPT_HASH_MAX_BLOCKS = 6,
     /* LDS bytes per row at which the global-memory path takes over (power of
-       two, 1024..65536, default 65536) */
+       two, 1024..65536, default 65536).  Numeric rows sum in FP64 and are
+       counted with 8 bytes per value; FP32 rows that need more than 16384
+       bytes so are counted with 4 and hold twice what is counted (limits of
+       32768 and 65536 only) */
     SPG_OPT_LDS_LIMIT = 7,
     /* keep each row's predictor features after symbolic even with upper-bound
        binning, so spg_export_rows can return them (default 0) */

@@ -247,8 +247,9 @@ __host__ __device__ inline int num_class_eb(int64_t ub, int32_t words, int32_t n
     else if (blocks <= c.hash_max_blocks && bh < b2) mode = MODE_HASHED, bytes = bh;
     else mode = MODE_TWOLEVEL, bytes = b2;
     int t = pick_tier(bytes, ub, c);
-    // FP32 sums: in the tiers that have them
-    if (eb < 8 && t <= ACC64_TIER) t = ACC64_TIER + 1;
+    // counted by 4 bytes per value: only in the tiers that are (num_class comes
+    // here for rows beyond the others), and not past the limit
+    if (eb < 8 && t <= ACC64_TIER) t = tier_bytes(ACC64_TIER + 1) <= c.lds_limit ? ACC64_TIER + 1 : TIER_GLOBAL;
     // a tier raised for the row's work may hold the direct table (one lookup per product)
     if (t == TIER_GLOBAL || bd <= tier_bytes(t)) mode = MODE_DIRECT;
     return mode * NTIER + t;
