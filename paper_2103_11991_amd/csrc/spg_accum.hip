@@ -1599,11 +1599,26 @@ void k_num(NumArgs a) {
 
 // Global path of the numeric phase.  Values are summed in LDS (in FP64 for
 // either value type: LDS adds of FP32 are the slower ones, see acc_bytes), one
-// segment of `wide_vals` ranks at a time (every segment walks the row's products and
-// keeps those whose rank falls in it), then copied out coalesced; a row with
-// more than eight segments instead adds straight into C with global atomics.
+// segment of ranks at a time (every segment walks the row's products and
+// keeps those whose rank falls in it), then copied out coalesced; a row of
+// more segments instead adds straight into C with global atomics.
+// A segment is what the row's own table leaves of the LDS (9856 values beside
+// a table of 64 KB, 18048 where the table lies in the slab), and up to 16 of
+// them beat the atomics while the table is in LDS: 512 rows of C of n columns
+// from unsorted B, 1.4 products per column / 8 products per column, in ms,
+//     n      FP32: FP32 segments of 19.7k, at most 8   now          atomics
+//     15k    0.130 / 0.40                              0.082 / 0.125
+//     60k    0.56 / 2.56                               0.51 / 1.69
+//     90k    0.94 / 4.19                               1.02 / 3.58  3.17 / 17.5
+//     120k   1.35 / 6.85                               1.77 / 6.93  4.23 / 23.4
+// and FP64 at 90k: 2.91 / 15.7 before, 1.14 / 3.9 now.  A walk with the table
+// in the slab costs five times as much, so such rows have as many ranks as
+// eight segments beside the largest LDS table, at most five of theirs (144k
+// columns, 1.4 products each: 5.5 ms in eight of their segments, 3.4 with
+// atomics).
+constexpr int WIDE_SEGMENTS = 16;
 template <typename T, bool IN_LDS>
-__device__ void wide_num_row(const NumArgs& a, int i, uint32_t* masks, int2* off, T* ava, Win* win, double* lv,
+__device__ void wide_num_row(const NumArgs& a, int i, uint32_t* masks, int2* off, T* ava, Win* win, uint8_t* lds,
                              int* red) {
     constexpr int G = WIDE_THREADS;
     constexpr int KB = 2;  // B groups per lane and batch (1024 lanes: 8192 products per batch)
@@ -1613,8 +1628,10 @@ __device__ void wide_num_row(const NumArgs& a, int i, uint32_t* masks, int2* off
     const RowInfo ri = a.rinfo[i];
     const int base = ri.x >> 5;
     const int words = (ri.y >> 5) - base + 1;
-    const int seg = a.wide_vals;
-    const bool in_lds = seg > 0 && n <= 8 * seg;
+    const int tab = IN_LDS ? (words * 8 + 15) & ~15 : 0;
+    const int seg = (a.wide_lds + a.wide_vals * 8 - tab) / 8 & ~31;
+    const bool in_lds = a.wide_vals > 0 && n <= (IN_LDS ? WIDE_SEGMENTS * seg : 8 * a.wide_vals);
+    double* lv = reinterpret_cast<double*>(lds + tab);
     int32_t* pref = reinterpret_cast<int32_t*>(masks + words);
     T* cv = reinterpret_cast<T*>(a.cval) + coff;
     int32_t* cc = a.ccol + coff;
@@ -1740,18 +1757,18 @@ __global__ __launch_bounds__(WIDE_THREADS) void k_num_wide(NumArgs a) {
     extern __shared__ __align__(16) uint32_t smem[];
     __shared__ int red[48];
     uint32_t* slab = a.slab ? a.slab + (int64_t)blockIdx.x * a.slab_words : nullptr;
-    uint8_t* stage = reinterpret_cast<uint8_t*>(smem) + a.wide_lds;
+    uint8_t* lds = reinterpret_cast<uint8_t*>(smem);  // the row's table, then its values
+    uint8_t* stage = lds + a.wide_lds + a.wide_vals * 8;
     int2* off = reinterpret_cast<int2*>(stage);
     T* ava = reinterpret_cast<T*>(stage + WIDE_THREADS * 8);
     Win* win = reinterpret_cast<Win*>(stage + WIDE_THREADS * 16);
-    double* lv = reinterpret_cast<double*>(stage + WIDE_THREADS * 16 + WIDE_WIN_BYTES);
     const int count = a.count_dev ? *a.count_dev : a.count;
     for (int r = blockIdx.x; r < count; r += gridDim.x) {
         const int i = a.perm[r];
         const RowInfo ri = a.rinfo[i];
         const int64_t words = row_words(ri.x, ri.y);
-        if (words * 8 <= a.wide_lds) wide_num_row<T, true>(a, i, smem, off, ava, win, lv, red);
-        else wide_num_row<T, false>(a, i, slab, off, ava, win, lv, red);
+        if (words * 8 <= a.wide_lds) wide_num_row<T, true>(a, i, smem, off, ava, win, lds, red);
+        else wide_num_row<T, false>(a, i, slab, off, ava, win, lds, red);
     }
 }
 

@@ -339,8 +339,8 @@ int wide_lds(spg_handle h) {
     return v;
 }
 
-// FP64 values per LDS segment of a global-path numeric workgroup: what the device
-// leaves beside the mask table and the staged entries, 0 if under 4 KB
+// FP64 values in the LDS of a global-path numeric workgroup beside the largest
+// mask table and the staged entries, 0 if under 4 KB
 int wide_vals(spg_handle h) {
     const int64_t left = (int64_t)h->max_lds - wide_lds(h) - WIDE_THREADS * 16 - WIDE_WIN_BYTES - 1024;
     return left >= 4096 ? (int)((left & ~(int64_t)255) / 8) : 0;

@@ -457,7 +457,7 @@ struct NumArgs {
     uint32_t* slab;               // global path: masks and prefixes per workgroup
     int64_t slab_words;
     int32_t wide_lds;
-    int32_t wide_vals;            // global path: FP64 values per LDS segment (0 = global atomics only)
+    int32_t wide_vals;            // global path: FP64 values in LDS beside the largest table (0 = global atomics only)
     const int32_t* lofs;          // per row: first pair of its list, -1 if it has none
     const int2* lists;            // {block, mask} pairs in ascending block order
     const int32_t* count_dev;     // global path: device-side row count (or null)
