@@ -512,10 +512,12 @@ struct Batch {
 // contiguous range per wavefront, and every wavefront walks its own range
 // with a window table of its own, so that nothing but the staging of a chunk
 // takes workgroup barriers.  Windows over the whole group take six per batch:
-// R-MAT scale 18, 1024-lane symbolic rows 4.44 ms with them, 2.82 so; scale 13
-// FP64, 1024-lane numeric rows 46 us and 42, groups of 128 to 512 lanes within
-// 7% either way.  The global path's walks keep the windows: their chunks are
-// one batch each (the tiled kernel 14.1 ms with windows, 15.0 with ranges).
+// R-MAT scale 18, 1024-lane symbolic rows 4.44 ms with them, 2.29 so; scale 13
+// FP64, 1024-lane numeric rows 46 us and 40; the 27-point stencil's rows of 128
+// lanes under the product bound 1.59 ms a symbolic phase either way (1.70 with
+// the K loads of a batch one behind another, see the wait below).  The global
+// path's walks keep the windows: their chunks are one batch each (the tiled
+// kernel 14.1 ms with windows, 15.0 with ranges).
 // body(group, entry, valid) is called by all lanes.
 template <int G, int K, int V, typename Load, typename Body>
 __device__ inline void wave_ranges(const int* pbs, int n_entries, int P, const int2* off, Win* win, Load& load,
@@ -559,6 +561,9 @@ __device__ inline void wave_ranges(const int* pbs, int n_entries, int P, const i
             entry[k] = before + __popcll(mk & le);
             before += __popcll(mk);
         }
+        // no load of the previous batch is in flight: as in Batch::issue, without
+        // the wait the compiler orders the K loads one behind another
+        __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0)
         int2 o[K];
 #pragma unroll
         for (int k = 0; k < K; ++k) {
