@@ -111,11 +111,11 @@ __device__ inline void max_to(int64_t* p, unsigned long long v) {
 
 // Rows of the two analysis passes are dealt to the workgroups CHUNK
 // consecutive rows at a time, chunk c to workgroup c mod grid, and a row of
-// more than long_row entries is walked by a whole wavefront, not by its few
-// lanes: the hub rows of a power-law matrix (low row indices) would otherwise
-// sit in a few workgroups that walk them in hundreds of dependent round trips
-// while the rest of the grid is done (R-MAT scale 18: 0.67 and 0.75 ms for
-// the two passes, nearly all of it that).
+// more than long_row entries may be walked by a whole wavefront, not by its few
+// lanes (by_wavefront, for A): the hub rows of a power-law matrix (low row
+// indices) would otherwise sit in a few workgroups that walk them in hundreds
+// of dependent round trips while the rest of the grid is done (R-MAT scale 18:
+// 0.67 and 0.75 ms for the two passes, nearly all of it that).
 // Lanes per row L: with at least SHORT_MIN_ROWS rows of at most SHORT_ROWS
 // entries on average every row gets one lane, which takes eight of its
 // entries at a time with two 16-byte loads: several lanes per row leave most
@@ -126,10 +126,36 @@ __device__ inline void max_to(int64_t* p, unsigned long long v) {
 // SHORT_MIN_ROWS the chip is not full (4096 rows of A: 9 us against 16).
 constexpr int SHORT_ROWS = 8;
 constexpr int SHORT_MIN_ROWS = 1 << 17;
+// (B rows, eight lanes each: 20 thousand rows of 200 entries took 45 us in all
+// with rows of more than 128 by a wavefront, 36 so)
 template <int L>
 constexpr int long_row() {
-    return L == 8 ? 128 : 64;
+    return L == 8 ? 256 : 64;
 }
+// Whether a row of `len` entries of A goes to a wavefront: its own lanes take
+// PER of its entries a round trip, beside the other rows of their wavefront; a
+// wavefront takes 512 of one row.  So the long rows go where all of them one
+// after another take fewer round trips than the longest does with its own
+// lanes: a hub row among short ones does, rows that are all somewhat long do
+// not (20 thousand rows of 128 entries: 66 us with every one of them by a
+// wavefront, 22 so).  Past ALWAYS_LONG entries they all go: their lanes read
+// from as many far places a round trip, which costs several times a
+// wavefront's 2 KB in a row (200 rows of 20000 entries, one behind another:
+// the analysis 0.95 ms with their own lanes, 0.27 so; 2000 rows of 2000: 0.13
+// and 0.07).
+constexpr int ALWAYS_LONG = 512;
+template <int L, int PER>
+__device__ inline bool by_wavefront(int len) {
+    const bool is_long = len > long_row<L>();
+    if (!__any(is_long)) return false;
+    int trips = is_long && threadIdx.x % L == 0 ? (len - 1) / 512 + 1 : 0, longest = is_long ? len : 0;
+    for (int d = 32; d > 0; d >>= 1) {
+        trips += __shfl_xor(trips, d, 64);
+        longest = max(longest, __shfl_xor(longest, d, 64));
+    }
+    return is_long && (len > ALWAYS_LONG || trips * PER < longest);
+}
+
 // A chunk is a wavefront's rows: neighbouring rows share what they gather and
 // the cache lines that they write.  One row where a single pass covers all
 // (m up to 131072): everything is in cache then, and the hub rows spread best
@@ -325,7 +351,7 @@ __global__ __launch_bounds__(256) void k_a_rowinfo(int32_t m, int32_t n, const i
                 r.bad = ERR_A_ROWPTR, s = e = 0;
         }
         const int len = e - s;
-        const bool put_off = len > long_row<L>();
+        const bool put_off = by_wavefront<L, L == 1 ? 8 : AN_LOADS * L>(len);
         if (put_off) {
             if (lane == 0) longs[atomicAdd(&nlong[pass & 1], 1)] = (int32_t)row;
             e = s;
@@ -1126,6 +1152,18 @@ inline unsigned grid_for(int64_t threads, int per_block) {
     return (unsigned)(g < 1 ? 1 : g);
 }
 
+// Workgroups of an analysis pass over `rows` rows with L lanes each.  Where
+// rows are long on average, at least one workgroup per four rows: as few
+// workgroups as their lanes need leave the chip idle (2000 rows of 2000
+// entries of A: the analysis 141 us with 32 workgroups, 38 so; 10 thousand rows
+// of 400: 55 and 47; 15 thousand rows of 256: 46 and 62).
+constexpr int LONG_AVERAGE = 320;
+inline unsigned analysis_grid(int64_t rows, int lanes, int64_t nnz, unsigned most) {
+    int64_t g = grid_for(rows * lanes, 256);
+    if (nnz > rows * LONG_AVERAGE) g = std::max(g, (rows + 3) / 4);
+    return (unsigned)std::min<int64_t>(g, most);
+}
+
 }  // namespace
 
 // Rows per thread of the scan: one for small m, where a thread's eight rows
@@ -1175,7 +1213,7 @@ void launch_b_rows(hipStream_t s, int32_t n, int32_t k, const int32_t* brp, cons
         hipLaunchKernelGGL(k_b_rows<1>, dim3(std::min(grid_for(n, 256), 2048u)), dim3(256), 0, s, n, k, brp, bci, bnnz,
                            binfo, bc, bhdr, ctl);
     else
-        hipLaunchKernelGGL(k_b_rows<ROW_LANES>, dim3(std::min(grid_for((int64_t)n * ROW_LANES, 256), 4096u)),
+        hipLaunchKernelGGL(k_b_rows<ROW_LANES>, dim3(analysis_grid(n, ROW_LANES, bnnz, 4096)),
                            dim3(256), 0, s, n, k, brp, bci, bnnz, binfo, bc, bhdr, ctl);
 }
 
@@ -1188,7 +1226,7 @@ void launch_a_rowinfo(hipStream_t s, int32_t m, int32_t n, const int32_t* arp, c
         hipLaunchKernelGGL(k_a_rowinfo<1>, dim3(std::min(grid_for(m, 256), 2048u)), dim3(256), 0, s, m, n, arp, aci,
                            annz, binfo, rinfo, feats, cfg, binning, sym_cls, row_nnz, row_blocks, lofs, shards, ctl);
     else
-        hipLaunchKernelGGL(k_a_rowinfo<AN_LANES>, dim3(std::min(grid_for((int64_t)m * AN_LANES, 256), 2048u)),
+        hipLaunchKernelGGL(k_a_rowinfo<AN_LANES>, dim3(analysis_grid(m, AN_LANES, annz, 2048)),
                            dim3(256), 0, s, m, n, arp, aci, annz, binfo, rinfo, feats, cfg, binning, sym_cls, row_nnz,
                            row_blocks, lofs, shards, ctl);
 }
