@@ -728,9 +728,10 @@ constexpr int SLOT_MAX = 16;
 // the mask OR-ed in, and the bits that were not yet set (and blocks that were
 // empty) are counted from the value the atomic OR returns.
 
-// One row of the symbolic phase in a table of MODE in the row's LDS share
+// One row of the symbolic phase in a table of MODE in the row's LDS share (with
+// SLOTS: with a slot table and the sparse direct table where they apply)
 // (`bytes` of table, then the staging; d = the slot's descriptor {row, A start, A end, list offset}).
-template <int G, int MODE>
+template <int G, int MODE, bool SLOTS>
 __device__ __forceinline__ void sym_row(const SymArgs& a, const int bytes, const int4 d, const int sub, uint32_t* smem,
                                         int* red, int* occ, int* ovf) {
     constexpr int KC = FLAT_KC;
@@ -783,7 +784,7 @@ __device__ __forceinline__ void sym_row(const SymArgs& a, const int bytes, const
     // anyway (direct rows); the words it touches are listed as an OR finds
     // them empty, so that nothing walks the range.
     bool sparse = false;
-    if constexpr (G == 64 && MODE != MODE_HASHED)
+    if constexpr (SLOTS && G == 64 && MODE != MODE_HASHED)
         sparse = ncell > 3 * G && ncell <= SPARSE_WORDS && (MODE == MODE_DIRECT || (ncell * 4 <= bytes && !a.ovf_list));
     // 16-byte clears (tables start 16-byte aligned and their bytes are multiples of 16)
     auto clear_table = [&]() {
@@ -802,7 +803,7 @@ __device__ __forceinline__ void sym_row(const SymArgs& a, const int bytes, const
     // rows of one batch with short pieces of compressed B: slot table
     bool slots = false;
     int s_ex = 0, s_tot = 0;
-    if constexpr (G <= 64 && MODE != MODE_HASHED) {  // (hashed rows are scattered: seldom of one batch)
+    if constexpr (SLOTS && G <= 64 && MODE != MODE_HASHED) {  // (hashed rows are scattered: seldom of one batch)
         const int x = wave_incl_scan<G>(h0.w);
         s_ex = x - h0.w, s_tot = group_last<G>(x);
         slots = __all(a1 - a0 <= G && s_tot <= KC * G && h0.w <= SLOT_MAX);
@@ -1152,7 +1153,7 @@ __device__ __forceinline__ void sym_tier_mode(const SymArgs& a, const int bytes,
         const int k = g * RPW + sub;
         if (k >= total) break;  // uniform in the group (in the workgroup when G >= 128)
         group_sync<G>();        // the previous row's readers are done with the table
-        sym_row<G, MODE>(a, bytes, a.desc[first + k], sub, smem, red, occ, ovf);
+        sym_row<G, MODE, false>(a, bytes, a.desc[first + k], sub, smem, red, occ, ovf);
     }
 }
 
@@ -1160,7 +1161,7 @@ template <int G>
 __device__ __forceinline__ void sym_tier(const SymArgs& a, const int t, uint32_t* smem, int* red, int* occ, int* ovf) {
     // a group of 64 or more lanes owns whole wavefronts: its row is wave-uniform
     const int sub = G >= 64 ? __builtin_amdgcn_readfirstlane(threadIdx.x / G) : threadIdx.x / G;
-    const int bytes = sym_table_bytes(t, true, a.max_words);
+    const int bytes = tier_bytes(t);
     const int c0 = MODE_DIRECT * NTIER + t, c1 = MODE_HASHED * NTIER + t, c2 = MODE_TWOLEVEL * NTIER + t;
     const int n0 = a.ctl->sym_cnt[c0], n1 = a.ctl->sym_cnt[c1], n2 = a.ctl->sym_cnt[c2];
     if (n0 + n1 + n2 == 0) return;
@@ -1175,8 +1176,11 @@ __device__ __forceinline__ void sym_tier(const SymArgs& a, const int t, uint32_t
 // All LDS tiers in three launches (an empty launch costs 2.5 to 3 us, and
 // most of nine were empty: 30 of a 2D 64^2 product's 94 us): tiers up to 4 in
 // one of 256-lane workgroups, the heaviest first; 5 and 6 with 256 lanes per
-// row; 7 and 8 with 1024.  (up to 256 lanes per row the symbolic kernel fits
+// row; 7 and 8 with 1024.  (up to 128 lanes per row the symbolic kernel fits
 // 64 VGPRs: full occupancy)
+// The rows go without slot tables, whose registers spill in these loops (a
+// symbolic phase of 120 thousand rows on 64 lanes: 250 us with them, 206 so;
+// on 16 lanes: 145 and 132).
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(8))) void k_sym_tiers0(SymArgs a) {
     extern __shared__ __align__(16) uint32_t smem[];
     __shared__ int red[48];
@@ -1215,7 +1219,7 @@ void k_sym(SymArgs a) {
     const int sub = G >= 64 ? __builtin_amdgcn_readfirstlane(threadIdx.x / G) : threadIdx.x / G;
     const int slot = xcd_block<G>(blockIdx.x, gridDim.x) * RPW + sub;
     if (slot >= a.count) return;  // uniform in the group (in the workgroup when G >= 128)
-    sym_row<G, MODE>(a, a.table_bytes, a.desc[slot], sub, smem, red, occ, ovf);
+    sym_row<G, MODE, true>(a, a.table_bytes, a.desc[slot], sub, smem, red, occ, ovf);
 }
 
 template <bool IN_LDS>
@@ -2336,7 +2340,7 @@ void launch_sym_tiers(hipStream_t s, const SymArgs& a, int part, int t_last, int
     size_t smem = 0;
     for (int t = t0; t <= t1; ++t) {
         const int g = part == 0 ? tier_threads(t) : threads;
-        smem = std::max(smem, (size_t)(threads / g) * (sym_table_bytes(t, true, a.max_words) + sym_stage_bytes(g)));
+        smem = std::max(smem, (size_t)(threads / g) * (tier_bytes(t) + sym_stage_bytes(g)));
     }
     // at most what the compute units hold at once (2048 lanes, 160 KB of
     // LDS), and a workgroup per row group of the widest mapping

@@ -567,7 +567,6 @@ spg_status sym_stage_rows(spg_handle h, int32_t* c_row_ptr, bool read_back = fal
     const bool learned = h->binning == 1;
     Control* ctl = h->ctl.as<Control>();
     const int wl = wide_lds(h);
-    const int64_t words_k = ((int64_t)h->k + 31) / 32 + 1;
     SymArgs base{};
     base.arp = h->arp, base.aci = h->aci, base.brp = h->brp, base.bci = h->bci;
     base.bc = h->bc.as<int2>(), base.bhdr = h->bhdr.as<int4>();
@@ -626,7 +625,6 @@ spg_status sym_stage_rows(spg_handle h, int32_t* c_row_ptr, bool read_back = fal
             SymArgs a = base;
             a.perm = h->perm_sym.as<int32_t>();
             a.desc = h->desc_sym.as<int4>();
-            a.max_words = words_k;
             rec(h, EV_SYMCLS + 2 * t);
             launch_sym_tiers(s, a, part, t_last, m, h->n_cu);
             rec(h, EV_SYMCLS + 2 * t + 1);

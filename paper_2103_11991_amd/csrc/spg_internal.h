@@ -165,8 +165,8 @@ __host__ __device__ inline int32_t num_twolevel_bytes(int32_t words, int32_t blo
 // makes room for, in words (with the staging, seven workgroups of four rows
 // fit a compute unit).
 constexpr int SPARSE_WORDS = 1280;
-// LDS table bytes per row of a symbolic launch: its tier's; two-level rows of
-// one wavefront get what the direct table of the widest row takes, where that
+// LDS table bytes per row of a symbolic class launch: its tier's; two-level rows
+// of one wavefront get what the direct table of the widest row takes, where that
 // is within SPARSE_WORDS (see sparse rows in sym_row).
 __host__ __device__ inline int32_t sym_table_bytes(int tier, bool twolevel, int64_t max_words) {
     const int32_t b = tier_bytes(tier);
@@ -406,7 +406,6 @@ void launch_pack(hipStream_t s, int32_t count, const int64_t* desc, const int32_
 // ---- accumulator kernels (spg_accum.hip) ----
 struct SymArgs {
     int32_t table_bytes;          // LDS bytes of one row's table (class launches)
-    int64_t max_words;            // bound on a row's words (tier launches)
     const int32_t* perm;
     const int4* desc;             // per slot {row, A start, A end, list offset} (row kernels)
     int32_t count;
