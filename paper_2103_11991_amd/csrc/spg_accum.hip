@@ -1176,8 +1176,9 @@ __device__ __forceinline__ void sym_tier(const SymArgs& a, const int t, uint32_t
 // All LDS tiers in three launches (an empty launch costs 2.5 to 3 us, and
 // most of nine were empty: 30 of a 2D 64^2 product's 94 us): tiers up to 4 in
 // one of 256-lane workgroups, the heaviest first; 5 and 6 with 256 lanes per
-// row; 7 and 8 with 1024.  (up to 128 lanes per row the symbolic kernel fits
-// 64 VGPRs: full occupancy)
+// row; 7 and 8 with 1024, or 5 and 7 in launches of their own (the caller's
+// rule).  (up to 128 lanes per row the symbolic kernel fits 64 VGPRs: full
+// occupancy)
 // The rows go without slot tables, whose registers spill in these loops (a
 // symbolic phase of 120 thousand rows on 64 lanes: 250 us with them, 206 so;
 // on 16 lanes: 145 and 132).
@@ -1195,7 +1196,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(8))) void k
 }
 
 template <int G>
-__global__ __launch_bounds__(G) __attribute__((amdgpu_waves_per_eu(4))) void k_sym_tiers(SymArgs a, int t0, int t1) {
+__global__ __launch_bounds__(G) __attribute__((amdgpu_waves_per_eu(G == 128 ? 8 : 4)))
+void k_sym_tiers(SymArgs a, int t0, int t1) {
     extern __shared__ __align__(16) uint32_t smem[];
     __shared__ int red[48];
     __shared__ int occ[1];
@@ -2331,25 +2333,28 @@ int launch_sym_class(hipStream_t s, const SymArgs& a, int grid_cap) {
     return 1;
 }
 
-void launch_sym_tiers(hipStream_t s, const SymArgs& a, int part, int t_last, int64_t max_rows, int n_cu) {
+void launch_sym_tiers(hipStream_t s, const SymArgs& a, int t0, int t1, int64_t max_rows, int n_cu) {
     if (max_rows <= 0) return;
-    const int t0 = part == 0 ? 0 : part == 1 ? 5 : 7;
-    const int t1 = std::min(part == 0 ? 4 : part == 1 ? 6 : 8, t_last);
-    if (t1 < t0) return;
-    const int threads = part == 2 ? 1024 : 256;
+    const int threads = t0 == 0 ? 256 : tier_threads(t1);
     size_t smem = 0;
     for (int t = t0; t <= t1; ++t) {
-        const int g = part == 0 ? tier_threads(t) : threads;
+        const int g = t0 == 0 ? tier_threads(t) : threads;
         smem = std::max(smem, (size_t)(threads / g) * (tier_bytes(t) + sym_stage_bytes(g)));
     }
     // at most what the compute units hold at once (2048 lanes, 160 KB of
     // LDS), and a workgroup per row group of the widest mapping
     const int occ = std::max(1, std::min(2048 / threads, (int)(163840 / (smem + 1024))));
-    const int64_t groups = part == 0 ? (max_rows + 3) / 4 : max_rows;
+    const int64_t groups = t0 == 0 ? (max_rows + 3) / 4 : max_rows;
     const unsigned grid = (unsigned)((std::min<int64_t>((int64_t)occ * n_cu, groups) + 7) / 8 * 8);
-    if (part == 0) hipLaunchKernelGGL(k_sym_tiers0, dim3(grid), dim3(256), smem, s, a);
-    else if (part == 1) hipLaunchKernelGGL(k_sym_tiers<256>, dim3(grid), dim3(256), smem, s, a, t0, t1);
-    else hipLaunchKernelGGL(k_sym_tiers<1024>, dim3(grid), dim3(1024), smem, s, a, t0, t1);
+    if (t0 == 0) {
+        hipLaunchKernelGGL(k_sym_tiers0, dim3(grid), dim3(256), smem, s, a);
+        return;
+    }
+    const auto kernel = threads == 128   ? k_sym_tiers<128>
+                        : threads == 256 ? k_sym_tiers<256>
+                        : threads == 512 ? k_sym_tiers<512>
+                                         : k_sym_tiers<1024>;
+    hipLaunchKernelGGL(kernel, dim3(grid), dim3(threads), smem, s, a, t0, t1);
 }
 
 int launch_num_class(hipStream_t s, const NumArgs& a, int elem_bytes, int grid_cap) {

@@ -614,21 +614,35 @@ spg_status sym_stage_rows(spg_handle h, int32_t* c_row_ptr, bool read_back = fal
         rec(h, EV_SYMCLS + 1);
         h->sym_cls_timed[0] = h->timing == 1;
     } else if (h->single_wait && !host_sized) {
-        // three persistent launches for the LDS tiers; each reads its rows
-        // from the control block the grouping kernel wrote, so none waits for
-        // the host.  Tiers above the LDS limit never get rows.  A launch's
+        // three to five persistent launches for the LDS tiers; each reads its
+        // rows from the control block the grouping kernel wrote, so none waits
+        // for the host.  Tiers above the LDS limit never get rows.  A launch's
         // time is kept in its first tier's direct class.
         int t_last = -1;
         while (t_last + 1 < TIER_GLOBAL && tier_bytes(t_last + 1) <= h->cfg.lds_limit) ++t_last;
-        for (int part = 0; part < 3; ++part) {
-            const int t = part == 0 ? 0 : part == 1 ? 5 : 7;
+        // (128- and 512-lane rows run in the launch of twice the lanes, which
+        // saves two launches, except in a product of many such rows: its
+        // average row, all the host knows, has half to twice their products.
+        // 20 thousand rows of 8192 products take 200 us longer on 1024 lanes
+        // than on 512 (360 us in all), of 2048 products 35 longer on 256 than
+        // on 128 (130); 1000 rows: equal; a launch without rows costs 3 to 5.)
+        const double avg = h->n > 0 ? (double)h->annz / m * ((double)h->bnnz / h->n) / h->cfg.work_per_lane : 0.0;
+        auto apart = [&](int t) {
+            return m >= 4 * h->n_cu && avg > tier_threads(t) / 4 && avg <= tier_threads(t) * 2;
+        };
+        const int last[] = {4, apart(5) ? 5 : 6, 6, apart(7) ? 7 : 8, 8};
+        int t = 0;
+        for (int l : last) {
+            const int t1 = std::min(l, t_last);
+            if (t1 < t) continue;
             SymArgs a = base;
             a.perm = h->perm_sym.as<int32_t>();
             a.desc = h->desc_sym.as<int4>();
             rec(h, EV_SYMCLS + 2 * t);
-            launch_sym_tiers(s, a, part, t_last, m, h->n_cu);
+            launch_sym_tiers(s, a, t, t1, m, h->n_cu);
             rec(h, EV_SYMCLS + 2 * t + 1);
             h->sym_cls_timed[t] = h->timing == 1;
+            t = t1 + 1;
         }
         if (h->sym_global_grid > 0) {
             const int gcls = MODE_DIRECT * NTIER + TIER_GLOBAL;

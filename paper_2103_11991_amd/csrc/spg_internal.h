@@ -590,12 +590,13 @@ inline void sym_class_offsets(const int32_t* rows, int32_t* off) {
             off[c] = run, run += rows[c];
         }
 }
-// Symbolic rows of the LDS tiers (all three table modes) up to t_last, sized
-// on the device: the kernels read each tier's rows and first slots from the
-// control block the grouping kernel wrote.  part 0: tiers 0 to 4, 1: 5 and 6,
-// 2: 7 and 8.  Persistent: a grid of what the device holds at once, at most
-// one workgroup per row group of max_rows, each XCD a contiguous share.
-void launch_sym_tiers(hipStream_t s, const SymArgs& a, int part, int t_last, int64_t max_rows, int n_cu);
+// Symbolic rows of the LDS tiers t0 to t1 (all three table modes), sized on
+// the device: the kernels read each tier's rows and first slots from the
+// control block the grouping kernel wrote.  From tier 0 to at most 4: each
+// with its own lanes; else one or two tiers, with the lanes of t1.
+// Persistent: a grid of what the device holds at once, at most one workgroup
+// per row group of max_rows, each XCD a contiguous share.
+void launch_sym_tiers(hipStream_t s, const SymArgs& a, int t0, int t1, int64_t max_rows, int n_cu);
 int launch_num_class(hipStream_t s, const NumArgs& a, int elem_bytes, int grid_cap);
 
 }  // namespace spg
