@@ -34,7 +34,8 @@ namespace {
 constexpr int WAVE = 64;
 constexpr int MID_CAP = 1024;      // keys per wavefront in LDS
 constexpr int NUM_CAP = 512;       // columns per wavefront in LDS, numeric (16 KB per workgroup: full occupancy)
-constexpr int NUM_SEGMENTS = 8;    // numeric rows of more than this many times NUM_CAP columns sum in C's storage
+constexpr int WIDE_THREADS = 256;  // lanes of a numeric row of more than NUM_CAP columns
+constexpr int WIDE_CAP = 4096;     // ... and its columns in LDS at a time, at most (32 KB)
 constexpr int LONG_CAP = 16384;    // keys per row on the long-row path
 constexpr int LONG_THREADS = 1024;
 constexpr int ROWS_PER_WG = 4;     // wavefronts (rows) per workgroup of the short/medium kernels
@@ -50,13 +51,9 @@ struct AddCtl {
     int32_t err;
     int32_t long_rows;      // rows queued for the long-row kernel
     int32_t tile_counter;   // dynamic tile id of the row-pointer scan
-    int32_t pad;
+    int32_t widest;         // longest row of C of more than NUM_CAP columns (0: no such row)
     int64_t nnz_c;
 };
-
-// Orders a wavefront's own global-memory accesses (the C row it writes):
-// workgroup scope is enough and writes nothing back from L2.
-__device__ inline void wg_fence() { __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "workgroup"); }
 
 __device__ inline void wave_sync() {
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
@@ -114,9 +111,13 @@ __device__ inline int positions_from_sorted(const K* key, int P, int L, int la, 
     const int per = P / G > 0 ? P / G : 1;
     const int s0 = lane * per, s1 = min(s0 + per, L);
     int local = 0;
+    K before = 0;  // the key of slot s0 - 1
+    if (s0 > 0 && s0 < s1) before = key[s0 - 1];
+    K prev = before;
     for (int s = s0; s < s1; ++s) {
         const K k = key[s];
-        local += s == 0 || (key[s - 1] >> key_bits<K>()) != (k >> key_bits<K>());
+        local += s == 0 || (prev >> key_bits<K>()) != (k >> key_bits<K>());
+        prev = k;
     }
     int total, ex;
     if constexpr (G == WAVE) {
@@ -138,9 +139,11 @@ __device__ inline int positions_from_sorted(const K* key, int P, int L, int la, 
         ex = pre + incl - local;
     }
     int pos = ex - 1;
+    prev = before;
     for (int s = s0; s < s1; ++s) {
         const K k = key[s];
-        pos += s == 0 || (key[s - 1] >> key_bits<K>()) != (k >> key_bits<K>());
+        pos += s == 0 || (prev >> key_bits<K>()) != (k >> key_bits<K>());
+        prev = k;
         const int t = key_entry(k);
         if (t < la) apos[t] = pos;
         else bpos[t - la] = pos;
@@ -476,7 +479,8 @@ __global__ __launch_bounds__(LONG_THREADS) void k_add_sym_long(int32_t n, const 
 }
 
 // C's row pointer: exclusive scan of the row sizes in int64, single pass with
-// decoupled look-back over tiles taken in order; flags nnz(C) >= 2^31.
+// decoupled look-back over tiles taken in order; flags nnz(C) >= 2^31 and finds
+// the longest row.
 __global__ __launch_bounds__(SCAN_THREADS) void k_add_scan(int32_t m, const int32_t* __restrict__ row_nnz,
                                                            int32_t* __restrict__ crp, uint64_t* tile_status,
                                                            AddCtl* ctl) {
@@ -489,11 +493,21 @@ __global__ __launch_bounds__(SCAN_THREADS) void k_add_scan(int32_t m, const int3
     const int64_t r0 = (int64_t)tile * SCAN_TILE + threadIdx.x * SCAN_ITEMS;
     int64_t v[SCAN_ITEMS];
     int64_t run = 0;
+    int longest = 0;
 #pragma unroll
     for (int t = 0; t < SCAN_ITEMS; ++t) {
         const int64_t r = r0 + t;
-        run += r < m ? row_nnz[r] : 0;
+        const int size = r < m ? row_nnz[r] : 0;
+        longest = max(longest, size);
+        run += size;
         v[t] = run;
+    }
+    // (read first: atomics of many wavefronts on one address take their turns)
+    if (__any(longest > NUM_CAP)) {
+        for (int d = 32; d > 0; d >>= 1) longest = max(longest, __shfl_xor(longest, d, 64));
+        if ((threadIdx.x & 63) == 0 &&
+            __hip_atomic_load(&ctl->widest, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < longest)
+            atomicMax(&ctl->widest, longest);
     }
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
     int64_t x = run;
@@ -554,61 +568,51 @@ __global__ __launch_bounds__(SCAN_THREADS) void k_add_scan(int32_t m, const int3
 
 // Numeric phase: per row, every entry adds alpha*a (A's first) or beta*b at
 // its position; columns written by every contributor (the same value).  The
-// values of NUM_CAP columns at a time are summed in the wavefront's LDS, in
-// FP64 (an LDS add of FP32 values serialises its lanes, see acc_bytes), and
-// copied out coalesced; rows of more than NUM_SEGMENTS times that sum in C's
-// own storage.  Entries of A are added before those of B, so a column with
-// one entry of each gets alpha*a + beta*b, each rounded once.  Two rows per
+// row's values are summed in LDS, in FP64 (an LDS add of FP32 values
+// serialises its lanes, see acc_bytes), and copied out coalesced.  Entries of A
+// are added before those of B, so a column with one entry of each gets
+// alpha*a + beta*b, each rounded once.  Two rows of up to 64 entries per
 // wavefront and step, their loads issued together and the next two rows'
 // pointers a step ahead: the kernel is bound by the latency of its two
 // dependent loads (1M rows of 30 + 30 entries, FP64: 0.62 ms with one row at
-// a time, 0.375 now, 4.7 TB/s, about what a copy of that size reaches).
-template <typename T>
-__device__ inline void add_long_row(const int32_t* __restrict__ aci, const T* __restrict__ av,
-                                    const int32_t* __restrict__ bci, const T* __restrict__ bv,
-                                    const int32_t* __restrict__ apos, const int32_t* __restrict__ bpos, T alpha,
-                                    T beta, uint32_t as, uint32_t ae, uint32_t bs, uint32_t be, int nc, int32_t* cc,
-                                    T* cv, double* s) {  // (unsigned: the step behind a row's end may pass 2^31)
-    const int lane = threadIdx.x % WAVE;
-    if (nc > NUM_SEGMENTS * NUM_CAP) {
-        for (int r = lane; r < nc; r += WAVE) cv[r] = T(0);
-        wg_fence();
-        wave_sync();
-        for (uint32_t t = as + lane; t < ae; t += WAVE) {
-            const int p = apos[t];
-            cc[p] = aci[t];
-            atomicAdd(&cv[p], alpha * av[t]);
-        }
-        wg_fence();
-        wave_sync();
-        for (uint32_t t = bs + lane; t < be; t += WAVE) {
-            const int p = bpos[t];
-            cc[p] = bci[t];
-            atomicAdd(&cv[p], beta * bv[t]);
-        }
-        wave_sync();
-        return;
+// a time, 0.375 now, 4.7 TB/s, about what a copy of that size reaches).  Rows
+// of more entries and up to NUM_CAP columns take a wavefront's LDS whole, one
+// after another; longer ones have a kernel of their own (k_add_num_wide).
+
+// U entries per lane from t0 on of one matrix's row (which ends at q1), added
+// at their positions less s0 by G lanes; positions outside [0, len) are left
+// out (ALL: none is).  Only the last U-th of them may pass the row's end.
+template <int G, int U, bool ALL, typename T>
+__device__ inline void add_chunk(uint32_t t0, uint32_t q1, const int32_t* __restrict__ pos,
+                                 const int32_t* __restrict__ ci, const T* __restrict__ v, T scale, int s0, int len,
+                                 int32_t* __restrict__ cc, double* s) {
+    const int lane = threadIdx.x % G;
+    int p[U], c[U];
+    T x[U];
+    const uint32_t q = t0 + lane;
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+        if (u < U - 1 || q + u * G < q1) p[u] = pos[q + u * G], c[u] = ci[q + u * G], x[u] = v[q + u * G];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        const int r = p[u] - s0;
+        if ((u == U - 1 && q + u * G >= q1) || (!ALL && (unsigned)r >= (unsigned)len)) continue;
+        cc[p[u]] = c[u];
+        atomicAdd(&s[r], (double)(scale * x[u]));
     }
-    for (int s0 = 0; s0 < nc; s0 += NUM_CAP) {
-        const int len = min(NUM_CAP, nc - s0);
-        for (int r = lane; r < len; r += WAVE) s[r] = 0.0;
-        wave_sync();
-        for (uint32_t t = as + lane; t < ae; t += WAVE) {
-            const int p = apos[t] - s0;
-            if ((unsigned)p >= (unsigned)len) continue;
-            cc[s0 + p] = aci[t];
-            atomicAdd(&s[p], (double)(alpha * av[t]));
-        }
-        wave_sync();
-        for (uint32_t t = bs + lane; t < be; t += WAVE) {
-            const int p = bpos[t] - s0;
-            if ((unsigned)p >= (unsigned)len) continue;
-            cc[s0 + p] = bci[t];
-            atomicAdd(&s[p], (double)(beta * bv[t]));
-        }
-        wave_sync();
-        for (int r = lane; r < len; r += WAVE) cv[s0 + r] = (T)s[r];
-        wave_sync();
+}
+
+// All entries [q0, q1) so, up to four per lane together.
+template <int G, bool ALL, typename T>
+__device__ inline void add_entries(uint32_t q0, uint32_t q1, const int32_t* __restrict__ pos,
+                                   const int32_t* __restrict__ ci, const T* __restrict__ v, T scale, int s0, int len,
+                                   int32_t* __restrict__ cc, double* s) {
+    for (uint32_t t0 = q0; t0 < q1; t0 += 4 * G) {  // (unsigned: the step behind a row's end may pass 2^31)
+        const uint32_t left = q1 - t0;
+        if (left > 3 * G) add_chunk<G, 4, ALL, T>(t0, q1, pos, ci, v, scale, s0, len, cc, s);
+        else if (left > 2 * G) add_chunk<G, 3, ALL, T>(t0, q1, pos, ci, v, scale, s0, len, cc, s);
+        else if (left > G) add_chunk<G, 2, ALL, T>(t0, q1, pos, ci, v, scale, s0, len, cc, s);
+        else add_chunk<G, 1, ALL, T>(t0, q1, pos, ci, v, scale, s0, len, cc, s);
     }
 }
 
@@ -648,10 +652,17 @@ __global__ __launch_bounds__(WAVE * ROWS_PER_WG) void k_add_num(int32_t m, const
 #pragma unroll
         for (int r = 0; r < R; ++r) small &= p[r].ae - p[r].as + p[r].be - p[r].bs <= WAVE;
         if (!small) {
-            for (int r = 0; r < R; ++r)
-                if (i0 + r < m)
-                    add_long_row<T>(aci, av, bci, bv, apos, bpos, alpha, beta, p[r].as, p[r].ae, p[r].bs, p[r].be,
-                                    p[r].nc, ccol + p[r].c0, cval + p[r].c0, s);
+            for (int r = 0; r < R; ++r) {
+                if (i0 + r >= m || p[r].nc > NUM_CAP) continue;
+                for (int t = lane; t < p[r].nc; t += WAVE) s[t] = 0.0;
+                wave_sync();
+                add_entries<WAVE, true, T>(p[r].as, p[r].ae, apos, aci, av, alpha, 0, p[r].nc, ccol + p[r].c0, s);
+                wave_sync();
+                add_entries<WAVE, true, T>(p[r].bs, p[r].be, bpos, bci, bv, beta, 0, p[r].nc, ccol + p[r].c0, s);
+                wave_sync();
+                for (int t = lane; t < p[r].nc; t += WAVE) cval[p[r].c0 + t] = (T)s[t];
+                wave_sync();
+            }
             continue;
         }
         // one entry per lane and row: A's, then B's
@@ -690,6 +701,62 @@ __global__ __launch_bounds__(WAVE * ROWS_PER_WG) void k_add_num(int32_t m, const
     }
 }
 
+// Numeric rows of more than NUM_CAP columns, a workgroup each, `cap` columns at
+// a time (what the longest row needs, at most WIDE_CAP, a quarter of the longest
+// possible: fewer leave room for more workgroups); launched where there are
+// such rows.  Every workgroup looks for them among m / grid rows, one per lane,
+// spread over the matrix.  One wavefront per row walked it once per 512
+// columns and, beyond 4096, summed in C's own storage; before that, beyond
+// 1024.  FP64 rows of 3500 entries, 1700 of them / 11 thousand, in order and
+// not, in us: 252 and 505 / 620 and 1353 so; 95 and 268 / 513 and 1862 before;
+// 49 and 56 / 288 and 378 in this kernel.  Of 700 entries, 57 thousand: 351 and
+// 522; 280 and 349; 262 and 327.
+template <typename T>
+__global__ __launch_bounds__(WIDE_THREADS) void k_add_num_wide(int32_t m, const int32_t* __restrict__ arp,
+                                                               const int32_t* __restrict__ aci,
+                                                               const T* __restrict__ av,
+                                                               const int32_t* __restrict__ brp,
+                                                               const int32_t* __restrict__ bci,
+                                                               const T* __restrict__ bv,
+                                                               const int32_t* __restrict__ apos,
+                                                               const int32_t* __restrict__ bpos,
+                                                               const int32_t* __restrict__ crp, T alpha, T beta,
+                                                               int32_t* __restrict__ ccol, T* __restrict__ cval,
+                                                               int cap) {
+    constexpr int G = WIDE_THREADS;
+    extern __shared__ double s[];
+    __shared__ int32_t rows[G];
+    __shared__ int count;
+    const int tid = threadIdx.x;
+    for (int64_t r0 = blockIdx.x; r0 < m; r0 += (int64_t)G * gridDim.x) {
+        if (tid == 0) count = 0;
+        __syncthreads();
+        const int64_t i = r0 + (int64_t)tid * gridDim.x;
+        if (i < m && crp[i + 1] - crp[i] > NUM_CAP) rows[atomicAdd(&count, 1)] = (int32_t)i;
+        __syncthreads();
+        for (int k = 0; k < count; ++k) {
+            const int row = rows[k];
+            const uint32_t as = arp[row], ae = arp[row + 1], bs = brp[row], be = brp[row + 1];
+            const int c0 = crp[row], nc = crp[row + 1] - c0;
+            int32_t* cc = ccol + c0;
+            for (int s0 = 0; s0 < nc; s0 += cap) {
+                const int len = min(cap, nc - s0);
+                for (int t = tid; t < len; t += G) s[t] = 0.0;
+                __syncthreads();
+                if (nc <= cap) add_entries<G, true, T>(as, ae, apos, aci, av, alpha, s0, len, cc, s);
+                else add_entries<G, false, T>(as, ae, apos, aci, av, alpha, s0, len, cc, s);
+                __syncthreads();
+                if (nc <= cap) add_entries<G, true, T>(bs, be, bpos, bci, bv, beta, s0, len, cc, s);
+                else add_entries<G, false, T>(bs, be, bpos, bci, bv, beta, s0, len, cc, s);
+                __syncthreads();
+                for (int t = tid; t < len; t += G) cval[c0 + s0 + t] = (T)s[t];
+                __syncthreads();
+            }
+        }
+        __syncthreads();
+    }
+}
+
 int64_t add_scan_tiles(int32_t m) { return ((int64_t)m + SCAN_TILE - 1) / SCAN_TILE; }
 
 }  // namespace
@@ -705,6 +772,7 @@ struct spg_add_s {
     int32_t* crp = nullptr;
     int64_t nnz_c = 0;
     bool have_sym = false;
+    int32_t widest = 0;      // longest row of C of more than NUM_CAP columns (0: no such row)
     void* buf = nullptr;     // apos | bpos | row_nnz | long list | tile status | control
     size_t cap = 0;
     AddCtl* hctl = nullptr;  // pinned copy of the control block
@@ -721,6 +789,22 @@ spg_status afail(spg_add h, spg_status s, const std::string& msg) {
 }
 
 size_t align256(size_t b) { return (b + 255) & ~(size_t)255; }
+
+template <typename T>
+void launch_num(spg_add h, T alpha, const void* a_vals, T beta, const void* b_vals, int32_t* c_col_idx, void* c_vals) {
+    const T *av = static_cast<const T*>(a_vals), *bv = static_cast<const T*>(b_vals);
+    T* cv = static_cast<T*>(c_vals);
+    const int grid = (int)std::min<int64_t>(((int64_t)h->m + ROWS_PER_WG - 1) / ROWS_PER_WG, (int64_t)h->n_cu * 32);
+    hipLaunchKernelGGL(k_add_num<T>, dim3(grid), dim3(WAVE * ROWS_PER_WG), 0, h->stream, h->m, h->arp, h->aci, av,
+                       h->brp, h->bci, bv, h->apos, h->bpos, h->crp, alpha, beta, c_col_idx, cv);
+    if (h->widest > 0) {
+        int cap = 2 * NUM_CAP;
+        while (cap < h->widest && cap < WIDE_CAP) cap *= 2;
+        hipLaunchKernelGGL(k_add_num_wide<T>, dim3((unsigned)std::min(h->m, h->n_cu * 8)), dim3(WIDE_THREADS),
+                           (size_t)cap * sizeof(double), h->stream, h->m, h->arp, h->aci, av, h->brp, h->bci, bv,
+                           h->apos, h->bpos, h->crp, alpha, beta, c_col_idx, cv, cap);
+    }
+}
 
 }  // namespace
 
@@ -836,6 +920,7 @@ spg_status spg_add_symbolic(spg_add h, int32_t m, int32_t n, const int32_t* a_ro
                                                      std::to_string(LONG_CAP) + " entries");
         if (c.err & AE_OVERFLOW) return afail(h, SPG_ERR_OVERFLOW, "nnz(C) exceeds the int32 range");
         h->nnz_c = m > 0 ? c.nnz_c : 0;
+        h->widest = c.widest;
         h->crp = c_row_ptr;
         h->have_sym = true;
         *nnz_c = h->nnz_c;
@@ -854,17 +939,8 @@ spg_status spg_add_numeric(spg_add h, spg_dtype dt, double alpha, const void* a_
         if ((h->annz > 0 && !a_vals) || (h->bnnz > 0 && !b_vals)) return afail(h, SPG_ERR_ARG, "null input values");
         if (h->nnz_c > 0 && (!c_col_idx || !c_vals)) return afail(h, SPG_ERR_ARG, "null output");
         if (h->m == 0) return SPG_OK;
-        const int grid = (int)std::min<int64_t>(((int64_t)h->m + ROWS_PER_WG - 1) / ROWS_PER_WG, (int64_t)h->n_cu * 32);
-        if (dt == SPG_F64)
-            hipLaunchKernelGGL(k_add_num<double>, dim3(grid), dim3(WAVE * ROWS_PER_WG), 0, h->stream, h->m, h->arp,
-                               h->aci, static_cast<const double*>(a_vals), h->brp, h->bci,
-                               static_cast<const double*>(b_vals), h->apos, h->bpos, h->crp, alpha, beta, c_col_idx,
-                               static_cast<double*>(c_vals));
-        else
-            hipLaunchKernelGGL(k_add_num<float>, dim3(grid), dim3(WAVE * ROWS_PER_WG), 0, h->stream, h->m, h->arp,
-                               h->aci, static_cast<const float*>(a_vals), h->brp, h->bci,
-                               static_cast<const float*>(b_vals), h->apos, h->bpos, h->crp, (float)alpha,
-                               (float)beta, c_col_idx, static_cast<float*>(c_vals));
+        if (dt == SPG_F64) launch_num<double>(h, alpha, a_vals, beta, b_vals, c_col_idx, c_vals);
+        else launch_num<float>(h, (float)alpha, a_vals, (float)beta, b_vals, c_col_idx, c_vals);
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return afail(h, SPG_ERR_HIP, std::string("numeric launch: ") + hipGetErrorString(e));
         return SPG_OK;
