@@ -129,7 +129,10 @@ typedef enum {
        when a row's LDS level fills).  With 1..3 the numeric phase leaves each
        row of C in hash order rather than ascending column order, and
        spg_numeric_jacobi is not available (SPG_ERR_UNSUPPORTED). */
-    SPG_OPT_METHOD = 12
+    SPG_OPT_METHOD = 12,
+    /* looks at an empty queue slot after which a wait of spg_batch_run_queued
+       is given up, 0..2^26 (default 2^26: some seconds); see there */
+    SPG_OPT_QUEUE_POLLS = 13
 } spg_option;
 
 #define SPG_NTIER 10
@@ -388,12 +391,19 @@ spg_status spg_batch_tune(spg_batch b, const void* a_val_pool, const void* b_val
        pointer block left unwritten);
      stamps: device int64[2 * count] or NULL: per product the device clock
        (wall_clock64, 100 MHz) when its first work item started and when its
-       last ended. */
+       last ended.
+   No wait of the kernel is without end: one that finds its queue slot empty
+   SPG_OPT_QUEUE_POLLS times gives up, its item is left out and every other
+   wait ends as well.  A run with such a wait leaves products incomplete;
+   spg_batch_get_stats reports it. */
 spg_status spg_batch_run_queued(spg_batch b, const void* a_val_pool, const void* b_val_pool, int32_t* c_row_ptr,
                                 int32_t* c_col, void* c_val, int64_t capacity, int64_t* c_offsets, int64_t* stamps);
 
 /* Statistics of the batch's last planned or tuned symbolic run and of its
-   numeric launches (per-class rows, products, times when timing is on). */
+   numeric launches (per-class rows, products, times when timing is on).  The
+   first call after spg_batch_run_queued waits for the batch's stream; it and
+   the following ones, until the next spg_batch_run_queued, return SPG_ERR_HIP
+   if a wait of the queued runs since the last such report was given up. */
 spg_status spg_batch_get_stats(spg_batch b, spg_stats* out, int32_t size);
 
 /* ---- sparse matrix addition C = alpha*A + beta*B (section 2.3) ----------

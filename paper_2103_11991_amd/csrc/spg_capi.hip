@@ -60,6 +60,7 @@ struct spg_handle_s {
     int lds_limit = 65536;
     int mlp_margin_milli = 500;
     int keep_features = 0;
+    int queue_polls = QUEUE_POLLS;
     int64_t list_limit_mb = 8192;
     int merge_classes = 1;
     int tiled_global = 1;
@@ -1141,6 +1142,10 @@ spg_status spg_set_option(spg_handle h, int32_t opt, int64_t val) {
             if (val < 0 || val > 3) return fail(h, SPG_ERR_ARG, "method must be 0..3");
             h->method = (int)val;
             break;
+        case SPG_OPT_QUEUE_POLLS:
+            if (val < 0 || val > QUEUE_POLLS) return fail(h, SPG_ERR_ARG, "queue polls must be 0..2^26");
+            h->queue_polls = (int)val;
+            break;
         case SPG_OPT_LIST_LIMIT_MB:
             if (val < 1 || val > 16383) return fail(h, SPG_ERR_ARG, "list memory limit must be 1..16383 MiB");
             h->list_limit_mb = val;
@@ -1257,6 +1262,9 @@ struct spg_batch_s {
     hipGraphExec_t q_exec = nullptr;
     const void* qg_key[7] = {};
     int64_t qg_cap = -1;
+    int qg_polls = -1;
+    bool q_unread = false;  // queued runs whose failure flag the host has not read
+    bool q_failed = false;  // a wait of theirs gave up
 };
 
 namespace {
@@ -1331,6 +1339,7 @@ spg_status queue_prepare(spg_batch b) {
     SPG_TRY(ensure(h, b->q_row_off, ((size_t)cnt + 1) * 8));
     SPG_TRY(ensure(h, b->q_crp_off, (size_t)std::max(cnt, 1) * 8));
     SPG_TRY(ensure(h, b->q_ctl, sizeof(QueueCtl)));
+    HIP_TRY(h, hipMemsetAsync(b->q_ctl.p, 0, sizeof(QueueCtl), b->stream));
     SPG_TRY(ensure(h, b->q_left, (size_t)std::max(cnt, 1) * 4));
     SPG_TRY(ensure(h, b->q_queue, (size_t)std::max<int64_t>(b->q_items, 1) * 8));
     // the rows' bitmaps from symbolic to numeric, when they take at most 4 GiB
@@ -1646,12 +1655,13 @@ spg_status spg_batch_run_queued(spg_batch b, const void* a_val_pool, const void*
         if (b->count == 0) return SPG_OK;
         const void* key[7] = {a_val_pool, b_val_pool, c_row_ptr, c_col, c_val, c_offsets, stamps};
         const bool same = b->q_exec && std::equal(std::begin(key), std::end(key), std::begin(b->qg_key)) &&
-                          b->qg_cap == capacity;
+                          b->qg_cap == capacity && b->qg_polls == h->queue_polls;
         if (!same) {
             drop_queue_graph(b);
             QueueArgs a{};
             a.count = b->count;
             a.rb = QUEUE_ROWS_PER_ITEM;
+            a.polls = h->queue_polls;
             a.n_items = b->q_items;
             a.item_off = b->q_item_off.as<int64_t>();
             a.row_off = b->q_row_off.as<int64_t>();
@@ -1681,9 +1691,12 @@ spg_status spg_batch_run_queued(spg_batch b, const void* a_val_pool, const void*
             }
             std::copy(std::begin(key), std::end(key), std::begin(b->qg_key));
             b->qg_cap = capacity;
+            b->qg_polls = h->queue_polls;
         }
+        b->q_failed = false;
         hipError_t e = hipGraphLaunch(b->q_exec, b->stream);
         if (e != hipSuccess) return bfail(b, SPG_ERR_HIP, std::string("graph launch: ") + hipGetErrorString(e));
+        b->q_unread = true;
         return SPG_OK;
     } catch (...) {
         return bfail(b, SPG_ERR_HIP, "host exception");
@@ -1692,6 +1705,16 @@ spg_status spg_batch_run_queued(spg_batch b, const void* a_val_pool, const void*
 
 spg_status spg_batch_get_stats(spg_batch b, spg_stats* out, int32_t size) {
     if (!b) return SPG_ERR_ARG;
+    if (b->q_unread) {
+        int64_t failed = 0, *flag = &b->q_ctl.as<QueueCtl>()->failed;
+        HIP_TRY(b->h, hipMemcpyAsync(&failed, flag, sizeof(failed), hipMemcpyDeviceToHost, b->stream));
+        HIP_TRY(b->h, hipStreamSynchronize(b->stream));
+        if (failed) HIP_TRY(b->h, hipMemsetAsync(flag, 0, sizeof(failed), b->stream));
+        b->q_unread = false;
+        b->q_failed = failed != 0;
+    }
+    if (b->q_failed)
+        return bfail(b, SPG_ERR_HIP, "a wait of a queued run was given up: products of that run are incomplete");
     return spg_get_stats(b->h, out, size);
 }
 

@@ -535,11 +535,13 @@ struct QueueCtl {
     int64_t head;   // next queue slot to take
     int64_t tail;   // numeric slots appended so far
     int64_t used;   // entries of the C pools handed out (bump allocator)
-    int64_t pad;    // nonzero if a numeric slot never filled (a wait gave up)
+    int64_t gave_up;  // nonzero if a numeric slot never filled in this run (a wait gave up)
+    int64_t failed;   // the same of any run since the host last looked
 };
 struct QueueArgs {
     int32_t count;              // products
     int32_t rb;                 // rows per work item
+    int32_t polls;              // looks at an empty slot before a wait is given up
     int64_t n_items;            // symbolic items (as many numeric ones)
     const int64_t* item_off;    // count + 1: first symbolic item of each product
     const int64_t* row_off;     // count + 1: first packed row of each product
@@ -569,6 +571,7 @@ struct QueueArgs {
     const int4* bhdr;           // per B row {start, length, run start, run count}
     int64_t bnnz;               // entries of B's pools
 };
+constexpr int QUEUE_POLLS = 1 << 26;   // of a wait, by default (and at most): some seconds
 constexpr int QUEUE_MAX_WORDS = 128;  // widest row range the queued kernel holds (4096 columns)
 size_t queue_lds_bytes(int wmax, int vmax, int elem_bytes);
 void launch_queue(hipStream_t s, const QueueArgs& a, int elem_bytes, int grid);

@@ -47,7 +47,6 @@ namespace {
 constexpr int QWAVES = 4;  // wavefronts per workgroup
 constexpr int RG = 32;     // lanes per row (two rows per wavefront)
 constexpr int QGROUPS = QWAVES * 64 / RG;
-constexpr int64_t QUEUE_SPIN_LIMIT = (int64_t)1 << 26;
 
 __device__ inline void qwave_sync() {
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
@@ -496,15 +495,17 @@ __global__ __launch_bounds__(64 * QWAVES) __attribute__((amdgpu_waves_per_eu(6))
             if (tid == 0) {
                 // bounded wait (seconds of sleeps): a slot that never fills
                 // (which the item counts rule out) ends as a skipped item and
-                // raises the queue's failure flag, which ends every other wait
+                // raises the queue's failure flags: one ends every other wait, the
+                // other is for the host
                 int64_t e;
-                int64_t spins = 0;
-                while ((e = ld_dev(&a.queue[k - n])) == 0 && spins < QUEUE_SPIN_LIMIT) {
+                int32_t polls = 0;
+                while ((e = ld_dev(&a.queue[k - n])) == 0 && polls < a.polls) {
                     __builtin_amdgcn_s_sleep(2);
-                    if ((++spins & 1023) == 0 && ld_dev(&a.qc->pad)) break;  // another wait gave up: so does this one
+                    if ((++polls & 1023) == 0 && ld_dev(&a.qc->gave_up)) break;  // another wait gave up: so does this one
                 }
                 if (e == 0) {
-                    atomicOr((unsigned long long*)&a.qc->pad, 1ull);
+                    atomicOr((unsigned long long*)&a.qc->gave_up, 1ull);
+                    atomicOr((unsigned long long*)&a.qc->failed, 1ull);
                     e = -1;  // product 0, block 0, skipped
                 }
                 s_e = e;
@@ -545,7 +546,7 @@ __global__ __launch_bounds__(64 * QWAVES) __attribute__((amdgpu_waves_per_eu(6))
 // time stamps reset; products without rows finished at once.
 __global__ void k_queue_init(QueueArgs a) {
     const int64_t g = blockIdx.x * (int64_t)blockDim.x + threadIdx.x, stride = (int64_t)gridDim.x * blockDim.x;
-    if (g == 0) a.qc->head = 0, a.qc->tail = 0, a.qc->used = 0, a.qc->pad = 0;
+    if (g == 0) a.qc->head = 0, a.qc->tail = 0, a.qc->used = 0, a.qc->gave_up = 0;
     for (int64_t q = g; q < a.n_items; q += stride) a.queue[q] = 0;
     for (int64_t p = g; p < a.count; p += stride) {
         a.sym_left[p] = (int32_t)(a.item_off[p + 1] - a.item_off[p]);

@@ -418,10 +418,14 @@ class SpGEMMBatch:
                                   b_vals.data_ptr() if b_vals.numel() else 0, self.q_rp.data_ptr(),
                                   self.q_col.data_ptr(), self.q_val.data_ptr(), capacity,
                                   self.q_offsets.data_ptr(), self.q_stamps.data_ptr() if stamps else 0)
+        self.q_checked = False
         cur.wait_stream(self.stream)
 
     def product_queued(self, i: int):
         """(row_ptr from 0, col_idx, values) of C_i after run_queued, or None if it did not fit."""
+        if not self.q_checked:
+            _lib.spg_batch_get_stats(self.b)  # raises where a wait of the run was given up
+            self.q_checked = True
         off = int(self.q_offsets[i].item())
         if off < 0:
             return None
