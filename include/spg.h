@@ -155,7 +155,8 @@ typedef struct {
     int32_t binning;                    /* SPG_OPT_BINNING of the last symbolic call */
     float sym_ms;                       /* GPU time of the last symbolic call (timing on) */
     float num_ms;                       /* GPU time of the last numeric call (timing on) */
-    float sym_class_ms[SPG_NCLASS];     /* per symbolic class launch (timing on) */
+    float sym_class_ms[SPG_NCLASS];     /* per symbolic class launch (timing on); a launch of several
+                                           classes (one-wait calls) counts in the first of them with rows */
     float num_class_ms[SPG_NCLASS];     /* per numeric class launch (timing on) */
     float analysis_ms;                  /* row analysis and binning (timing on) */
     float scan_ms;                      /* row-pointer scan (timing on) */

@@ -113,6 +113,7 @@ struct spg_handle_s {
     bool ev_made = false;
     bool sym_timed = false, num_timed = false;
     bool sym_cls_timed[NCLS] = {}, num_cls_timed[NCLS] = {};
+    int sym_launch_last[NTIER] = {};  // last tier of the symbolic launch timed under direct class t
     // numeric class launches: two event sets used in turn; a set's previous
     // pair is read (long complete by then) when the set is reused or stats
     // are read, and summed per class
@@ -617,8 +618,9 @@ spg_status sym_stage_rows(spg_handle h, int32_t* c_row_ptr, bool read_back = fal
     } else if (h->single_wait && !host_sized) {
         // three to five persistent launches for the LDS tiers; each reads its
         // rows from the control block the grouping kernel wrote, so none waits
-        // for the host.  Tiers above the LDS limit never get rows.  A launch's
-        // time is kept in its first tier's direct class.
+        // for the host.  Tiers above the LDS limit never get rows.  A launch is
+        // timed under its first tier's direct class and its last tier kept, as
+        // which of its classes have rows is not known here.
         int t_last = -1;
         while (t_last + 1 < TIER_GLOBAL && tier_bytes(t_last + 1) <= h->cfg.lds_limit) ++t_last;
         // (128- and 512-lane rows run in the launch of twice the lanes, which
@@ -643,6 +645,7 @@ spg_status sym_stage_rows(spg_handle h, int32_t* c_row_ptr, bool read_back = fal
             launch_sym_tiers(s, a, t, t1, m, h->n_cu);
             rec(h, EV_SYMCLS + 2 * t + 1);
             h->sym_cls_timed[t] = h->timing == 1;
+            h->sym_launch_last[t] = t1;
             t = t1 + 1;
         }
         if (h->sym_global_grid > 0) {
@@ -1014,6 +1017,7 @@ spg_status spg_symbolic(spg_handle h, int32_t* c_row_ptr, int64_t* nnz_c) {
         if (h->timing) SPG_TRY(make_events(h));
         h->sym_timed = h->timing == 1;
         std::fill(std::begin(h->sym_cls_timed), std::end(h->sym_cls_timed), false);
+        std::fill(std::begin(h->sym_launch_last), std::end(h->sym_launch_last), -1);
         SPG_TRY(sym_prepare(h));
         rec(h, EV_SYM0);
         sym_stage_analysis(h);
@@ -1181,6 +1185,14 @@ spg_status spg_get_stats(spg_handle h, spg_stats* out, int32_t size) {
             st.mlp_ms = st.binning == 1 ? elapsed(h, EV_MLP0, EV_MLP1) : 0.f;
             for (int c = 0; c < NCLS; ++c)
                 st.sym_class_ms[c] = h->sym_cls_timed[c] ? elapsed(h, EV_SYMCLS + 2 * c, EV_SYMCLS + 2 * c + 1) : 0.f;
+            // a launch of several tiers: under the first of its classes that has rows
+            for (int t = 0; t < NTIER; ++t) {
+                if (h->sym_launch_last[t] < t) continue;
+                int first = t;
+                for (int c = NCLS; c-- > 0;)
+                    if (st.sym_rows[c] && c % NTIER >= t && c % NTIER <= h->sym_launch_last[t]) first = c;
+                std::swap(st.sym_class_ms[t], st.sym_class_ms[first]);
+            }
         }
         if (h->num_timed) {
             st.num_ms = h->timing == 1 ? elapsed(h, EV_NUM0, EV_NUM1) : 0.f;
