@@ -9,18 +9,20 @@ from gpu_util import run_gpu
 pytestmark = pytest.mark.gpu
 
 
-def _long_rows():
-    rng = np.random.default_rng(5)
-    lens = rng.integers(100, 160, size=1500)
-    ci = np.concatenate([rng.choice(700, size=int(l), replace=False) for l in lens])
-    A = gen.csr_from_rows_cols(1500, 700, np.repeat(np.arange(1500), lens), ci, np.ones(ci.size))
-    return A, gen.csr_from_rows_cols(700, 1500, np.repeat(np.arange(700), 40), rng.permuted(
-        np.tile(np.arange(1500), (700, 1)), axis=1)[:, :40].ravel(), np.ones(28000))
+def _matrix(m, n, per_row, seed):
+    rng = np.random.default_rng(seed)
+    ci = np.concatenate([rng.choice(n, size=per_row, replace=False) for _ in range(m)])
+    return gen.csr_from_rows_cols(m, n, np.repeat(np.arange(m), per_row), ci, np.ones(ci.size))
 
 
-@pytest.mark.parametrize("which,binning", [("lap2d", 2), ("lap2d", 0), ("long", 2), ("long", 0)])
-def test_times_lie_in_classes_with_rows(which, binning):
-    A, B = (gen.laplace2d_5pt(64),) * 2 if which == "lap2d" else _long_rows()
+# rows of the direct classes 0, 4, 6 and 7, and of class 11 (two-level, second tier)
+@pytest.mark.parametrize("binning", [2, 0])
+@pytest.mark.parametrize("case", ["lap2d", (20, 30000, 20), (60, 30000, 40), (130, 1500, 40), (6, 200000, 8)])
+def test_times_lie_in_classes_with_rows(case, binning):
+    if case == "lap2d":
+        A = B = gen.laplace2d_5pt(64)
+    else:
+        A, B = _matrix(1500, 700, case[0], 1), _matrix(700, case[1], case[2], 2)
     op = run_gpu(A, B, binning=binning, timing=1)[3]
     for _ in range(3):  # (the first call's times hold the loading of the kernels)
         op.symbolic()
