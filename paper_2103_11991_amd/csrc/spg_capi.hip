@@ -1025,6 +1025,8 @@ spg_status spg_symbolic(spg_handle h, int32_t* c_row_ptr, int64_t* nnz_c) {
             launch_fill_i32(h->stream, c_row_ptr, 0, 1);
             SPG_TRY(sync_ctl(h));
             h->sym_waits = 1;
+            h->geom = *h->hctl;
+            h->tiled = false;
             rec(h, EV_SYM1);
             *nnz_c = 0;
             h->nnz_c = 0;
