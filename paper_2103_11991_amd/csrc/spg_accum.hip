@@ -728,9 +728,10 @@ constexpr int SLOT_MAX = 16;
 // the mask OR-ed in, and the bits that were not yet set (and blocks that were
 // empty) are counted from the value the atomic OR returns.
 
-// One row of the symbolic phase in a table of MODE in the row's LDS share (with
-// SLOTS: with a slot table and the sparse direct table where they apply)
-// (`bytes` of table, then the staging; d = the slot's descriptor {row, A start, A end, list offset}).
+// One row of the symbolic phase in a table of MODE in the row's LDS share
+// (`bytes` of table, then the staging; d = the slot's descriptor {row, A start,
+// A end, list offset}).  SLOTS: with a slot table and the sparse direct table
+// where they apply.
 template <int G, int MODE, bool SLOTS>
 __device__ __forceinline__ void sym_row(const SymArgs& a, const int bytes, const int4 d, const int sub, uint32_t* smem,
                                         int* red, int* occ, int* ovf) {
@@ -1785,11 +1786,11 @@ __global__ __launch_bounds__(WIDE_THREADS) void k_num_wide(NumArgs a) {
 
 // ---------------------------------------------------- tiled global path
 // Long rows of the numeric phase, cut by column tile.  B's columns are split
-// into tiles of W = TILE_BYTES / (element size) columns, and every B row
-// keeps the offsets where its entries of each tile begin (built once per
-// symbolic result; the entries of a row must be grouped by tile, which holds
-// for rows stored in ascending column order).  A work item is one (row, tile)
-// pair: its products are exactly the products of the B rows' entries in the
+// into tiles of W = TILE_BYTES / 8 columns (sums are FP64 for both value
+// types), and every B row keeps the offsets where its entries of each tile
+// begin (built once per symbolic result; the entries of a row must be grouped
+// by tile, which holds for rows stored in ascending column order).  A work
+// item is one (row, tile) pair: its products are exactly the products of the B rows' entries in the
 // tile, summed into a dense LDS window indexed by column minus the tile's
 // first column (the paper's dense accumulator restricted to one tile), so no
 // product is walked twice and no rank is looked up per product.  The row's

@@ -1049,7 +1049,7 @@ spg_status spg_symbolic(spg_handle h, int32_t* c_row_ptr, int64_t* nnz_c) {
         }
         SPG_TRY(sym_stage_rows(h, c_row_ptr, true));
         rec(h, EV_SYM1);
-        // the one wait: the control block copied right after the row-pointer
+        // the one wait: the control block published right after the row-pointer
         // scan gives nnz(C), input errors and the numeric launch geometry
         // (the numeric grouping may still run; numeric is ordered after it)
         SPG_TRY(wait_ctl(h));

@@ -163,7 +163,12 @@ __host__ __device__ inline int32_t num_twolevel_bytes(int32_t words, int32_t blo
 }
 // Symbolic rows of one wavefront: widest range whose direct table a launch
 // makes room for, in words (with the staging, seven workgroups of four rows
-// fit a compute unit).
+// fit a compute unit).  27-point stencils, symbolic phase, sparse direct /
+// two-level table: 80^3 0.50 / 0.54 ms, 90^3 0.66 / 0.73, 100^3 (1264 words)
+// 0.93 / 0.96; with room for 1536 words and six workgroups 101^3 (1289) 1.02 /
+// 0.98, 105^3 1.17 / 1.11, 110^3 (1526) 1.33 / 1.27.  The widest row of the
+// product decides, as all rows of a launch have the same LDS: with one row past
+// the line all take the two-level table and these 4 to 11 % longer.
 constexpr int SPARSE_WORDS = 1280;
 // LDS table bytes per row of a symbolic class launch: its tier's; two-level rows
 // of one wavefront get what the direct table of the widest row takes, where that
@@ -304,8 +309,9 @@ inline void merge_classes(const int32_t* hist, uint8_t* remap, int32_t* merged, 
     for (int mode = 0; mode < 3; ++mode) merge_classes_mode(hist, remap, merged, mode, enable);
 }
 
-// Device-side control block: counters and histograms the host reads back
-// in one copy at each of symbolic's two synchronisation points.
+// Device-side control block: counters and histograms.  At each of symbolic's
+// one or two waits a kernel writes it to the host's pinned copy, whose last
+// word the host polls.
 struct Control {
     int32_t err;
     int32_t overflow_rows;        // learned binning: rows queued for retry
