@@ -153,16 +153,16 @@ __device__ inline int entry_of(const int* pre, int cnt, int q) {
 template <typename T>
 __device__ inline void row_walk(const QueueArgs& a, int64_t r, int base, const Win_<T>& w) {
     const int lane = threadIdx.x & (RG - 1);
-    const uint32_t a0 = a.arp[r], a1 = a.arp[r + 1];  // unsigned: the step behind a row's end may pass 2^31
-    for (uint32_t e0 = a0; e0 < a1; e0 += RG) {
+    const int a0 = a.arp[r], a1 = a.arp[r + 1];
+    for (int left = a1 - a0; left > 0; left -= RG) {  // (an index stepped past the row's end may pass 2^31)
         // the chunk's entries: unconditional loads (index clamped into the row)
-        const bool in_row = e0 + lane < a1;
-        const int j = a.aci[min(e0 + lane, a1 - 1)];
+        const bool in_row = lane < left;
+        const int j = a.aci[a1 - left + min(lane, left - 1)];
         const int s0 = a.brp[j];
         const int len = in_row ? a.brp[j + 1] - s0 : 0;
         const int incl = wscan_incl(len);
         const int total = __shfl(incl, RG - 1, RG);
-        const int cnt = min((uint32_t)RG, a1 - e0);
+        const int cnt = min(RG, left);
         w.pre[lane] = incl - len, w.st[lane] = s0;
         qwave_sync();
         for (int Q = 0; Q < total; Q += QU * RG) {
@@ -212,7 +212,7 @@ template <typename T>
 __device__ inline QGroup<T> load_group(const int32_t* __restrict__ bci, const T* __restrict__ bv, int64_t bnnz,
                                        int b) {
     QGroup<T> g;
-    if ((int64_t)b + 4 <= bnnz) {
+    if (b <= (int)(bnnz - 4)) {
         const QI4 c = *reinterpret_cast<const QI4*>(bci + b);
         g.c[0] = c.x, g.c[1] = c.y, g.c[2] = c.z, g.c[3] = c.w;
         if constexpr (sizeof(T) == 8) {
@@ -227,7 +227,7 @@ __device__ inline QGroup<T> load_group(const int32_t* __restrict__ bci, const T*
         // the pools' last group: every index clamped to the last entry
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
-            const int64_t q = min<int64_t>((int64_t)b + j, bnnz - 1);
+            const int q = b + min(j, (int)(bnnz - 1) - b);
             g.c[j] = bci[q];
             g.y[j] = bv[q];
         }
@@ -242,12 +242,12 @@ __device__ inline QGroup<T> load_group(const int32_t* __restrict__ bci, const T*
 template <typename T>
 __device__ inline void row_walk_num(const QueueArgs& a, int64_t r, int base, const Win_<T>& w) {
     const int lane = threadIdx.x & (RG - 1);
-    const uint32_t a0 = a.arp[r], a1 = a.arp[r + 1];  // unsigned: the step behind a row's end may pass 2^31
+    const int a0 = a.arp[r], a1 = a.arp[r + 1];
     const T* av = reinterpret_cast<const T*>(a.av);
     const T* bv = reinterpret_cast<const T*>(a.bv);
-    for (uint32_t e0 = a0; e0 < a1; e0 += RG) {
-        const bool in_row = e0 + lane < a1;
-        const uint32_t e = min(e0 + lane, a1 - 1);
+    for (int left = a1 - a0; left > 0; left -= RG) {  // (an index stepped past the row's end may pass 2^31)
+        const bool in_row = lane < left;
+        const int e = a1 - left + min(lane, left - 1);
         const int j = a.aci[e];
         const T x = av[e];
         const int s0 = a.brp[j];
@@ -255,7 +255,7 @@ __device__ inline void row_walk_num(const QueueArgs& a, int64_t r, int base, con
         const int ng = (len + 3) >> 2;
         const int incl = wscan_incl(ng);
         const int total = __shfl(incl, RG - 1, RG);
-        const int cnt = min((uint32_t)RG, a1 - e0);
+        const int cnt = min(RG, left);
         w.pre[lane] = incl - ng, w.st[lane] = s0, w.len[lane] = len;
         w.av[lane] = x;
         qwave_sync();
@@ -288,14 +288,14 @@ __device__ inline void row_walk_num(const QueueArgs& a, int64_t r, int base, con
 template <typename T>
 __device__ inline void row_walk_runs(const QueueArgs& a, int64_t r, int base, const Win_<T>& w) {
     const int lane = threadIdx.x & (RG - 1);
-    const uint32_t a0 = a.arp[r], a1 = a.arp[r + 1];  // unsigned: the step behind a row's end may pass 2^31
-    for (uint32_t e0 = a0; e0 < a1; e0 += RG) {
-        const bool in_row = e0 + lane < a1;
-        const int4 h = a.bhdr[a.aci[min(e0 + lane, a1 - 1)]];
+    const int a0 = a.arp[r], a1 = a.arp[r + 1];
+    for (int left = a1 - a0; left > 0; left -= RG) {  // (an index stepped past the row's end may pass 2^31)
+        const bool in_row = lane < left;
+        const int4 h = a.bhdr[a.aci[a1 - left + min(lane, left - 1)]];
         const int s0 = h.z, len = in_row ? h.w : 0;
         const int incl = wscan_incl(len);
         const int total = __shfl(incl, RG - 1, RG);
-        const int cnt = min((uint32_t)RG, a1 - e0);
+        const int cnt = min(RG, left);
         w.pre[lane] = incl - len, w.st[lane] = s0;
         qwave_sync();
         for (int Q = 0; Q < total; Q += QU * RG) {
